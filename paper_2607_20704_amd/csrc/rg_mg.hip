@@ -12,6 +12,8 @@
 // with the 7-point Laplacian; every value is formed in the same order as in
 // the serial reference so that the results agree bit for bit.
 #include "rg_internal.hpp"
+#include "rg_mg_brick.hpp"
+#include "rg_mg_tail.hpp"
 
 namespace rg {
 namespace {
@@ -42,8 +44,6 @@ __device__ __forceinline__ double sum6(const double *__restrict__ phi, const int
 }
 
 // cells of one colour: even (0, 3, 5, 6) or odd (1, 2, 4, 7) coordinate sum
-__constant__ int c_colour[2][4] = {{0, 3, 5, 6}, {1, 2, 4, 7}};
-
 // Gauss-Seidel update of cell c of oct o
 __device__ __forceinline__ void smooth_cell(double *phi, const double *f, const int32_t *__restrict__ nbr27, int64_t o,
                                             int c, double h2)
@@ -64,14 +64,6 @@ __device__ __forceinline__ void residual_cell(const double *phi, const double *f
     r[cell] = f[cell] - lap;
 }
 
-// coarse right-hand side at fine oct o's father cell: the mean of the 8
-// fine residuals, summed pairwise in cell order
-__device__ __forceinline__ void restrict_oct(const double *r, double *f, const int32_t *__restrict__ father, int64_t o)
-{
-    const double *c = r + 8 * o;
-    f[father[o]] = 0.125 * (((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7])));
-}
-
 // one colour pass of Gauss-Seidel over the octs [ob, oe): four cells per oct
 __global__ void k_mg_smooth(double *phi, const double *__restrict__ f, const int32_t *__restrict__ nbr27, int64_t ob,
                             int64_t oe, double h2, int colour)
@@ -79,7 +71,7 @@ __global__ void k_mg_smooth(double *phi, const double *__restrict__ f, const int
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     const int64_t o = ob + (t >> 2);
     if (o >= oe) return;
-    smooth_cell(phi, f, nbr27, o, c_colour[colour][t & 3], h2);
+    smooth_cell(phi, f, nbr27, o, colour_cell(colour, static_cast<int>(t & 3)), h2);
 }
 
 __global__ void k_mg_residual(const double *__restrict__ phi, const double *__restrict__ f, double *__restrict__ r,
@@ -89,20 +81,6 @@ __global__ void k_mg_residual(const double *__restrict__ phi, const double *__re
     const int64_t o = ob + (t >> 3);
     if (o >= oe) return;
     residual_cell(phi, f, r, nbr27, o, static_cast<int>(t & 7), h2);
-}
-
-__global__ void k_mg_restrict(const double *__restrict__ r, double *__restrict__ f, const int32_t *__restrict__ father,
-                              int64_t ob, int64_t oe)
-{
-    const int64_t o = ob + int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (o >= oe) return;
-    restrict_oct(r, f, father, o);
-}
-
-__global__ void k_mg_zero(double *p, int64_t b, int64_t e)
-{
-    const int64_t i = b + int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < e) p[i] = 0.0;
 }
 
 // phi of each fine cell += trilinear interpolation of the coarse correction:
@@ -150,90 +128,6 @@ __global__ void k_mg_prolong(double *phi, const int32_t *__restrict__ nbr27, con
     prolong_cell(phi, nbr27, father, o, static_cast<int>(t & 7));
 }
 
-// The levels of at most kTailOcts octs (those below lfine's first such
-// level are smaller still) run their whole part of the V-cycle in one
-// workgroup: the same passes in the same order as the per-level launches,
-// separated by barriers, so the same bits.  Each launch (two per sweep, 100
-// for 50 sweeps on the coarsest level) costs a few microseconds of GPU time.
-constexpr int64_t kTailOcts = 512;
-constexpr int kTailThreads = 1024;
-
-struct MgTail {
-    double *phi, *f, *r;
-    const int32_t *nbr27, *father;
-    int64_t begin[RG_MAX_LEVEL + 2];
-    double h2[RG_MAX_LEVEL + 1];
-    int m0, lcoarse, nu1, nu2, ncoarse;
-};
-
-__device__ void tail_sweeps(const MgTail &A, int l, int sweeps)
-{
-    const int64_t ob = A.begin[l], n4 = 4 * (A.begin[l + 1] - ob);
-    for (int sw = 0; sw < sweeps; ++sw)
-        for (int colour = 0; colour < 2; ++colour) {
-            for (int64_t t = threadIdx.x; t < n4; t += blockDim.x)
-                smooth_cell(A.phi, A.f, A.nbr27, ob + (t >> 2), c_colour[colour][t & 3], A.h2[l]);
-            __syncthreads();
-        }
-}
-
-// The coarsest level's sweeps (50 by default, each pass depending on the
-// last) with its values staged in LDS when it holds at most kLdsCells cells:
-// the same update of each cell, read from and written to LDS.
-constexpr int kLdsCells = 1024;
-
-__device__ void tail_sweeps_lds(const MgTail &A, int l, int sweeps, double *sp, double *sf)
-{
-    const int64_t ob = A.begin[l], cb = 8 * ob, n = 8 * (A.begin[l + 1] - ob);
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-        sp[i] = A.phi[cb + i];
-        sf[i] = A.f[cb + i];
-    }
-    __syncthreads();
-    for (int sw = 0; sw < sweeps; ++sw)
-        for (int colour = 0; colour < 2; ++colour) {
-            for (int64_t t = threadIdx.x; t < n / 2; t += blockDim.x) {
-                const int64_t o = ob + (t >> 2);
-                const int c = c_colour[colour][t & 3];
-                int64_t nb[6];
-                face_cells(A.nbr27, o, c, nb);
-                const double s6 = ((((sp[nb[0] - cb] + sp[nb[1] - cb]) + sp[nb[2] - cb]) + sp[nb[3] - cb]) +
-                                   sp[nb[4] - cb]) + sp[nb[5] - cb];
-                const int64_t k = 8 * o + c - cb;
-                sp[k] = (s6 - A.h2[l] * sf[k]) / 6.0;
-            }
-            __syncthreads();
-        }
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) A.phi[cb + i] = sp[i];
-    __syncthreads();
-}
-
-__global__ __launch_bounds__(kTailThreads) void k_mg_tail(MgTail A)
-{
-    __shared__ double sp[kLdsCells], sf[kLdsCells];
-    for (int l = A.m0; l > A.lcoarse; --l) {
-        tail_sweeps(A, l, A.nu1);
-        const int64_t ob = A.begin[l], oe = A.begin[l + 1];
-        for (int64_t t = threadIdx.x; t < 8 * (oe - ob); t += blockDim.x)
-            residual_cell(A.phi, A.f, A.r, A.nbr27, ob + (t >> 3), static_cast<int>(t & 7), A.h2[l]);
-        __syncthreads();
-        for (int64_t o = ob + threadIdx.x; o < oe; o += blockDim.x) restrict_oct(A.r, A.f, A.father, o);
-        for (int64_t i = 8 * A.begin[l - 1] + threadIdx.x; i < 8 * A.begin[l]; i += blockDim.x) A.phi[i] = 0.0;
-        __syncthreads();
-    }
-    if (8 * (A.begin[A.lcoarse + 1] - A.begin[A.lcoarse]) <= kLdsCells)
-        tail_sweeps_lds(A, A.lcoarse, A.ncoarse, sp, sf);
-    else
-        tail_sweeps(A, A.lcoarse, A.ncoarse);
-    for (int l = A.lcoarse + 1; l <= A.m0; ++l) {
-        const int64_t ob = A.begin[l], oe = A.begin[l + 1];
-        for (int64_t t = threadIdx.x; t < 8 * (oe - ob); t += blockDim.x)
-            prolong_cell(A.phi, A.nbr27, A.father, ob + (t >> 3), static_cast<int>(t & 7));
-        __syncthreads();
-        tail_sweeps(A, l, A.nu2);
-    }
-}
-
 struct Mg {
     const rg_tree *t;
     double *phi, *f, *r;
@@ -241,13 +135,25 @@ struct Mg {
     hipStream_t s;
 };
 
-rg_status smooth(const Mg &m, int l, int sweeps)
+// Sweeps over level l >= 4, with prolong after adding the correction of the
+// level below: brick sweeps two by two (they go from phi to r and back; r's
+// entries of the level are free between residuals), the last of an odd number
+// in place, colour by colour.
+rg_status smooth(const Mg &m, int l, int sweeps, bool prolong = false)
 {
-    const int64_t ob = m.t->level_begin[l], oe = m.t->level_begin[l + 1];
-    const double h2 = ldexp(1.0, -2 * l);
-    for (int sw = 0; sw < sweeps; ++sw)
+    const rg_tree *t = m.t;
+    const int64_t ob = t->level_begin[l], oe = t->level_begin[l + 1];
+    const int pairs = sweeps & ~1;
+    if (prolong && pairs == 0) {
+        k_mg_prolong<<<grid_for(8 * (oe - ob), 256), 256, 0, m.s>>>(m.phi, t->d_nbr27, t->d_father_cell, ob, oe);
+        RG_TRY(launch_status("multigrid prolong"));
+    }
+    RG_TRY(mg_brick_sweeps(m.phi + 8 * ob, m.r + 8 * ob, m.f + 8 * ob,
+                           prolong ? m.phi + 8 * t->level_begin[l - 1] : nullptr, l, pairs, m.s));
+    if (sweeps & 1)
         for (int colour = 0; colour < 2; ++colour) {
-            k_mg_smooth<<<grid_for(4 * (oe - ob), 256), 256, 0, m.s>>>(m.phi, m.f, m.t->d_nbr27, ob, oe, h2, colour);
+            k_mg_smooth<<<grid_for(4 * (oe - ob), 256), 256, 0, m.s>>>(m.phi, m.f, t->d_nbr27, ob, oe,
+                                                                      ldexp(1.0, -2 * l), colour);
             RG_TRY(launch_status("multigrid smooth"));
         }
     return RG_OK;
@@ -256,6 +162,7 @@ rg_status smooth(const Mg &m, int l, int sweeps)
 rg_status residual(const rg_tree *t, const double *phi, const double *f, double *r, int l, hipStream_t s)
 {
     const int64_t ob = t->level_begin[l], oe = t->level_begin[l + 1];
+    if (l >= 4 && r != phi && r != f) return mg_brick_residual(phi + 8 * ob, f + 8 * ob, r + 8 * ob, l, s);
     k_mg_residual<<<grid_for(8 * (oe - ob), 256), 256, 0, s>>>(phi, f, r, t->d_nbr27, ob, oe, ldexp(1.0, -2 * l));
     return launch_status("multigrid residual");
 }
@@ -263,36 +170,29 @@ rg_status residual(const rg_tree *t, const double *phi, const double *f, double 
 rg_status vcycle(const Mg &m, int l)
 {
     const rg_tree *t = m.t;
-    if (t->level_begin[l + 1] - t->level_begin[l] <= kTailOcts) {
-        MgTail A;
-        A.phi = m.phi;
+    if (t->level_begin[l + 1] - t->level_begin[m.lcoarse] <= kTailOcts) {
+        TailArgs A;
+        A.e = m.phi;
         A.f = m.f;
-        A.r = m.r;
-        A.nbr27 = t->d_nbr27;
+        A.diag = nullptr;
+        A.nbr = t->d_nbr27;
         A.father = t->d_father_cell;
         for (int k = 0; k <= RG_MAX_LEVEL + 1; ++k) A.begin[k] = t->level_begin[k];
-        for (int k = 0; k <= RG_MAX_LEVEL; ++k) A.h2[k] = ldexp(1.0, -2 * k);
         A.m0 = l;
         A.lcoarse = m.lcoarse;
         A.nu1 = m.nu1;
         A.nu2 = m.nu2;
         A.ncoarse = m.ncoarse;
-        k_mg_tail<<<1, kTailThreads, 0, m.s>>>(A);
+        k_mg_tail<false><<<1, kTailThreads, 0, m.s>>>(A);
         return launch_status("multigrid small levels");
     }
     if (l == m.lcoarse) return smooth(m, l, m.ncoarse);
     RG_TRY(smooth(m, l, m.nu1));
-    RG_TRY(residual(t, m.phi, m.f, m.r, l, m.s));
-    const int64_t ob = t->level_begin[l], oe = t->level_begin[l + 1];
-    k_mg_restrict<<<grid_for(oe - ob, 256), 256, 0, m.s>>>(m.r, m.f, t->d_father_cell, ob, oe);
-    RG_TRY(launch_status("multigrid restrict"));
-    const int64_t cb = 8 * t->level_begin[l - 1], ce = 8 * t->level_begin[l];
-    k_mg_zero<<<grid_for(ce - cb, 256), 256, 0, m.s>>>(m.phi, cb, ce);
-    RG_TRY(launch_status("multigrid zero"));
+    const int64_t ob = t->level_begin[l];
+    const int64_t below = 8 * t->level_begin[l - 1];
+    RG_TRY(mg_brick_restrict(m.phi + 8 * ob, m.f + 8 * ob, m.f + below, m.phi + below, l, m.s));
     RG_TRY(vcycle(m, l - 1));
-    k_mg_prolong<<<grid_for(8 * (oe - ob), 256), 256, 0, m.s>>>(m.phi, t->d_nbr27, t->d_father_cell, ob, oe);
-    RG_TRY(launch_status("multigrid prolong"));
-    return smooth(m, l, m.nu2);
+    return smooth(m, l, m.nu2, true);
 }
 
 rg_status check_hierarchy(const rg_tree *t, int lfine, int lcoarse)

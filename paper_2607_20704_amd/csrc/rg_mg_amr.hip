@@ -23,6 +23,8 @@
 // to the Gauss-Seidel diagonal.  Every value is formed in the same order as
 // in the serial reference so that the results agree bit for bit.
 #include "rg_internal.hpp"
+#include "rg_mg_brick.hpp"
+#include "rg_mg_tail.hpp"
 
 #include <hipcub/hipcub.hpp>
 
@@ -39,8 +41,14 @@ struct rg_mg_level {
     int32_t *nbr;                        // [n_mg][27] same-level coarse oct, -1 if none
     int32_t *father;                     // [n_mg] coarse cell of the father, -1 on lcoarse
     int32_t *fine_father;                // [n_fine] coarse cell of each fine oct's father
-    double *e, *f, *r, *mask;            // [8 n_mg]
-    double *rfine;                       // [8 n_fine]
+    double *e, *f, *mask, *diag;         // [8 n_mg]
+    double *tmp;                         // [8 n_fine] when the level is complete, else null
+    int32_t *face;                       // [n_fine][6] face lists of the level (see list_sum6)
+    int32_t *slots;                      // [n_wall] oct * 6 + side of every absent face
+    int64_t n_wall;
+    double *wall;                        // [n_wall][4] potential across the absent faces
+    int32_t *cface;                      // [n_mg][6] face lists of the coarse levels
+    double *zeros;                       // four zeros: the absent faces of the coarse levels
     void *hash_ws;
 };
 
@@ -48,6 +56,117 @@ namespace rg {
 namespace {
 
 __device__ __forceinline__ int cell_of(const int p[3]) { return (p[0] & 1) + 2 * (p[1] & 1) + 4 * (p[2] & 1); }
+
+// Face lists: six entries per oct in the order x-, x+, y-, y+, z-, z+: the
+// oct across that face, or -1 - slot where there is none.  On a coarse level
+// every absent oct has slot 0, four zeros; on the solved level each absent
+// face has a slot of its own for the potential at the centres of the four
+// cells across it (in the order of the two other axes, lower axis first).
+// Those values come from level L-1 and stay the same while level L is solved,
+// so they are interpolated once per call: inside a smoothing pass each took a
+// chain of three dependent loads (list entry, father cell, potential) per
+// face, and a pass over a small level 10 us instead of 5.
+__device__ __forceinline__ int face_step(int side)
+{
+    const int step = side < 2 ? 1 : (side < 4 ? 3 : 9);
+    return (side & 1) ? step : -step;
+}
+
+// place of cell c among the four cells of a face across axis ax
+__device__ __forceinline__ int face_place(int c, int ax)
+{
+    return ax == 0 ? c >> 1 : (ax == 1 ? (c & 1) | ((c >> 1) & 2) : c & 3);
+}
+
+// the six face neighbours' values of cell c of oct o, summed in the order of
+// the sides; p: first cell of the level's octs, oct indices relative to it
+__device__ __forceinline__ double list_sum6(const double *p, const double *wall, const int32_t *__restrict__ face,
+                                            int64_t o, int c)
+{
+    double v[6];
+#pragma unroll
+    for (int side = 0; side < 6; ++side) {
+        const int ax = side >> 1, hi = side & 1;
+        int64_t n = o;
+        if (((c >> ax) & 1) == hi) n = face[6 * o + side];
+        v[side] = n >= 0 ? p[8 * n + (c ^ (1 << ax))] : wall[4 * (-1 - n) + face_place(c, ax)];
+    }
+    return ((((v[0] + v[1]) + v[2]) + v[3]) + v[4]) + v[5];
+}
+
+// face lists of the solved level, with the absent faces counted off
+__global__ void k_fine_faces(const int32_t *__restrict__ nbr27, int64_t ob, int64_t n, int32_t *__restrict__ face,
+                             int32_t *__restrict__ slots, int32_t *count)
+{
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (t >= 6 * n) return;
+    const int64_t o = t / 6;
+    const int side = static_cast<int>(t - 6 * o);
+    const int32_t e = nbr27[27 * (ob + o) + 13 + face_step(side)];
+    if (e >= 0) {
+        face[t] = static_cast<int32_t>(e - ob);
+    } else {
+        const int32_t slot = atomicAdd(count, 1);
+        if (slots) slots[slot] = static_cast<int32_t>(t);
+        face[t] = -1 - slot;
+    }
+}
+
+__global__ void k_coarse_faces(const int32_t *__restrict__ nbr, int64_t n, int32_t *__restrict__ face)
+{
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (t < 6 * n) face[t] = nbr[27 * (t / 6) + 13 + face_step(static_cast<int>(t % 6))];
+}
+
+// The potential across the absent faces: trilinear interpolation from level
+// L-1 at the centre of the cell across face `side` from cell c of oct o.  The
+// neighbour sits in coarse cell F + dv (F the father of o), toward side s of
+// that cell's centre: the 8 coarse cells F + dv + {0, s}^3.
+__global__ void k_fine_walls(const double *__restrict__ phi, const int32_t *__restrict__ nbr27,
+                             const int32_t *__restrict__ fcell, const int32_t *__restrict__ slots, int64_t n,
+                             int64_t ob, double *__restrict__ wall)
+{
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (t >= 4 * n) return;
+    const int32_t os = slots[t >> 2];
+    const int64_t o = ob + os / 6;
+    const int side = os % 6, q = static_cast<int>(t & 3);
+    const int ax = side >> 1, d = (side & 1) ? 1 : -1;
+    // the cell across the face, by its place within its own (absent) oct
+    int p[3];
+    p[ax] = d < 0 ? 1 : 0;
+    p[ax == 0 ? 1 : 0] = q & 1;
+    p[ax == 2 ? 1 : 2] = q >> 1;
+    const int st[3] = {1, 3, 9};
+    int far = 13, step[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        if (a == ax) far += d * st[a];
+        step[a] = p[a] ? st[a] : -st[a];
+    }
+    double v[8];
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const int32_t e = nbr27[27 * o + far + ((b & 1) ? step[0] : 0) + ((b & 2) ? step[1] : 0) +
+                                ((b & 4) ? step[2] : 0)];
+        v[b] = phi[e >= 0 ? int64_t(fcell[e]) : int64_t(-1 - e)];
+    }
+    const double w = ((((((27.0 * v[0] + 9.0 * v[1]) + 9.0 * v[2]) + 9.0 * v[4]) + 3.0 * v[3]) + 3.0 * v[5]) +
+                      3.0 * v[6]) + v[7];
+    wall[t] = 0.015625 * w;
+}
+
+// one colour pass; p and f start at the level's first cell
+__global__ void k_fine_smooth(double *p, const double *__restrict__ f, const double *__restrict__ wall,
+                              const int32_t *__restrict__ face, int64_t n, double h2, int colour)
+{
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t o = t >> 2;
+    if (o >= n) return;
+    const int c = colour_cell(colour, static_cast<int>(t & 3));
+    const int64_t cell = 8 * o + c;
+    p[cell] = (list_sum6(p, wall, face, o, c) - h2 * f[cell]) / 6.0;
+}
 
 // value of face neighbour `side` (x-, x+, y-, y+, z-, z+) of fine cell c of
 // tree oct o: a level-L cell, or the interpolated level-(L-1) potential
@@ -90,19 +209,6 @@ __device__ __forceinline__ double fine_sum6(const double *phi, const int32_t *__
             fine_neighbour(phi, nbr27, fcell, o, c, 4)) + fine_neighbour(phi, nbr27, fcell, o, c, 5);
 }
 
-__constant__ int c_amr_colour[2][4] = {{0, 3, 5, 6}, {1, 2, 4, 7}};
-
-__global__ void k_fine_smooth(double *phi, const double *__restrict__ f, const int32_t *__restrict__ nbr27,
-                              const int32_t *__restrict__ fcell, int64_t ob, int64_t oe, double h2, int colour)
-{
-    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t o = ob + (t >> 2);
-    if (o >= oe) return;
-    const int c = c_amr_colour[colour][t & 3];
-    const int64_t cell = 8 * o + c;
-    phi[cell] = (fine_sum6(phi, nbr27, fcell, o, c) - h2 * f[cell]) / 6.0;
-}
-
 // r of every fine cell, at out[8 (o - out_base) + c]
 __global__ void k_fine_residual(const double *__restrict__ phi, const double *__restrict__ f,
                                 const int32_t *__restrict__ nbr27, const int32_t *__restrict__ fcell, int64_t ob,
@@ -117,66 +223,83 @@ __global__ void k_fine_residual(const double *__restrict__ phi, const double *__
     out[8 * (o - out_base) + c] = f[cell] - lap;
 }
 
-// inside-neighbour sum s and diagonal excess d of coarse cell c of oct g
-__device__ __forceinline__ void coarse_terms(const double *e, const double *__restrict__ mask,
-                                             const int32_t *__restrict__ nbr, int64_t g, int c, double mi, double &s,
-                                             double &d)
+// Residual of the level restricted into its fathers' cells of the level below
+// (the mean of an oct's 8 values, summed pairwise in cell order by the eight
+// lanes that hold them); the corrections below, [cb, ce), set to zero.  The
+// right-hand sides of coarse cells without children are zero from the build
+// on: nothing writes them.
+__global__ void k_fine_restrict(const double *__restrict__ p, const double *__restrict__ f,
+                                const double *__restrict__ wall, const int32_t *__restrict__ face, int64_t n,
+                                double h2, const int32_t *__restrict__ father, double *__restrict__ fc,
+                                double *__restrict__ ec, int64_t cb, int64_t ce)
 {
-    s = 0.0;
-    d = 0.0;
-#pragma unroll
-    for (int side = 0; side < 6; ++side) {
-        const int ax = side >> 1, dd = (side & 1) ? 1 : -1;
-        int p[3] = {c & 1, (c >> 1) & 1, c >> 2};
-        p[ax] += dd;
-        int64_t j = -1;
-        if (p[ax] >= 0 && p[ax] <= 1) {
-            j = 8 * g + cell_of(p);
-        } else {
-            const int32_t n = nbr[27 * g + 13 + (ax == 0 ? dd : ax == 1 ? 3 * dd : 9 * dd)];
-            if (n >= 0) j = 8 * int64_t(n) + cell_of(p);
-        }
-        const double mj = j >= 0 ? mask[j] : -1.0;
-        if (mj > 0.0)
-            s = s + e[j];
-        else
-            d = d + ((mi - mj) / mi - 1.0);
-    }
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t o = t >> 3;
+    if (o >= n) return;
+    const int c = static_cast<int>(t & 7);
+    const double lap = (list_sum6(p, wall, face, o, c) - 6.0 * p[t]) / h2;
+    double r = f[t] - lap;
+    r = r + __shfl_xor(r, 1, 64);
+    r = r + __shfl_xor(r, 2, 64);
+    r = r + __shfl_xor(r, 4, 64);
+    if (c == 0) fc[father[o]] = 0.125 * r;
+    if (cb + t < ce) ec[cb + t] = 0.0;
 }
 
-__global__ void k_coarse_smooth(double *e, const double *__restrict__ f, const double *__restrict__ mask,
-                                const int32_t *__restrict__ nbr, int64_t gb, int64_t ge, double h2, int colour)
+// Gauss-Seidel diagonal of every coarse cell: 6 plus, for each face neighbour
+// that is outside or absent (mask -1), (m_i - m_j) / m_i - 1; 0 on cells
+// outside.  Built once with the masks.
+__global__ void k_coarse_diag(const double *__restrict__ mask, const int32_t *__restrict__ nbr, int64_t n,
+                              double *__restrict__ diag)
+{
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t g = t >> 3;
+    if (g >= n) return;
+    const int c = static_cast<int>(t & 7);
+    const double mi = mask[t];
+    double d = 0.0;
+    for (int side = 0; side < 6; ++side) {
+        const int ax = side >> 1, hi = side & 1;
+        int64_t o = g;
+        if (((c >> ax) & 1) == hi) o = nbr[27 * g + 13 + face_step(side)];
+        const double mj = o >= 0 ? mask[8 * o + (c ^ (1 << ax))] : -1.0;
+        if (!(mj > 0.0)) d = d + ((mi - mj) / mi - 1.0);
+    }
+    diag[t] = mi > 0.0 ? 6.0 + d : 0.0;
+}
+
+__global__ void k_coarse_smooth(double *e, const double *__restrict__ f, const double *__restrict__ diag,
+                                const double *__restrict__ wall, const int32_t *__restrict__ face, int64_t gb, int64_t ge, double h2, int colour)
 {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     const int64_t g = gb + (t >> 2);
     if (g >= ge) return;
-    const int c = c_amr_colour[colour][t & 3];
+    const int c = colour_cell(colour, static_cast<int>(t & 3));
     const int64_t cell = 8 * g + c;
-    const double mi = mask[cell];
-    if (!(mi > 0.0)) return;
-    double s, d;
-    coarse_terms(e, mask, nbr, g, c, mi, s, d);
-    e[cell] = (s - h2 * f[cell]) / (6.0 + d);
+    const double d = diag[cell];
+    if (d == 0.0) return;
+    e[cell] = (list_sum6(e, wall, face, g, c) - h2 * f[cell]) / d;
 }
 
-__global__ void k_coarse_residual(const double *__restrict__ e, const double *__restrict__ f,
-                                  const double *__restrict__ mask, const int32_t *__restrict__ nbr, int64_t gb,
-                                  int64_t ge, double h2, double *__restrict__ r)
+// as k_fine_restrict, on a coarse level
+__global__ void k_coarse_restrict(double *e, double *f, const double *__restrict__ diag,
+                                  const double *__restrict__ wall, const int32_t *__restrict__ face,
+                                  const int32_t *__restrict__ father, int64_t gb, int64_t ge, double h2, int64_t cb,
+                                  int64_t ce)
 {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     const int64_t g = gb + (t >> 3);
     if (g >= ge) return;
     const int c = static_cast<int>(t & 7);
     const int64_t cell = 8 * g + c;
-    const double mi = mask[cell];
-    if (!(mi > 0.0)) {
-        r[cell] = 0.0;
-        return;
-    }
-    double s, d;
-    coarse_terms(e, mask, nbr, g, c, mi, s, d);
-    const double lap = (s - (6.0 + d) * e[cell]) / h2;
-    r[cell] = f[cell] - lap;
+    const double d = diag[cell];
+    const double lap = (list_sum6(e, wall, face, g, c) - d * e[cell]) / h2;
+    double r = d == 0.0 ? 0.0 : f[cell] - lap;
+    r = r + __shfl_xor(r, 1, 64);
+    r = r + __shfl_xor(r, 2, 64);
+    r = r + __shfl_xor(r, 4, 64);
+    if (c == 0) f[father[g]] = 0.125 * r;
+    if (cb + t < ce) e[cb + t] = 0.0;
 }
 
 // dst[father[o]] = mean of src[8 o .. 8 o + 7], summed pairwise in cell order
@@ -243,7 +366,7 @@ __global__ void k_prolong_fine(double *phi, const double *__restrict__ e, const 
     phi[cell] = phi[cell] + prolong_value(e, nbr, fine_father[ol], c);
 }
 
-__global__ void k_prolong_coarse(double *e, const double *__restrict__ mask, const int32_t *__restrict__ nbr,
+__global__ void k_prolong_coarse(double *e, const double *__restrict__ diag, const int32_t *__restrict__ nbr,
                                  const int32_t *__restrict__ father, int64_t gb, int64_t ge)
 {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -251,147 +374,8 @@ __global__ void k_prolong_coarse(double *e, const double *__restrict__ mask, con
     if (g >= ge) return;
     const int c = static_cast<int>(t & 7);
     const int64_t cell = 8 * g + c;
-    if (!(mask[cell] > 0.0)) return;
+    if (diag[cell] == 0.0) return;
     e[cell] = e[cell] + prolong_value(e, nbr, father[g], c);
-}
-
-// ---------------------------------------------------------------- small levels
-//
-// The coarse levels with at most kTailOcts octs (all levels below the first
-// such level are smaller still) run their whole part of the V-cycle in one
-// workgroup: the same passes in the same order as the per-level launches,
-// separated by barriers instead of kernel boundaries, so the results are the
-// same bits.  Each of those launches (two per sweep, 100 for 50 sweeps on
-// the coarsest level) costs a few microseconds of GPU time however little
-// it does.
-
-constexpr int64_t kTailOcts = 512;
-constexpr int kTailThreads = 1024;
-
-struct TailArgs {
-    double *e, *f, *r;
-    const double *mask;
-    const int32_t *nbr, *father;
-    int64_t begin[RG_MAX_LEVEL + 2];
-    double h2[RG_MAX_LEVEL + 1];
-    int m0, lcoarse, nu1, nu2, ncoarse;
-};
-
-__device__ void tail_smooth(const TailArgs &A, int m, int sweeps)
-{
-    const int64_t gb = A.begin[m], n4 = 4 * (A.begin[m + 1] - gb);
-    for (int sw = 0; sw < sweeps; ++sw)
-        for (int colour = 0; colour < 2; ++colour) {
-            for (int64_t t = threadIdx.x; t < n4; t += blockDim.x) {
-                const int64_t g = gb + (t >> 2);
-                const int c = c_amr_colour[colour][t & 3];
-                const int64_t cell = 8 * g + c;
-                const double mi = A.mask[cell];
-                if (!(mi > 0.0)) continue;
-                double s, d;
-                coarse_terms(A.e, A.mask, A.nbr, g, c, mi, s, d);
-                A.e[cell] = (s - A.h2[m] * A.f[cell]) / (6.0 + d);
-            }
-            __syncthreads();
-        }
-}
-
-// The coarsest level's sweeps (50 by default, each pass depending on the
-// last) with its corrections, right-hand sides and masks staged in LDS when
-// it holds at most kLdsCells cells: the same update of each cell.
-constexpr int kLdsCells = 1024;
-
-__device__ void tail_sweeps_lds(const TailArgs &A, int m, int sweeps, double *se, double *sf, double *sm)
-{
-    const int64_t gb = A.begin[m], cb = 8 * gb, n = 8 * (A.begin[m + 1] - gb);
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-        se[i] = A.e[cb + i];
-        sf[i] = A.f[cb + i];
-        sm[i] = A.mask[cb + i];
-    }
-    __syncthreads();
-    for (int sw = 0; sw < sweeps; ++sw)
-        for (int colour = 0; colour < 2; ++colour) {
-            for (int64_t t = threadIdx.x; t < n / 2; t += blockDim.x) {
-                const int64_t g = gb + (t >> 2);
-                const int c = c_amr_colour[colour][t & 3];
-                const int64_t k = 8 * g + c - cb;
-                const double mi = sm[k];
-                if (!(mi > 0.0)) continue;
-                double s = 0.0, d = 0.0;
-#pragma unroll
-                for (int side = 0; side < 6; ++side) {
-                    const int ax = side >> 1, dd = (side & 1) ? 1 : -1;
-                    int p[3] = {c & 1, (c >> 1) & 1, c >> 2};
-                    p[ax] += dd;
-                    int64_t j = -1;
-                    if (p[ax] >= 0 && p[ax] <= 1) {
-                        j = 8 * g + cell_of(p);
-                    } else {
-                        const int32_t nn = A.nbr[27 * g + 13 + (ax == 0 ? dd : ax == 1 ? 3 * dd : 9 * dd)];
-                        if (nn >= 0) j = 8 * int64_t(nn) + cell_of(p);
-                    }
-                    const double mj = j >= 0 ? sm[j - cb] : -1.0;
-                    if (mj > 0.0)
-                        s = s + se[j - cb];
-                    else
-                        d = d + ((mi - mj) / mi - 1.0);
-                }
-                se[k] = (s - A.h2[m] * sf[k]) / (6.0 + d);
-            }
-            __syncthreads();
-        }
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) A.e[cb + i] = se[i];
-    __syncthreads();
-}
-
-__global__ __launch_bounds__(kTailThreads) void k_vcycle_tail(TailArgs A)
-{
-    __shared__ double se[kLdsCells], sf[kLdsCells], sm[kLdsCells];
-    for (int m = A.m0; m > A.lcoarse; --m) {
-        tail_smooth(A, m, A.nu1);
-        const int64_t gb = A.begin[m], ge = A.begin[m + 1];
-        for (int64_t t = threadIdx.x; t < 8 * (ge - gb); t += blockDim.x) {
-            const int64_t g = gb + (t >> 3);
-            const int c = static_cast<int>(t & 7);
-            const int64_t cell = 8 * g + c;
-            const double mi = A.mask[cell];
-            if (!(mi > 0.0)) {
-                A.r[cell] = 0.0;
-                continue;
-            }
-            double s, d;
-            coarse_terms(A.e, A.mask, A.nbr, g, c, mi, s, d);
-            const double lap = (s - (6.0 + d) * A.e[cell]) / A.h2[m];
-            A.r[cell] = A.f[cell] - lap;
-        }
-        for (int64_t i = 8 * A.begin[m - 1] + threadIdx.x; i < 8 * A.begin[m]; i += blockDim.x) {
-            A.f[i] = 0.0;
-            A.e[i] = 0.0;
-        }
-        __syncthreads();
-        for (int64_t g = gb + threadIdx.x; g < ge; g += blockDim.x) {
-            const double *c = A.r + 8 * g;
-            A.f[A.father[g]] = 0.125 * (((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7])));
-        }
-        __syncthreads();
-    }
-    if (8 * (A.begin[A.lcoarse + 1] - A.begin[A.lcoarse]) <= kLdsCells)
-        tail_sweeps_lds(A, A.lcoarse, A.ncoarse, se, sf, sm);
-    else
-        tail_smooth(A, A.lcoarse, A.ncoarse);
-    for (int m = A.lcoarse + 1; m <= A.m0; ++m) {
-        const int64_t gb = A.begin[m], ge = A.begin[m + 1];
-        for (int64_t t = threadIdx.x; t < 8 * (ge - gb); t += blockDim.x) {
-            const int64_t g = gb + (t >> 3);
-            const int c = static_cast<int>(t & 7);
-            const int64_t cell = 8 * g + c;
-            if (!(A.mask[cell] > 0.0)) continue;
-            A.e[cell] = A.e[cell] + prolong_value(A.e, A.nbr, A.father[g], c);
-        }
-        __syncthreads();
-        tail_smooth(A, m, A.nu2);
-    }
 }
 
 // ---------------------------------------------------------------- build
@@ -439,29 +423,49 @@ struct Ctx {
     hipStream_t s;
 };
 
-rg_status fine_smooth(const Ctx &x, int sweeps)
+// Brick passes (rg_mg_brick.hpp) serve a complete level of at least 8^3 octs:
+// all its ancestor levels are complete too, with no cell outside.
+bool bricks(const rg_mg_level *h, int m) { return h->tmp && m >= 4; }
+
+// the level's own sweeps; with prolong, after adding the correction below
+rg_status fine_smooth(const Ctx &x, int sweeps, bool prolong = false)
 {
     const rg_mg_level *h = x.h;
-    const int64_t ob = h->fine_begin, oe = ob + h->n_fine;
+    const int64_t ob = h->fine_begin;
     const double h2 = ldexp(1.0, -2 * h->level);
-    for (int sw = 0; sw < sweeps; ++sw)
+    const int pairs = bricks(h, h->level) ? sweeps & ~1 : 0;
+    if (prolong && pairs == 0) {
+        k_prolong_fine<<<grid_for(8 * h->n_fine, 256), 256, 0, x.s>>>(x.phi, h->e, h->nbr, h->fine_father, ob,
+                                                                     h->n_fine);
+        RG_TRY(launch_status("level multigrid prolong"));
+    }
+    RG_TRY(mg_brick_sweeps(x.phi + 8 * ob, h->tmp, x.f + 8 * ob,
+                           prolong ? h->e + 8 * h->mg_begin[h->level - 1] : nullptr, h->level, pairs, x.s));
+    for (int sw = pairs; sw < sweeps; ++sw)
         for (int colour = 0; colour < 2; ++colour) {
-            k_fine_smooth<<<grid_for(4 * h->n_fine, 256), 256, 0, x.s>>>(x.phi, x.f, x.t->d_nbr27, x.t->d_father_cell,
-                                                                        ob, oe, h2, colour);
+            k_fine_smooth<<<grid_for(4 * h->n_fine, 256), 256, 0, x.s>>>(x.phi + 8 * ob, x.f + 8 * ob, h->wall, h->face,
+                                                                        h->n_fine, h2, colour);
             RG_TRY(launch_status("level multigrid smooth"));
         }
     return RG_OK;
 }
 
-rg_status coarse_smooth(const Ctx &x, int m, int sweeps)
+rg_status coarse_smooth(const Ctx &x, int m, int sweeps, bool prolong = false)
 {
     const rg_mg_level *h = x.h;
     const int64_t gb = h->mg_begin[m], ge = h->mg_begin[m + 1];
     const double h2 = ldexp(1.0, -2 * m);
-    for (int sw = 0; sw < sweeps; ++sw)
+    const int pairs = bricks(h, m) ? sweeps & ~1 : 0;
+    if (prolong && pairs == 0) {
+        k_prolong_coarse<<<grid_for(8 * (ge - gb), 256), 256, 0, x.s>>>(h->e, h->diag, h->nbr, h->father, gb, ge);
+        RG_TRY(launch_status("level multigrid coarse prolong"));
+    }
+    RG_TRY(mg_brick_sweeps(h->e + 8 * gb, h->tmp, h->f + 8 * gb, prolong ? h->e + 8 * h->mg_begin[m - 1] : nullptr, m,
+                           pairs, x.s));
+    for (int sw = pairs; sw < sweeps; ++sw)
         for (int colour = 0; colour < 2; ++colour) {
-            k_coarse_smooth<<<grid_for(4 * (ge - gb), 256), 256, 0, x.s>>>(h->e, h->f, h->mask, h->nbr, gb, ge, h2,
-                                                                          colour);
+            k_coarse_smooth<<<grid_for(4 * (ge - gb), 256), 256, 0, x.s>>>(h->e, h->f, h->diag, h->zeros, h->cface, gb,
+                                                                          ge, h2, colour);
             RG_TRY(launch_status("level multigrid coarse smooth"));
         }
     return RG_OK;
@@ -477,39 +481,36 @@ rg_status fill(double *p, int64_t b, int64_t e, double v, hipStream_t s)
 rg_status vcoarse(const Ctx &x, int m)
 {
     rg_mg_level *h = x.h;
-    if (h->mg_begin[m + 1] - h->mg_begin[m] <= kTailOcts) {
+    if (h->mg_begin[m + 1] - h->mg_begin[h->lcoarse] <= kTailOcts) {
         TailArgs A;
         A.e = h->e;
         A.f = h->f;
-        A.r = h->r;
-        A.mask = h->mask;
+        A.diag = h->diag;
         A.nbr = h->nbr;
         A.father = h->father;
         for (int k = 0; k <= RG_MAX_LEVEL + 1; ++k) A.begin[k] = h->mg_begin[k];
-        for (int k = 0; k <= RG_MAX_LEVEL; ++k) A.h2[k] = ldexp(1.0, -2 * k);
         A.m0 = m;
         A.lcoarse = h->lcoarse;
         A.nu1 = x.nu1;
         A.nu2 = x.nu2;
         A.ncoarse = x.ncoarse;
-        k_vcycle_tail<<<1, kTailThreads, 0, x.s>>>(A);
+        k_mg_tail<true><<<1, kTailThreads, 0, x.s>>>(A);
         return launch_status("level multigrid small levels");
     }
     if (m == h->lcoarse) return coarse_smooth(x, m, x.ncoarse);
     RG_TRY(coarse_smooth(x, m, x.nu1));
     const int64_t gb = h->mg_begin[m], ge = h->mg_begin[m + 1];
-    k_coarse_residual<<<grid_for(8 * (ge - gb), 256), 256, 0, x.s>>>(h->e, h->f, h->mask, h->nbr, gb, ge,
-                                                                    ldexp(1.0, -2 * m), h->r);
-    RG_TRY(launch_status("level multigrid coarse residual"));
-    const int64_t cb = 8 * h->mg_begin[m - 1], ce = 8 * h->mg_begin[m];
-    RG_TRY(fill(h->f, cb, ce, 0.0, x.s));
-    k_restrict8<<<grid_for(ge - gb, 256), 256, 0, x.s>>>(h->r, h->father, gb, ge, h->f);
-    RG_TRY(launch_status("level multigrid restrict"));
-    RG_TRY(fill(h->e, cb, ce, 0.0, x.s));
+    const int64_t below = 8 * h->mg_begin[m - 1];
+    if (bricks(h, m)) {
+        RG_TRY(mg_brick_restrict(h->e + 8 * gb, h->f + 8 * gb, h->f + below, h->e + below, m, x.s));
+    } else {
+        k_coarse_restrict<<<grid_for(8 * (ge - gb), 256), 256, 0, x.s>>>(h->e, h->f, h->diag, h->zeros, h->cface,
+                                                                        h->father, gb, ge, ldexp(1.0, -2 * m), below,
+                                                                        8 * gb);
+        RG_TRY(launch_status("level multigrid coarse restrict"));
+    }
     RG_TRY(vcoarse(x, m - 1));
-    k_prolong_coarse<<<grid_for(8 * (ge - gb), 256), 256, 0, x.s>>>(h->e, h->mask, h->nbr, h->father, gb, ge);
-    RG_TRY(launch_status("level multigrid coarse prolong"));
-    return coarse_smooth(x, m, x.nu2);
+    return coarse_smooth(x, m, x.nu2, true);
 }
 
 rg_status vfine(const Ctx &x)
@@ -518,20 +519,18 @@ rg_status vfine(const Ctx &x)
     const int L = h->level;
     if (L == h->lcoarse) return fine_smooth(x, x.ncoarse);
     RG_TRY(fine_smooth(x, x.nu1));
-    const int64_t ob = h->fine_begin, oe = ob + h->n_fine;
-    k_fine_residual<<<grid_for(8 * h->n_fine, 256), 256, 0, x.s>>>(x.phi, x.f, x.t->d_nbr27, x.t->d_father_cell, ob,
-                                                                  oe, ldexp(1.0, -2 * L), h->rfine, ob);
-    RG_TRY(launch_status("level multigrid residual"));
-    const int64_t cb = 8 * h->mg_begin[L - 1], ce = 8 * h->mg_begin[L];
-    RG_TRY(fill(h->f, cb, ce, 0.0, x.s));
-    k_restrict8<<<grid_for(h->n_fine, 256), 256, 0, x.s>>>(h->rfine, h->fine_father, 0, h->n_fine, h->f);
-    RG_TRY(launch_status("level multigrid restrict"));
-    RG_TRY(fill(h->e, cb, ce, 0.0, x.s));
+    const int64_t ob = h->fine_begin;
+    const int64_t below = 8 * h->mg_begin[L - 1];
+    if (bricks(h, L)) {
+        RG_TRY(mg_brick_restrict(x.phi + 8 * ob, x.f + 8 * ob, h->f + below, h->e + below, L, x.s));
+    } else {
+        k_fine_restrict<<<grid_for(8 * h->n_fine, 256), 256, 0, x.s>>>(
+            x.phi + 8 * ob, x.f + 8 * ob, h->wall, h->face, h->n_fine, ldexp(1.0, -2 * L), h->fine_father, h->f, h->e,
+            below, 8 * h->mg_begin[L]);
+        RG_TRY(launch_status("level multigrid restrict"));
+    }
     RG_TRY(vcoarse(x, L - 1));
-    k_prolong_fine<<<grid_for(8 * h->n_fine, 256), 256, 0, x.s>>>(x.phi, h->e, h->nbr, h->fine_father, ob,
-                                                                 h->n_fine);
-    RG_TRY(launch_status("level multigrid prolong"));
-    return fine_smooth(x, x.nu2);
+    return fine_smooth(x, x.nu2, true);
 }
 
 rg_status check_level(const rg_mg_level *h, const rg_tree *t)
@@ -612,6 +611,19 @@ rg_status rg_mg_level_create(const rg_tree *t, int level, int lcoarse, rg_mg_lev
         prev = lists[m];
         nprev = c;
     }
+    // face lists of the level, absent faces counted off
+    int32_t *face = nullptr, *slots = nullptr, n_wall = 0;
+    RG_TRY(tmp.alloc(reinterpret_cast<void **>(&face), size_t(n_fine) * 24));
+    RG_TRY(tmp.alloc(reinterpret_cast<void **>(&slots), size_t(n_fine) * 24));
+    RG_TRY(fill_u32(reinterpret_cast<uint32_t *>(d_count), 1, 0u, s));
+    k_fine_faces<<<grid_for(6 * n_fine, 256), 256, 0, s>>>(t->d_nbr27, fb, n_fine, face, slots,
+                                                          reinterpret_cast<int32_t *>(d_count));
+    RG_TRY(launch_status("level multigrid faces"));
+    {
+        hipError_t e = hipMemcpyAsync(&n_wall, d_count, sizeof(n_wall), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return fail(RG_EHIP, "level multigrid faces: %s", hipGetErrorString(e));
+    }
     rg_mg_level *h = new rg_mg_level();
     h->level = level;
     h->lcoarse = lcoarse;
@@ -626,8 +638,12 @@ rg_status rg_mg_level_create(const rg_tree *t, int level, int lcoarse, rg_mg_lev
     h->n_mg = n_mg;
     const size_t hash_bytes = rg_hash_workspace_bytes(n_mg);
     const size_t nm = static_cast<size_t>(n_mg);
+    // a level of at most 10 bits a side: the brick passes' oct indices and grids are sized for it
+    const bool complete = level <= 10 && n_fine == int64_t(1) << (3 * (level - 1));
     const size_t bytes = al256(nm * 8) + al256(nm * 27 * 4) + al256(nm * 4) + al256(size_t(n_fine) * 4) +
-                         4 * al256(nm * 8 * 8) + al256(size_t(n_fine) * 8 * 8) + al256(hash_bytes);
+                         4 * al256(nm * 8 * 8) + al256(complete ? size_t(n_fine) * 64 : 0) + al256(size_t(n_fine) * 24) +
+                         al256(size_t(n_wall) * 4) + al256(size_t(n_wall) * 32) + al256(nm * 24) + al256(32) +
+                         al256(hash_bytes);
     hipError_t e = hipMalloc(&h->mem, bytes);
     if (e != hipSuccess) {
         delete h;
@@ -645,9 +661,15 @@ rg_status rg_mg_level_create(const rg_tree *t, int level, int lcoarse, rg_mg_lev
     h->fine_father = reinterpret_cast<int32_t *>(take(size_t(n_fine) * 4));
     h->e = reinterpret_cast<double *>(take(nm * 64));
     h->f = reinterpret_cast<double *>(take(nm * 64));
-    h->r = reinterpret_cast<double *>(take(nm * 64));
     h->mask = reinterpret_cast<double *>(take(nm * 64));
-    h->rfine = reinterpret_cast<double *>(take(size_t(n_fine) * 64));
+    h->diag = reinterpret_cast<double *>(take(nm * 64));
+    h->tmp = complete ? reinterpret_cast<double *>(take(size_t(n_fine) * 64)) : nullptr;
+    h->n_wall = n_wall;
+    h->face = reinterpret_cast<int32_t *>(take(size_t(n_fine) * 24));
+    h->slots = reinterpret_cast<int32_t *>(take(size_t(n_wall) * 4));
+    h->wall = reinterpret_cast<double *>(take(size_t(n_wall) * 32));
+    h->cface = reinterpret_cast<int32_t *>(take(nm * 24));
+    h->zeros = reinterpret_cast<double *>(take(32));
     h->hash_ws = take(hash_bytes);
     rg_status st = RG_OK;
     for (int m = lcoarse; m < level && st == RG_OK; ++m)
@@ -655,6 +677,13 @@ rg_status rg_mg_level_create(const rg_tree *t, int level, int lcoarse, rg_mg_lev
             e = hipMemcpyAsync(h->keys + h->mg_begin[m], lists[m], size_t(counts[m]) * 8, hipMemcpyDeviceToDevice, s);
             if (e != hipSuccess) st = fail(RG_EHIP, "level multigrid keys: %s", hipGetErrorString(e));
         }
+    if (st == RG_OK) st = fill(h->zeros, 0, 4, 0.0, s);
+    if (st == RG_OK) {
+        e = hipMemcpyAsync(h->face, face, size_t(n_fine) * 24, hipMemcpyDeviceToDevice, s);
+        if (e == hipSuccess && n_wall > 0)
+            e = hipMemcpyAsync(h->slots, slots, size_t(n_wall) * 4, hipMemcpyDeviceToDevice, s);
+        if (e != hipSuccess) st = fail(RG_EHIP, "level multigrid faces: %s", hipGetErrorString(e));
+    }
     if (st == RG_OK && n_mg > 0) st = rg_hash_build(h->keys, n_mg, h->hash_ws, hash_bytes, stream);
     if (st == RG_OK && n_mg > 0) {
         HashView hv = hash_view(h->hash_ws, hash_capacity(n_mg));
@@ -663,6 +692,10 @@ rg_status rg_mg_level_create(const rg_tree *t, int level, int lcoarse, rg_mg_lev
         if (st == RG_OK) {
             k_fine_links<<<grid_for(n_fine, 256), 256, 0, s>>>(t->d_keys + fb, n_fine, hv, h->fine_father);
             st = launch_status("level multigrid fine links");
+        }
+        if (st == RG_OK) {
+            k_coarse_faces<<<grid_for(6 * n_mg, 256), 256, 0, s>>>(h->nbr, n_mg, h->cface);
+            st = launch_status("level multigrid coarse faces");
         }
         // masks, finest coarse level first
         if (st == RG_OK) st = fill(h->mask, 0, 8 * n_mg, -1.0, s);
@@ -675,7 +708,12 @@ rg_status rg_mg_level_create(const rg_tree *t, int level, int lcoarse, rg_mg_lev
             k_restrict8<<<grid_for(ge - gb, 256), 256, 0, s>>>(h->mask, h->father, gb, ge, h->mask);
             st = launch_status("level multigrid masks");
         }
+        if (st == RG_OK) {
+            k_coarse_diag<<<grid_for(8 * n_mg, 256), 256, 0, s>>>(h->mask, h->nbr, n_mg, h->diag);
+            st = launch_status("level multigrid diagonals");
+        }
         if (st == RG_OK) st = fill(h->e, 0, 8 * n_mg, 0.0, s);
+        if (st == RG_OK) st = fill(h->f, 0, 8 * n_mg, 0.0, s);
     }
     if (st == RG_OK) {
         e = hipStreamSynchronize(s);
@@ -714,6 +752,11 @@ rg_status rg_mg_level_vcycles(rg_mg_level *h, const rg_tree *t, double *d_phi, c
     x.nu2 = nu2;
     x.ncoarse = ncoarse;
     x.s = as_stream(stream);
+    if (h->n_wall > 0 && ncycles > 0) {
+        k_fine_walls<<<grid_for(4 * h->n_wall, 256), 256, 0, x.s>>>(d_phi, t->d_nbr27, t->d_father_cell, h->slots,
+                                                                   h->n_wall, h->fine_begin, h->wall);
+        RG_TRY(launch_status("level multigrid walls"));
+    }
     for (int c = 0; c < ncycles; ++c) RG_TRY(vfine(x));
     return RG_OK;
 }

@@ -1,0 +1,88 @@
+"""GPU parity of the multigrid's brick passes and its single-workgroup tail at
+the sizes where they change hands, bit for bit against the oracle.
+
+- Unigrids: one brick that wraps onto itself (level 4 as the coarsest level),
+  coarsest levels in bricks, odd and unequal sweep counts (the last of an odd
+  number runs colour by colour), no sweeps after the correction.
+- Level by level: a complete level in bricks with odd sweep counts; a tree
+  whose hierarchy crosses the tail's bound of 640 octs; a tail that starts
+  above level 1; right-hand sides with zeros and values near the ends of the
+  exponent range (the tail's division falls back to the general one)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2607_20704_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def _api():
+    from paper_2607_20704_amd import api
+    return api
+
+
+def _cells(M, dense):
+    ijk = M.fine_cells_ijk()
+    return torch.as_tensor(np.ascontiguousarray(dense[ijk[:, 2], ijk[:, 1], ijk[:, 0]])).cuda()
+
+
+def _unigrid(lfine, lcoarse, nu1, nu2, ncoarse, ncycles, scale=1.0, sparse=False):
+    M = _api().Multigrid(lfine, lcoarse)
+    N = 1 << lfine
+    rng = np.random.default_rng(31 + lfine + 7 * nu1)
+    f = rng.standard_normal((N, N, N))
+    phi = rng.standard_normal((N, N, N))
+    if sparse:
+        f[f < 1.0] = 0.0
+        phi[:] = 0.0
+    f = (f - f.mean() if not sparse else f) * scale
+    phi *= scale
+    M.phi[M.fine] = _cells(M, phi)
+    M.f[M.fine] = _cells(M, f)
+    M.vcycles(ncycles, nu1, nu2, ncoarse)
+    want, _ = O.mg_vcycles(phi.copy(), f, ncycles, lcoarse, nu1, nu2, ncoarse)
+    assert np.array_equal(M.phi[M.fine].cpu().numpy(), _cells(M, want).cpu().numpy())
+    r = M.residual().cpu().numpy()
+    assert np.array_equal(r, _cells(M, O.mg_residual(want, f)).cpu().numpy())
+
+
+@pytest.mark.parametrize("lfine,lcoarse,nu1,nu2,ncoarse,ncycles", [
+    (4, 4, 2, 2, 5, 2), (5, 4, 2, 2, 6, 2), (5, 5, 0, 0, 3, 1), (5, 1, 1, 3, 9, 2), (6, 3, 3, 1, 8, 2),
+    (6, 1, 2, 0, 50, 2), (5, 2, 0, 2, 4, 2), (3, 1, 2, 2, 50, 2), (2, 2, 2, 2, 3, 1), (1, 1, 1, 1, 50, 1)])
+def test_unigrid_passes(lfine, lcoarse, nu1, nu2, ncoarse, ncycles):
+    _unigrid(lfine, lcoarse, nu1, nu2, ncoarse, ncycles)
+
+
+@pytest.mark.parametrize("scale,sparse", [(1e-270, False), (1e-300, False), (1e260, False), (1.0, True)])
+def test_unigrid_range(scale, sparse):
+    _unigrid(4, 1, 2, 2, 10, 2, scale, sparse)
+
+
+# 640 octs: the ancestors of the first tree's level 6 on levels 1-5 stay below,
+# those of the second one's go beyond it at level 5, alone or with those below
+@pytest.mark.parametrize("base,lmax,radius,lcoarse,nu1,nu2,ncoarse", [
+    (5, 6, 0.12, 1, 2, 2, 50), (5, 6, 0.3, 1, 2, 2, 50), (5, 6, 0.3, 5, 2, 2, 7), (5, 7, 0.1, 3, 1, 3, 5),
+    (6, 6, 0.0, 1, 3, 1, 4),
+    (5, 5, 0.0, 4, 2, 1, 6), (4, 4, 0.0, 4, 2, 2, 3)])
+def test_level_passes(base, lmax, radius, lcoarse, nu1, nu2, ncoarse):
+    api = _api()
+    ijkl = I.sphere_tree(base, lmax, (0.31, 0.62, 0.44), radius, I.PERIODIC) if lmax > base else I.uniform_tree(base)
+    T, D = O.Tree(ijkl, I.PERIODIC), api.DeviceTree(ijkl, I.PERIODIC)
+    rng = np.random.default_rng(base * 10 + lmax)
+    f = rng.standard_normal(8 * T.n)
+    c = slice(8 * T.level_begin[base], 8 * T.level_begin[base + 1])
+    f[c] -= f[c].mean()
+    ref = np.zeros(8 * T.n)
+    fd = torch.as_tensor(f).cuda()
+    phi = torch.zeros_like(fd)
+    for l in range(base, lmax + 1):
+        h = api.MgLevel(D, l, lcoarse)
+        for _ in range(2):   # the values across the level's boundary are taken anew by every call
+            O.mg_amr_level(T, ref, f, l, 1, lcoarse, nu1, nu2, ncoarse)
+            h.vcycles(phi, fd, 1, nu1, nu2, ncoarse)
+        cl = slice(8 * T.level_begin[l], 8 * T.level_begin[l + 1])
+        assert np.array_equal(phi[cl].cpu().numpy(), ref[cl]), l
+        assert np.array_equal(h.residual(phi, fd).cpu().numpy(), O.mg_amr_residual(T, ref, f, l)), l
+        h.close()
