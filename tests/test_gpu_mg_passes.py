@@ -5,7 +5,7 @@ the sizes where they change hands, bit for bit against the oracle.
   coarsest levels in bricks, odd and unequal sweep counts (the last of an odd
   number runs colour by colour), no sweeps after the correction.
 - Level by level: a complete level in bricks with odd sweep counts; a tree
-  whose hierarchy crosses the tail's bound of 640 octs; a tail that starts
+  whose hierarchy crosses the tail's bound of 1120 octs; a tail that starts
   above level 1; right-hand sides with zeros and values near the ends of the
   exponent range (the tail's division falls back to the general one)."""
 import numpy as np
@@ -60,10 +60,12 @@ def test_unigrid_range(scale, sparse):
     _unigrid(4, 1, 2, 2, 10, 2, scale, sparse)
 
 
-# 640 octs: the ancestors of the first tree's level 6 on levels 1-5 stay below,
-# those of the second one's go beyond it at level 5, alone or with those below
+# 1120 octs: the ancestors of the first two trees' level 6 stay below, alone
+# more than the 512 that one round of the tail's threads holds in the second
+# tree; those of the third one go beyond, with the levels below or alone
 @pytest.mark.parametrize("base,lmax,radius,lcoarse,nu1,nu2,ncoarse", [
-    (5, 6, 0.12, 1, 2, 2, 50), (5, 6, 0.3, 1, 2, 2, 50), (5, 6, 0.3, 5, 2, 2, 7), (5, 7, 0.1, 3, 1, 3, 5),
+    (5, 6, 0.12, 1, 2, 2, 50), (5, 6, 0.3, 1, 2, 2, 50), (5, 6, 0.4, 1, 2, 2, 50),
+    (5, 6, 0.3, 5, 2, 2, 7), (5, 6, 0.4, 5, 1, 2, 7), (5, 7, 0.1, 3, 1, 3, 5),
     (6, 6, 0.0, 1, 3, 1, 4),
     (5, 5, 0.0, 4, 2, 1, 6), (4, 4, 0.0, 4, 2, 2, 3)])
 def test_level_passes(base, lmax, radius, lcoarse, nu1, nu2, ncoarse):
