@@ -101,8 +101,8 @@ rg_status check_sink(int64_t *h_bad_index, hipStream_t s)
 
 struct LevelArgs;
 rg_status hydro_level(const LevelArgs &a, int form, const rg_tuning *tune, hipStream_t s);
-rg_status coarse_corrections_list(double *unew, const double *corr, int64_t corr_base, const int32_t *nbr27,
-                                  const int32_t *list, int64_t count, hipStream_t s);
+rg_status tree_corrections(const rg_tree *t, double *unew, const double *corr, const int32_t *list, int64_t ob,
+                           int64_t oe, double gamma, double cfl, double *dt_next, hipStream_t s);
 
 }  // namespace rg
 
@@ -201,18 +201,20 @@ rg_status rg_step(const rg_tree *t, const double *d_uold, double *d_unew, double
         }
     }
     if (t->lmax > t->lmin) {
-        if (t->sched) {
+        if (t->d_keys) {
             // the border lists of all levels above lmin follow each other
             const rg_schedule *sc = t->sched;
-            const int64_t b = sc->border_begin[t->lmin + 1];
-            const int64_t e = sc->border_begin[t->lmax] + sc->border_count[t->lmax];
-            RG_TRY(coarse_corrections_list(d_unew, t->d_corr, corr_base, t->d_nbr27, sc->d_list + b, e - b, s));
+            const int64_t ob = sc ? 0 : corr_base;
+            const int64_t oe = sc ? sc->border_begin[t->lmax] + sc->border_count[t->lmax] -
+                                        sc->border_begin[t->lmin + 1] : t->n_oct;
+            RG_TRY(tree_corrections(t, d_unew, t->d_corr, sc ? sc->d_list + sc->border_begin[t->lmin + 1] : nullptr,
+                                    ob, oe, gamma, cfl, dt_next, s));
         } else {
             RG_TRY(rg_apply_coarse_corrections(d_unew, t->d_corr, corr_base, t->d_nbr27, corr_base, t->n_oct, stream));
+            if (chain)
+                RG_TRY(rg_cfl_dt_corrected(d_unew, t->d_nbr27, t->level_begin, t->lmin, t->lmax, gamma, cfl, dt_next,
+                                           stream));
         }
-        if (chain)
-            RG_TRY(rg_cfl_dt_corrected(d_unew, t->d_nbr27, t->level_begin, t->lmin, t->lmax, gamma, cfl, dt_next,
-                                       stream));
         for (int l = t->lmax; l > t->lmin; --l)
             RG_TRY(rg_restrict_level(d_unew, t->d_father_cell, t->level_begin[l], t->level_begin[l + 1], stream));
     }

@@ -18,6 +18,7 @@
 // All intermediate data stay in LDS; HBM sees uold (stencil reads, mostly
 // L2 hits between neighbouring octs), the neighbour list and unew.
 #include "rg_internal.hpp"
+#include "rg_corr.hpp"
 #include "rg_math.hpp"
 #include "rg_oct.hpp"
 #include "rg_sib.hpp"
@@ -62,8 +63,13 @@ struct DtArgs {
 
 __global__ void k_set_u64(unsigned long long *p, unsigned long long v) { *p = v; }
 
-// Grid-stride over cells: a bounded grid keeps the final atomics few.
-__global__ __launch_bounds__(256) void k_cfl_dt(DtArgs a)
+// Grid-stride over cells.  At most 512 workgroups of 1024 threads: workgroups
+// that end together all find the stored limit above theirs, and their atomics
+// on one address queue up (2048 workgroups: 21 us on 0.5 M cells).
+constexpr int kDtThreads = 1024;
+constexpr unsigned kDtBlocks = 512;
+
+__global__ __launch_bounds__(kDtThreads) void k_cfl_dt(DtArgs a)
 {
     double best = __longlong_as_double(0x7ff0000000000000ll);   // +inf
     double nf = 0.0;
@@ -88,34 +94,20 @@ __global__ __launch_bounds__(256) void k_cfl_dt(DtArgs a)
         if (cd < best) best = cd;
         track_finite(nf, sp, U);
     }
-    best = nonfinite_limit(best, nf);
     // wavefront minimum, then across the block's waves, then one atomic
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        double o = __shfl_xor(best, off, 64);
-        best = o < best ? o : best;
-    }
-    __shared__ double s_min[4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) s_min[wave] = best;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double m = s_min[0];
-        for (int k = 1; k < (int)(blockDim.x >> 6); ++k) m = s_min[k] < m ? s_min[k] : m;
-        fold_min(a.dt_bits, m, a.hdr);
-    }
+    __shared__ double s_min[kDtThreads / 64];
+    fold_block(best, nf, s_min, kDtThreads, a.dt_bits, a.hdr);
 }
 
-// octs ob..oe, or list[ob..oe) when a list is given
+// one side of the corrections of octs ob..oe (rg_apply_coarse_corrections,
+// which is given no keys)
 __global__ void k_coarse_corr(double *__restrict__ unew, const double *__restrict__ corr, int64_t corr_base,
-                              const int32_t *__restrict__ nbr27, const int32_t *__restrict__ list, int64_t ob,
-                              int64_t oe, int side)
+                              const int32_t *__restrict__ nbr27, int64_t ob, int64_t oe, int side)
 {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t i = ob + t / NV;
+    const int64_t o = ob + t / NV;
     const int v = static_cast<int>(t % NV);
-    if (i >= oe) return;
-    const int64_t o = list ? int64_t(list[i]) : i;
+    if (o >= oe) return;
     const int ax = side >> 1, hi = side & 1;
     const int slot = nslot(ax == 0 ? (hi ? 1 : -1) : 0, ax == 1 ? (hi ? 1 : -1) : 0, ax == 2 ? (hi ? 1 : -1) : 0);
     const int32_t e = nbr27[27 * o + slot];
@@ -153,20 +145,25 @@ __global__ __launch_bounds__(256) void k_cfl_dt_corrected(DtArgs a, const int32_
         if (cd < best) best = cd;
         track_finite(nf, sp, U);
     }
-    best = nonfinite_limit(best, nf);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        double o = __shfl_xor(best, off, 64);
-        best = o < best ? o : best;
-    }
     __shared__ double s_min[4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) s_min[wave] = best;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double m = s_min[0];
-        for (int k = 1; k < (int)(blockDim.x >> 6); ++k) m = s_min[k] < m ? s_min[k] : m;
-        fold_min(a.dt_bits, m, a.hdr);
+    fold_block(best, nf, s_min, 256, a.dt_bits, a.hdr);
+}
+
+// Every coarse-fine correction of octs ob..oe (or list[ob..oe)) in one pass,
+// six threads per oct (see correct_cell), with the corrected cells' CFL limit
+// folded into dt_next if set.
+__global__ __launch_bounds__(256) void k_corrections(CorrTree a, const int32_t *__restrict__ list, int64_t ob,
+                                                     int64_t oe, unsigned long long *dt_next, HashHeader *hdr)
+{
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t i = ob + t / 6;
+    double best = __longlong_as_double(0x7ff0000000000000ll);
+    double nf = 0.0;
+    if (i < oe)
+        correct_cell(a, list ? int64_t(list[i]) : i, static_cast<int>(t % 6), dt_next != nullptr, best, nf);
+    if (dt_next) {
+        __shared__ double s_min[4];
+        fold_block(best, nf, s_min, 256, dt_next, hdr);
     }
 }
 
@@ -297,17 +294,28 @@ rg_status hydro_groups_list(const double *uold, double *unew, const int32_t *nbr
     return launch_sib_form<float>(a, father, tune, s);
 }
 
-// coarse-fine corrections from the octs list[0..count), side by side
-rg_status coarse_corrections_list(double *unew, const double *corr, int64_t corr_base, const int32_t *nbr27,
-                                  const int32_t *list, int64_t count, hipStream_t s)
+// coarse-fine corrections of unew owed by octs [ob, oe) of tree t (list[ob..oe)
+// when a list is given); with dt_next, the corrected cells' CFL limits folded
+// into it
+rg_status tree_corrections(const rg_tree *t, double *unew, const double *corr, const int32_t *list, int64_t ob,
+                           int64_t oe, double gamma, double cfl, double *dt_next, hipStream_t s)
 {
-    if (count <= 0) return RG_OK;
-    const int64_t items = count * NV;
-    for (int side = 0; side < 6; ++side) {
-        k_coarse_corr<<<grid_for(items, 256), 256, 0, s>>>(unew, corr, corr_base, nbr27, list, 0, count, side);
-        RG_TRY(launch_status("coarse corrections"));
-    }
-    return RG_OK;
+    if (oe <= ob) return RG_OK;
+    CorrTree a;
+    a.unew = unew;
+    a.corr = corr;
+    a.corr_base = t->level_begin[t->lmin + 1];
+    a.nbr27 = t->d_nbr27;
+    a.son = t->d_son_mask;
+    a.keys = t->d_keys;
+    for (int l = 0; l < RG_MAX_LEVEL + 2; ++l) a.begin[l] = t->level_begin[l];
+    a.lmin = t->lmin;
+    a.lmax = t->lmax;
+    a.gamma = gamma;
+    a.cfl = cfl;
+    k_corrections<<<grid_for(6 * (oe - ob), 256), 256, 0, s>>>(
+        a, list, ob, oe, reinterpret_cast<unsigned long long *>(dt_next), current_sink());
+    return launch_status("coarse-fine corrections");
 }
 
 // restriction of octs [ob, oe) from src into their father cells in dst
@@ -346,8 +354,8 @@ rg_status cfl_dt_pass(const double *d_u, const uint32_t *d_son_mask, const int64
     k_set_u64<<<1, 1, 0, s>>>(a.dt_bits, 0x7ff0000000000000ull);
     RG_TRY(launch_status("rg_cfl_dt init"));
     if (a.n_cell == 0) return RG_OK;
-    const unsigned blocks = grid_for(a.n_cell, 256);
-    k_cfl_dt<<<blocks < 2048 ? blocks : 2048, 256, 0, s>>>(a);
+    const unsigned blocks = grid_for(a.n_cell, kDtThreads);
+    k_cfl_dt<<<blocks < kDtBlocks ? blocks : kDtBlocks, kDtThreads, 0, s>>>(a);
     return launch_status("rg_cfl_dt");
 }
 
@@ -406,8 +414,8 @@ rg_status rg_apply_coarse_corrections(double *d_unew, const double *d_corr, int6
     hipStream_t s = as_stream(stream);
     const int64_t items = (oct_end - oct_begin) * NV;
     for (int side = 0; side < 6; ++side) {
-        k_coarse_corr<<<grid_for(items, 256), 256, 0, s>>>(d_unew, d_corr, corr_base, d_nbr27, nullptr, oct_begin,
-                                                           oct_end, side);
+        k_coarse_corr<<<grid_for(items, 256), 256, 0, s>>>(d_unew, d_corr, corr_base, d_nbr27, oct_begin, oct_end,
+                                                           side);
         RG_TRY(launch_status("rg_apply_coarse_corrections"));
     }
     return RG_OK;

@@ -27,8 +27,8 @@ rg_status hydro_tree_level(const rg_tree *t, const rg_schedule *sc, int level, c
                            int corr_mode, const double *d_ucoarse2);
 rg_status restrict_level2(const double *src, double *dst, const int32_t *father, int64_t ob, int64_t oe,
                           hipStream_t s);
-rg_status coarse_corrections_list(double *unew, const double *corr, int64_t corr_base, const int32_t *nbr27,
-                                  const int32_t *list, int64_t count, hipStream_t s);
+rg_status tree_corrections(const rg_tree *t, double *unew, const double *corr, const int32_t *list, int64_t ob,
+                           int64_t oe, double gamma, double cfl, double *dt_next, hipStream_t s);
 rg_status cfl_dt_pass(const double *d_u, const uint32_t *d_son_mask, const int64_t *h_level_begin, int lmin, int lmax,
                       double gamma, double cfl, double *d_dt, int sub, void *stream);
 
@@ -68,16 +68,14 @@ rg_status advance(Sub &c, int l, int sub)
                                 c.form, c.tune, c.s, c.acc, 1 + sub, coarse2));
     if (l < t->lmax) {
         const int64_t fb = t->level_begin[l + 1], fe = t->level_begin[l + 2];
-        const int64_t base = t->level_begin[t->lmin + 1];
         for (int s2 = 0; s2 < 2; ++s2) RG_TRY(advance(c, l + 1, s2));
         if (fe > fb) {
-            if (t->sched) {
-                const rg_schedule *sc = t->sched;
-                RG_TRY(coarse_corrections_list(out, c.acc, base, t->d_nbr27, sc->d_list + sc->border_begin[l + 1],
-                                               sc->border_count[l + 1], c.s));
-            } else {
-                RG_TRY(rg_apply_coarse_corrections(out, c.acc, base, t->d_nbr27, fb, fe, c.s));
-            }
+            const rg_schedule *sc = t->sched;
+            if (t->d_keys)
+                RG_TRY(tree_corrections(t, out, c.acc, sc ? sc->d_list + sc->border_begin[l + 1] : nullptr,
+                                        sc ? 0 : fb, sc ? sc->border_count[l + 1] : fe, c.gamma, 0.0, nullptr, c.s));
+            else
+                RG_TRY(rg_apply_coarse_corrections(out, c.acc, t->level_begin[t->lmin + 1], t->d_nbr27, fb, fe, c.s));
             RG_TRY(restrict_level2(c.buf[c.cur[l + 1]], out, t->d_father_cell, fb, fe, c.s));
         }
     }
