@@ -784,7 +784,7 @@ def main():
         # the box is a complete periodic level: its bricks go two by two
         # along z unless the chosen variant turns that off
         single = r["tune"] is not None and len(r["tune"]) > 7 and r["tune"][7]
-        kernel = "k_hydro_brick" if single else "k_hydro_brick_pair"
+        kernel = "k_hydro_brick" if single else "k_hydro_column"
         return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic(f),
                 "copy_ceiling": round(copy_gbs, 1), "frac_of_copy": round(achieved / copy_gbs, 4),

@@ -244,8 +244,8 @@ typedef struct rg_tuning {
                                  (FP64: 2 or 3, mixed: 3 or 4; 0 = default: 2 for FP64, 3 mixed) */
     int32_t no_groups;        /* 1: scheduled updates leave complete sibling groups to the per-oct kernel */
     int32_t group_threads;    /* sibling-group kernel workgroup size: 256, 320 or 384 (0 = default) */
-    int32_t no_pairs;         /* 1: a complete periodic finest level's bricks one by one, not two
-                                 stacked along z per workgroup (the same bits either way) */
+    int32_t no_pairs;         /* 1: a complete finest level by its bricks, not by columns cut into
+                                 segments of the length that fills the chip (the same bits either way) */
 } rg_tuning;
 
 /* Kernel schedule of a tree.  A brick is a Hilbert-aligned cube of 8x8x8
@@ -431,9 +431,10 @@ rg_status rg_prepare_tree(const rg_tree *t, unsigned flags, void *stream);
  *   rg_cfl_dt) and the next step's dt is computed from unew inside the level
  *   updates plus rg_cfl_dt_corrected into d_dt[1], saving the separate pass
  *   over the state (so a chain of steps s = 0, 1, ... passes d_dt + s);
- *   every level: rg_hydro_step_scheduled if t->sched is set, else
- *   rg_hydro_step_level over the level (uold -> unew);
- *   rg_apply_coarse_corrections over all levels above lmin (restricted to
+ *   every level: rg_hydro_step_scheduled if t->sched is set (one launch per
+ *   kernel for all levels), else rg_hydro_step_level over the level (uold ->
+ *   unew);
+ *   rg_apply_coarse_corrections over all levels above lmin (in one pass, over
  *   the schedule's border lists when t->sched is set: same bits);
  *   rg_restrict_level from lmax down to lmin + 1 on unew.
  * The caller swaps uold and unew afterwards. */

@@ -99,8 +99,10 @@ rg_status check_sink(int64_t *h_bad_index, hipStream_t s)
     return RG_OK;
 }
 
-struct LevelArgs;
-rg_status hydro_level(const LevelArgs &a, int form, const rg_tuning *tune, hipStream_t s);
+rg_status hydro_tree_levels(const rg_tree *t, const rg_schedule *sc, int l0, int l1, const double *d_dt, double gamma,
+                            const double *d_uold, const double *d_ucoarse, double *d_unew, double cfl,
+                            double *d_dt_next, int form, const rg_tuning *tune, hipStream_t s, double *d_corr,
+                            int corr_mode, const double *d_ucoarse2);
 rg_status tree_corrections(const rg_tree *t, double *unew, const double *corr, const int32_t *list, int64_t ob,
                            int64_t oe, double gamma, double cfl, double *dt_next, hipStream_t s);
 
@@ -176,6 +178,8 @@ rg_status rg_step(const rg_tree *t, const double *d_uold, double *d_unew, double
     RG_REQUIRE((flags & ~(RG_STEP_REBUILD | RG_STEP_REKEY | RG_STEP_CHAIN_DT)) == 0, "unknown flags %u", flags);
     RG_REQUIRE(gamma > 1 && cfl > 0, "bad gamma or cfl");
     RG_REQUIRE(t->ghost == RG_GHOST_INJECT || t->ghost == RG_GHOST_LINEAR, "bad ghost mode %d", t->ghost);
+    RG_REQUIRE(d_uold != d_unew, "uold and unew must not alias");
+    RG_REQUIRE(form == RG_FP64 || form == RG_MIXED, "bad form %d", form);
     hipStream_t s = as_stream(stream);
     const SinkScope sink(t->d_hash_ws);
     const unsigned prep = flags & (RG_STEP_REBUILD | RG_STEP_REKEY);
@@ -188,18 +192,8 @@ rg_status rg_step(const rg_tree *t, const double *d_uold, double *d_unew, double
         RG_TRY(rg_cfl_dt(d_uold, t->d_son_mask, t->level_begin, t->lmin, t->lmax, gamma, cfl, d_dt, stream));
     }
     const int64_t corr_base = t->level_begin[t->lmin + 1];
-    for (int l = t->lmin; l <= t->lmax; ++l) {
-        const int64_t b = t->level_begin[l], e = t->level_begin[l + 1];
-        if (e == b) continue;
-        if (t->sched) {
-            RG_TRY(rg_hydro_step_scheduled(t, t->sched, l, d_dt, gamma, d_uold, d_unew, cfl, dt_next, form, tune,
-                                           stream));
-        } else {
-            RG_TRY(rg_hydro_step_level(ldexp(1.0, -l), d_dt, gamma, d_uold, d_unew, t->d_nbr27, t->d_son_mask, b, e,
-                                       l > t->lmin ? t->d_corr : nullptr, corr_base, cfl, dt_next, form, tune,
-                                       stream));
-        }
-    }
+    RG_TRY(hydro_tree_levels(t, t->sched, t->lmin, t->lmax, d_dt, gamma, d_uold, d_uold, d_unew, cfl, dt_next, form,
+                             tune, s, t->d_corr, 0, d_uold));
     if (t->lmax > t->lmin) {
         if (t->d_keys) {
             // the border lists of all levels above lmin follow each other

@@ -164,7 +164,8 @@ __global__ __launch_bounds__(BT, sizeof(R) == 8 ? 2 : 3) void k_batch_bricks(con
         a.son = T.son;
         a.keys = T.keys;
         a.bricks = nullptr;
-        a.nbricks = 0;
+        a.first = 0;
+        a.nb = 0;
         a.dt = dt + I.tree;
         a.dx = ldexp(1.0, -(I.a >> 2));
         a.gamma = T.gamma;
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(BT, sizeof(R) == 8 ? 2 : 3) void k_batch_bricks(con
         a.cfl = T.cfl;
         a.dt_next = reinterpret_cast<unsigned long long *>(dt_next + I.tree);
         a.hdr = T.hdr;
-        brick_body<R, sizeof(R) == 8>(a, T.list[I.first], I.first, S);
+        brick_body<R, sizeof(R) == 8>(a, T.list[I.first], I.first, 0, BC, S);
         __syncthreads();
     }
 }
@@ -201,8 +202,7 @@ __global__ __launch_bounds__(kT) void k_batch_octs(const BTree *__restrict__ tre
         a.corr_mode = 0;
         a.ghost = T.ghost;
         a.ucoarse2 = T.u[parity];
-        a.oct_begin = I.first;
-        a.oct_end = I.first + I.count;
+        a.oct_begin = 0;
         a.dt = dt + I.tree;
         a.dx = ldexp(1.0, -level);
         a.gamma = T.gamma;
@@ -238,8 +238,7 @@ __global__ __launch_bounds__(kT) void k_batch_groups(const BTree *__restrict__ t
         a.corr_mode = 0;
         a.ghost = T.ghost;
         a.ucoarse2 = T.u[parity];
-        a.oct_begin = I.first;
-        a.oct_end = I.first + 1;
+        a.oct_begin = 0;
         a.dt = dt + I.tree;
         a.dx = ldexp(1.0, -level);
         a.gamma = T.gamma;

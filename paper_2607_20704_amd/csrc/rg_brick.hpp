@@ -24,7 +24,6 @@ struct BrickArgs {
     const uint32_t *son;
     const uint64_t *keys;
     const int32_t *bricks;     // first oct of each brick
-    int64_t nbricks;
     const double *dt;
     double dx;
     double gamma;
@@ -32,6 +31,8 @@ struct BrickArgs {
     double cfl;
     unsigned long long *dt_next;   // if set: CFL limit of the new state folded in (bits of a positive double)
     HashHeader *hdr;               // device-side errors (non-finite state)
+    int64_t first;                 // columns of a complete level: its first oct and bits per oct coordinate
+    int nb;
 };
 
 // LDS holds every 5-variable quantity as five planes, one per variable
@@ -78,17 +79,66 @@ template <typename R> __device__ __forceinline__ void ring_put(BrickFaces<R> &F,
     for (int v = 0; v < NV; ++v) flat[base + v * stride] = src[v];
 }
 
+struct Geom {
+    int cx0, cy0, cz0;   // global cell coordinates of the sweep's origin
+    int ncell;           // cells per side of the level
+    int outflow;
+};
+
+// Where the octs around a sweep are: the slot (sa, sb, sc) is the oct sa, sb,
+// sc octs from the sweep's first one.
+//
+// BrickTable: a brick, or a slab of it, with every slot around it held at
+// once: inside the brick the octs' own indices, outside the entries of their
+// neighbour lists.
+struct BrickTable {
+    static constexpr bool rolling = false;
+    int32_t slot[HS * HS * HS];   // oct index, or the list's entry for a missing one
+    uint8_t son[HS * HS * HS];    // son mask of same-level slot octs, 0 otherwise
+
+    static __device__ __forceinline__ int at(int sa, int sb, int sc)
+    {
+        return (sa + 1) + HS * (sb + 1) + HS * HS * (sc + 1);
+    }
+};
+
+// ColumnTable: a column of a complete level, four planes of octs at a time.
+// An oct's index on such a level is its position on the Hilbert curve, so a
+// plane of slots is computed from coordinates, two planes of octs ahead of
+// the sweep, and no neighbour list is read.
+struct ColumnTable {
+    static constexpr bool rolling = true;
+    int32_t slot[4 * HS * HS];
+
+    static __device__ __forceinline__ int at(int sa, int sb, int sc)
+    {
+        return (sa + 1) + HS * (sb + 1) + HS * HS * (sc & 3);
+    }
+
+    // slot k = 0..99 of plane sc; the octs of the level start at `first`
+    __device__ __forceinline__ void fill(const Geom &g, int64_t first, int nb, int k, int sc)
+    {
+        const int sa = k % HS - 1, sb = k / HS - 1;
+        const int n = 1 << nb;
+        int i = (g.cx0 >> 1) + sa, j = (g.cy0 >> 1) + sb, l = (g.cz0 >> 1) + sc;
+        // beyond a wall no slot is read; any oct will do
+        i = g.outflow ? min(max(i, 0), n - 1) : i & (n - 1);
+        j = g.outflow ? min(max(j, 0), n - 1) : j & (n - 1);
+        l = g.outflow ? min(max(l, 0), n - 1) : l & (n - 1);
+        slot[at(sa, sb, sc)] = static_cast<int32_t>(
+            first + static_cast<int64_t>(hilbert_index_bits(static_cast<uint32_t>(i), static_cast<uint32_t>(j),
+                                                            static_cast<uint32_t>(l), nb)));
+    }
+};
+
 // NB = 2: two face buffers and two split-flag planes (planes of even and odd
-// z), which saves one barrier per plane (see brick_body) for 23 KB more LDS
+// z), which saves one barrier per plane (see brick_sweep) for 23 KB more LDS
 // in FP64 -- free at two workgroups per CU, which the FP64 kernel's registers
 // allow anyway; NB = 1 for variants that fit more workgroups.
-// NZ = 2: two bricks stacked along z swept as one column of 32 planes (the
-// slot table then spans octs -1..16 in z).
-template <typename R, int NB = 1, int NZ = 1> struct BrickSmem {
+template <typename R, int NB = 1, typename TAB = BrickTable> struct BrickSmem {
+    using Table = TAB;
     BrickFaces<R> u_[NB];           // face states and fluxes (NB = 2: planes of even / odd z)
-    int32_t slot[HS * HS * (BO * NZ + 2)];   // oct slots -1..8 (z: -1..8 NZ) around the brick(s): oct
-                                             // index inside, neighbour entry outside
-    uint8_t son[HS * HS * (BO * NZ + 2)];    // son mask of same-level slot octs, 0 otherwise
+    TAB tab;                        // octs around the sweep
     R w[NV][PW * PW];               // primitive variables of the current plane
     R hw[3][NV][4 * BC];            // primitive variables of the reconstructed ghost ring, planes r-1, r, r+1
     uint8_t split[NB][PW * PW];     // split flags of the current plane's cells
@@ -100,23 +150,14 @@ template <typename R, int NB = 1, int NZ = 1> struct BrickSmem {
     double acc[NV][(sizeof(R) == 4 && NB == 1) ? BT : 1];
 };
 
-struct Geom {
-    int cx0, cy0, cz0;   // global cell coordinates of the brick origin
-    int ncell;           // cells per side of the level
-    int outflow;
-};
-
-// slot index of the oct slot (sa, sb, sc) in [-1, 8]^3
-__device__ __forceinline__ int slot_index(int sa, int sb, int sc) { return (sa + 1) + HS * (sb + 1) + HS * HS * (sc + 1); }
-
-// Source of the cell at brick-relative position (x, y, z): its global cell
+// Source of the cell at sweep-relative position (x, y, z): its global cell
 // id, and whether it is a split cell.  Outside the domain (outflow) the
 // position takes the nearest cell inside (zero gradient) and counts as not
 // split; a missing same-level oct gives its coarse cell (injection).  GEN =
-// false: the brick has no split cell in reach and no position outside the
-// domain (checked once per brick), so neither is looked at.
-template <bool GEN, typename SM>
-__device__ __forceinline__ int64_t source_cell(const SM &S, const Geom &g, int x, int y, int z, bool &split)
+// false: the sweep has no split cell in reach and no position outside the
+// domain (checked once per sweep), so neither is looked at.
+template <bool GEN, typename TAB>
+__device__ __forceinline__ int64_t source_cell(const TAB &T, const Geom &g, int x, int y, int z, bool &split)
 {
     bool clamped = false;
     if (GEN && g.outflow) {
@@ -129,11 +170,16 @@ __device__ __forceinline__ int64_t source_cell(const SM &S, const Geom &g, int x
         if (gz >= g.ncell) { z = g.ncell - 1 - g.cz0; clamped = true; }
     }
     const int bit = (x & 1) + 2 * (y & 1) + 4 * (z & 1);
-    const int si = slot_index(x >> 1, y >> 1, z >> 1);
-    int32_t e = S.slot[si];
-    split = GEN && !clamped && ((S.son[si] >> bit) & 1u);
-    if (e == RG_NBR_OUTSIDE) e = S.slot[slot_index(0, 0, 0)];   // unreachable for a consistent list
-    return e >= 0 ? 8 * int64_t(e) + bit : (-1 - int64_t(e));
+    const int si = TAB::at(x >> 1, y >> 1, z >> 1);
+    int32_t e = T.slot[si];
+    if constexpr (TAB::rolling) {
+        split = false;
+        return 8 * int64_t(e) + bit;
+    } else {
+        split = GEN && !clamped && ((T.son[si] >> bit) & 1u);
+        if (e == RG_NBR_OUTSIDE) e = T.slot[TAB::at(0, 0, 0)];   // unreachable for a consistent list
+        return e >= 0 ? 8 * int64_t(e) + bit : (-1 - int64_t(e));
+    }
 }
 
 __device__ __forceinline__ void load_u(const double *__restrict__ u, int64_t cell, double *U)
@@ -222,40 +268,41 @@ __device__ __forceinline__ double signal_speed(const double *U, double gamma)
     return ((fabs(Wn[1]) + fabs(Wn[2])) + fabs(Wn[3])) + 3.0 * cs;
 }
 
-// One brick (first oct `base`) by one workgroup of BT threads, each owning
-// an interior column.  The ghost ring (loads of the two-cell halo,
+// A sweep over nz (even) planes of 16 x 16 cells by one workgroup of BT
+// threads, each owning a column.  The ghost ring (loads of the two-cell halo,
 // reconstruction of the face layer x = -1, 16 / y = -1, 16, the fluxes of
 // the faces x = 16 / y = 16) is shared out to whole waves, with the roles
-// rotated by the brick index b so that the extra work lands on a different
-// SIMD from brick to brick.  (A fifth wave holding the whole ring measured
+// rotated by the sweep's index b so that the extra work lands on a different
+// SIMD from sweep to sweep.  (A fifth wave holding the whole ring measured
 // slower: the column waves wait for it at every barrier.)
 //
 // KU: keep each column's conserved state of the current plane in registers
 // until the update instead of reading it again (10 more registers, one
 // 40-byte read per cell less).
 //
-// GEN: the brick has a split cell within reach of its stencil, or an
+// GEN: the sweep has a split cell within reach of its stencil, or an
 // outflow wall within two cells; otherwise (GEN = false, decided once per
-// brick) the sweep skips the split flags, the zeroed fluxes, the leaf tests
-// of the folded time step and the clamping at walls.  Both give the same
-// bits where both apply.
-template <typename R, bool KU, int NB, bool GEN, int NZ>
-__device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const Geom &g, BrickSmem<R, NB, NZ> &S);
+// sweep) it skips the split flags, the zeroed fluxes, the leaf tests of the
+// folded time step and the clamping at walls.  Both give the same bits where
+// both apply.
+template <typename R, bool KU, int NB, bool GEN, typename TAB>
+__device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const Geom &g, BrickSmem<R, NB, TAB> &S,
+                                            int nz);
 
-// Slot table and geometry of the brick whose first oct is `base` (NZ = 2:
-// and of the brick directly above it, first oct `base2`), built by NT
-// threads; returns GEN (see brick_sweep) for the brick(s).
-template <int NT, int NZ, typename SM>
-__device__ __forceinline__ bool brick_setup(const BrickArgs &a, int64_t base, int64_t base2, SM &S, Geom &g)
+// Slot table and geometry of planes [z0, z0 + nz) of the brick whose first
+// oct is `base`, built by NT threads; returns GEN (see brick_sweep).
+template <int NT, typename SM>
+__device__ __forceinline__ bool brick_setup(const BrickArgs &a, int64_t base, int z0, int nz, SM &S, Geom &g)
 {
-    constexpr int ZO = BO * NZ;   // octs along z
     const int tid = threadIdx.x;
-    for (int k = tid; k < NZ * BO * BO * BO; k += NT) {
-        const bool upper = k >= BO * BO * BO;
-        const int64_t o = upper ? base2 + (k - BO * BO * BO) : base + k;
+    BrickTable &T = S.tab;
+    const int c0 = z0 >> 1, nc = nz >> 1;   // the slab's planes of octs
+    for (int k = tid; k < BO * BO * BO; k += NT) {
+        const int64_t o = base + k;
         int32_t i, j, kk, l;
         key_coords(a.keys[o], i, j, kk, l);
-        S.slot[slot_index(i & 7, j & 7, (kk & 7) + (upper ? BO : 0))] = static_cast<int32_t>(o);
+        const int sc = (kk & 7) - c0;
+        if (sc >= -1 && sc <= nc) T.slot[T.at(i & 7, j & 7, sc)] = static_cast<int32_t>(o);
     }
     if (tid == 0) S.any_son = 0;
     {
@@ -263,51 +310,75 @@ __device__ __forceinline__ bool brick_setup(const BrickArgs &a, int64_t base, in
         key_coords(a.keys[base], i, j, kk, l);
         g.cx0 = 2 * (i & ~7);
         g.cy0 = 2 * (j & ~7);
-        g.cz0 = 2 * (kk & ~7);
+        g.cz0 = 2 * (kk & ~7) + z0;
         g.ncell = 1 << l;
         g.outflow = a.outflow;
     }
     __syncthreads();
-    for (int s = tid; s < HS * HS * (ZO + 2); s += NT) {
+    for (int s = tid; s < HS * HS * (nc + 2); s += NT) {
         const int sa = s % HS - 1, sb = (s / HS) % HS - 1, sc = s / (HS * HS) - 1;
-        const int out = (sa < 0 || sa >= BO) + (sb < 0 || sb >= BO) + (sc < 0 || sc >= ZO);
+        const int bc = sc + c0;   // plane of octs within the brick
+        const int out = (sa < 0 || sa >= BO) + (sb < 0 || sb >= BO) + (bc < 0 || bc >= BO);
         int32_t e = RG_NBR_OUTSIDE;
         if (out == 0) {
-            e = S.slot[s];
+            e = T.slot[s];
         } else if (out <= 2) {
             // the nearest brick oct and its neighbour entry towards this slot
             const int ca = sa < 0 ? 0 : (sa >= BO ? BO - 1 : sa);
             const int cb = sb < 0 ? 0 : (sb >= BO ? BO - 1 : sb);
-            const int cc = sc < 0 ? 0 : (sc >= ZO ? ZO - 1 : sc);
-            const int32_t o = S.slot[slot_index(ca, cb, cc)];
-            e = a.nbr27[27 * int64_t(o) + (sa - ca + 1) + 3 * (sb - cb + 1) + 9 * (sc - cc + 1)];
+            const int cc = bc < 0 ? 0 : (bc >= BO ? BO - 1 : bc);
+            const int32_t o = T.slot[T.at(ca, cb, cc - c0)];
+            e = a.nbr27[27 * int64_t(o) + (sa - ca + 1) + 3 * (sb - cb + 1) + 9 * (bc - cc + 1)];
         }
         const uint8_t m = e >= 0 ? static_cast<uint8_t>(a.son[e]) : 0;
-        S.son[s] = m;
+        T.son[s] = m;
         if (m) S.any_son = 1;
-        if (out) S.slot[s] = e;
+        if (out) T.slot[s] = e;
     }
     __syncthreads();
     const bool wall = g.outflow && (g.cx0 == 0 || g.cy0 == 0 || g.cz0 == 0 || g.cx0 + BC == g.ncell ||
-                                    g.cy0 + BC == g.ncell || g.cz0 + NZ * BC == g.ncell);
+                                    g.cy0 + BC == g.ncell || g.cz0 + nz == g.ncell);
     return S.any_son != 0 || wall;
 }
 
-template <typename R, bool KU = false, int NB = 1, int NZ = 1>
-__device__ __forceinline__ void brick_body(const BrickArgs &a, int64_t base, int64_t b, BrickSmem<R, NB, NZ> &S,
-                                           int64_t base2 = -1)
+// planes [z0, z0 + nz) of the brick whose first oct is `base`
+template <typename R, bool KU = false, int NB = 1>
+__device__ __forceinline__ void brick_body(const BrickArgs &a, int64_t base, int64_t b, int z0, int nz,
+                                           BrickSmem<R, NB, BrickTable> &S)
 {
     Geom g;
-    if (brick_setup<BT, NZ>(a, base, base2, S, g))
-        brick_sweep<R, KU, NB, true, NZ>(a, b, g, S);
+    if (brick_setup<BT>(a, base, z0, nz, S, g))
+        brick_sweep<R, KU, NB, true>(a, b, g, S, nz);
     else
-        brick_sweep<R, KU, NB, false, NZ>(a, b, g, S);
+        brick_sweep<R, KU, NB, false>(a, b, g, S, nz);
 }
 
-template <typename R, bool KU, int NB, bool GEN, int NZ>
-__device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const Geom &g, BrickSmem<R, NB, NZ> &S)
+// planes [z0, z0 + nz) of the column at cells (x0, y0) of a complete level
+// without split cells
+template <typename R, bool KU, int NB>
+__device__ __forceinline__ void column_body(const BrickArgs &a, int x0, int y0, int z0, int nz, int64_t b,
+                                            BrickSmem<R, NB, ColumnTable> &S)
 {
-    constexpr int ZC = NZ * BC;   // planes swept
+    Geom g;
+    g.cx0 = x0;
+    g.cy0 = y0;
+    g.cz0 = z0;
+    g.ncell = 2 << a.nb;
+    g.outflow = a.outflow;
+    for (int k = threadIdx.x; k < 3 * HS * HS; k += BT) S.tab.fill(g, a.first, a.nb, k % (HS * HS), k / (HS * HS) - 1);
+    __syncthreads();
+    const bool wall = g.outflow && (x0 == 0 || y0 == 0 || z0 == 0 || x0 + BC == g.ncell || y0 + BC == g.ncell ||
+                                    z0 + nz == g.ncell);
+    if (wall)
+        brick_sweep<R, KU, NB, true>(a, b, g, S, nz);
+    else
+        brick_sweep<R, KU, NB, false>(a, b, g, S, nz);
+}
+
+template <typename R, bool KU, int NB, bool GEN, typename TAB>
+__device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const Geom &g, BrickSmem<R, NB, TAB> &S,
+                                            int nz)
+{
     const int tid = threadIdx.x;
     const double r = *a.dt / a.dx;
     const R h = static_cast<R>(0.5 * r);
@@ -349,14 +420,14 @@ __device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const
         bool sdummy;
         sp_cur = false;
         {
-            load_u(a.uold, source_cell<GEN>(S, g, x, y, -2, sdummy), U);
+            load_u(a.uold, source_cell<GEN>(S.tab, g, x, y, -2, sdummy), U);
             to_prim(U, a.gamma, Wm);
-            load_u(a.uold, source_cell<GEN>(S, g, x, y, -1, sp_cur), U);
+            load_u(a.uold, source_cell<GEN>(S.tab, g, x, y, -1, sp_cur), U);
             inv0 = to_prim(U, a.gamma, W0);
             if constexpr (KU) copy5(Uc, U);
         }
         if (do_face) {
-            load_u(a.uold, source_cell<GEN>(S, g, hx, hy, -1, sdummy), U);
+            load_u(a.uold, source_cell<GEN>(S.tab, g, hx, hy, -1, sdummy), U);
             R Wh[NV];
             to_prim(U, a.gamma, Wh);
             lds_put(S.hw[2], lane, Wh);
@@ -375,8 +446,8 @@ __device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const
     double Upf[NV];
     if constexpr (PF) {
         bool sdummy;
-        if (do_face) load_u(a.uold, source_cell<GEN>(S, g, hx, hy, 0, sdummy), Upf);
-        if (ring_role) load_u(a.uold, source_cell<GEN>(S, g, rx, ry, 0, sdummy), Upf);
+        if (do_face) load_u(a.uold, source_cell<GEN>(S.tab, g, hx, hy, 0, sdummy), Upf);
+        if (ring_role) load_u(a.uold, source_cell<GEN>(S.tab, g, rx, ry, 0, sdummy), Upf);
     }
     // DB (NB = 2): planes alternate between two face buffers and split-flag
     // planes, so the fluxes of plane rz are read -- and plane rz is updated --
@@ -398,31 +469,31 @@ __device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const
         zp_prev[v] = R(0);
     }
 
-    for (int rz = -1; rz <= ZC; ++rz) {
-        const bool inner = rz >= 0 && rz < ZC;      // plane with x/y faces
+    for (int rz = -1; rz <= nz; ++rz) {
+        const bool inner = rz >= 0 && rz < nz;      // plane with x/y faces
         const int fb = DB ? (rz & 1) : 0;           // this plane's face buffer and split flags
         BrickFaces<R> &FB = S.u_[fb];
         uint8_t *spl = S.split[fb];
         double Un[NV];                               // conserved variables of plane rz+1, own column
         sp_next = false;
-        load_u(a.uold, source_cell<GEN>(S, g, x, y, rz + 1, sp_next), Un);
+        load_u(a.uold, source_cell<GEN>(S.tab, g, x, y, rz + 1, sp_next), Un);
         // 1. the reconstructed ghost ring: primitive variables of plane rz+1
         bool hsplit = false;
         if (do_face) {
-            if (rz + 1 <= ZC) {
+            if (rz + 1 <= nz) {
                 R Wh[NV];
                 bool sdummy;
                 if constexpr (PF) {
                     to_prim(Upf, a.gamma, Wh);
-                    if (rz + 2 <= ZC) load_u(a.uold, source_cell<GEN>(S, g, hx, hy, rz + 2, sdummy), Upf);
+                    if (rz + 2 <= nz) load_u(a.uold, source_cell<GEN>(S.tab, g, hx, hy, rz + 2, sdummy), Upf);
                 } else {
                     double U[NV];
-                    load_u(a.uold, source_cell<GEN>(S, g, hx, hy, rz + 1, sdummy), U);
+                    load_u(a.uold, source_cell<GEN>(S.tab, g, hx, hy, rz + 1, sdummy), U);
                     to_prim(U, a.gamma, Wh);
                 }
                 lds_put(S.hw[(rz + 4) % 3], lane, Wh);
             }
-            (void)source_cell<GEN>(S, g, hx, hy, rz, hsplit);
+            (void)source_cell<GEN>(S.tab, g, hx, hy, rz, hsplit);
         }
         // 2. plane rz into LDS: W and split flags
         {
@@ -438,15 +509,24 @@ __device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const
             bool sdummy;
             if constexpr (PF) {
                 to_prim(Upf, a.gamma, Wr);
-                if (rz + 1 < ZC) load_u(a.uold, source_cell<GEN>(S, g, rx, ry, rz + 1, sdummy), Upf);
+                if (rz + 1 < nz) load_u(a.uold, source_cell<GEN>(S.tab, g, rx, ry, rz + 1, sdummy), Upf);
             } else {
                 double U[NV];
-                load_u(a.uold, source_cell<GEN>(S, g, rx, ry, rz, sdummy), U);
+                load_u(a.uold, source_cell<GEN>(S.tab, g, rx, ry, rz, sdummy), U);
                 to_prim(U, a.gamma, Wr);
             }
             lds_put(S.w, (rx + 2) + PW * (ry + 2), Wr);
         }
         __syncthreads();
+        // the next plane of octs of a column, by the waves that hold no
+        // reconstructed ring and wait for the one that does at the next
+        // barrier; its place was last read two planes ago
+        if constexpr (TAB::rolling) {
+            const int k = lane + (wave == ((ew + 2) & 3) ? 64 : 0);
+            if (!(rz & 1) && (rz >> 1) + 2 <= (nz >> 1) && k < HS * HS &&
+                (wave == ((ew + 1) & 3) || wave == ((ew + 2) & 3)))
+                S.tab.fill(g, a.first, a.nb, k, (rz >> 1) + 2);
+        }
 
         // 3. reconstruction of plane rz: the ghost ring first, then the own
         //    column, whose z face (rz-1 | rz) is evaluated at once
@@ -503,7 +583,7 @@ __device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const
                         copy5(Ucur, Ucp);
                     } else {
                         bool sdummy;
-                        load_u(a.uold, source_cell<GEN>(S, g, x, y, rz - 1, sdummy), Ucur);
+                        load_u(a.uold, source_cell<GEN>(S.tab, g, x, y, rz - 1, sdummy), Ucur);
                     }
 #pragma unroll
                     for (int v = 0; v < NV; ++v) {
@@ -515,7 +595,7 @@ __device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const
                         out[v] = acc + (gz_prev[v] - gz[v]);
                     }
                     bool sdummy;
-                    const int64_t cell = source_cell<GEN>(S, g, x, y, rz - 1, sdummy);
+                    const int64_t cell = source_cell<GEN>(S.tab, g, x, y, rz - 1, sdummy);
 #pragma unroll
                     for (int v = 0; v < NV; ++v) a.unew[NV * cell + v] = out[v];
                     if (a.dt_next && !sp_prev && !(nxy_prev || sp_prev2 || sp_cur)) {
@@ -575,7 +655,7 @@ __device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const
             for (int v = 0; v < NV; ++v)
                 out[v] = (ACC_LDS ? S.acc[v][ACC_LDS ? tid : 0] : acc_prev[v]) + (gz_prev[v] - gz[v]);
             bool sdummy;
-            const int64_t cell = source_cell<GEN>(S, g, x, y, rz - 1, sdummy);
+            const int64_t cell = source_cell<GEN>(S.tab, g, x, y, rz - 1, sdummy);
 #pragma unroll
             for (int v = 0; v < NV; ++v) a.unew[NV * cell + v] = out[v];
             if (a.dt_next && !sp_prev && !(nxy_prev || sp_prev2 || sp_cur)) {
@@ -590,7 +670,7 @@ __device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const
                 copy5(Ucur, Uc);
             } else {
                 bool sdummy;
-                load_u(a.uold, source_cell<GEN>(S, g, x, y, rz, sdummy), Ucur);
+                load_u(a.uold, source_cell<GEN>(S.tab, g, x, y, rz, sdummy), Ucur);
             }
 #pragma unroll
             for (int v = 0; v < NV; ++v) {

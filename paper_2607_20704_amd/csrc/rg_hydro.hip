@@ -26,23 +26,36 @@
 namespace rg {
 namespace {
 
-template <typename R, int G, int NT, bool GH>
-__global__ __launch_bounds__(NT) void k_hydro_level(LevelArgs a)
+// the level of item i (see LevelTab), set in a; returns the item's place
+// among the level's items
+__device__ __forceinline__ int enter_level(LevelArgs &a, const LevelTab &lv, int i, int &count)
 {
-    __shared__ Smem<R, G> S;
-    const int64_t first = a.oct_begin + int64_t(blockIdx.x) * G;
-    const int64_t left = a.oct_end - first;
-    const int count = left < G ? static_cast<int>(left) : G;
-    hydro_group<R, G, NT, GH>(a, first, count, S);
+    const int k = tab_entry(lv, i);
+    count = lv.count[k];
+    a.dx = lv.dx[k];
+    if (a.list) a.list += lv.list0[k];
+    if (!((lv.owes >> k) & 1u)) a.corr = nullptr;
+    return i;
 }
 
-// one complete sibling group per workgroup: list[oct_begin + block] is the
-// group's first oct
+template <typename R, int G, int NT, bool GH>
+__global__ __launch_bounds__(NT) void k_hydro_level(LevelArgs a, LevelTab lv)
+{
+    __shared__ Smem<R, G> S;
+    int count;
+    const int first = G * enter_level(a, lv, static_cast<int>(blockIdx.x), count);
+    hydro_group<R, G, NT, GH>(a, a.oct_begin + first, min(G, count - first), S);
+}
+
+// one complete sibling group per workgroup: the list's entry is the group's
+// first oct
 template <typename R, int NT, bool GH>
-__global__ __launch_bounds__(NT) void k_hydro_sib(LevelArgs a, const int32_t *__restrict__ father)
+__global__ __launch_bounds__(NT) void k_hydro_sib(LevelArgs a, LevelTab lv, const int32_t *__restrict__ father)
 {
     __shared__ SibSmem<R> S;
-    hydro_sib<R, NT, GH>(a, father, a.list[a.oct_begin + blockIdx.x], S);
+    int count;
+    const int i = enter_level(a, lv, static_cast<int>(blockIdx.x), count);
+    hydro_sib<R, NT, GH>(a, father, a.list[i], S);
 }
 
 // ---------------------------------------------------------------------------
@@ -186,112 +199,71 @@ __global__ void k_restrict(const double *src, double *dst, const int32_t *__rest
 // dispatch
 // ---------------------------------------------------------------------------
 
-template <typename R, int G, int NT> rg_status launch_level(const LevelArgs &a, hipStream_t s)
+template <typename R, int G, int NT> rg_status launch_level(const LevelArgs &a, const LevelTab &lv, hipStream_t s)
 {
-    const int64_t n = a.oct_end - a.oct_begin;
-    const unsigned blocks = static_cast<unsigned>((n + G - 1) / G);
+    LevelTab t = lv;   // items: groups of up to G octs of one level
+    for (int k = 0, end = 0; k < t.n; ++k) t.item_end[k] = end += (t.count[k] + G - 1) / G;
+    const unsigned blocks = static_cast<unsigned>(tab_items(t));
     if (a.ghost)
-        k_hydro_level<R, G, NT, true><<<blocks, NT, 0, s>>>(a);
+        k_hydro_level<R, G, NT, true><<<blocks, NT, 0, s>>>(a, t);
     else
-        k_hydro_level<R, G, NT, false><<<blocks, NT, 0, s>>>(a);
+        k_hydro_level<R, G, NT, false><<<blocks, NT, 0, s>>>(a, t);
     return launch_status("rg_hydro_step_level");
 }
 
-template <typename R> rg_status launch_form(const LevelArgs &a, const rg_tuning *tune, hipStream_t s)
+template <typename R> rg_status launch_form(const LevelArgs &a, const LevelTab &lv, const rg_tuning *tune, hipStream_t s)
 {
     const int g = tune && tune->octs_per_group ? tune->octs_per_group : 4;
     const int nt = tune && tune->threads ? tune->threads : 256;
-    if (g == 4 && nt == 256) return launch_level<R, 4, 256>(a, s);
-    if (g == 2 && nt == 128) return launch_level<R, 2, 128>(a, s);
-    if (g == 8 && nt == 256) return launch_level<R, 8, 256>(a, s);
-    if (g == 7 && nt == 256) return launch_level<R, 7, 256>(a, s);
-    if (g == 3 && nt == 128) return launch_level<R, 3, 128>(a, s);
+    if (g == 4 && nt == 256) return launch_level<R, 4, 256>(a, lv, s);
+    if (g == 2 && nt == 128) return launch_level<R, 2, 128>(a, lv, s);
+    if (g == 8 && nt == 256) return launch_level<R, 8, 256>(a, lv, s);
+    if (g == 7 && nt == 256) return launch_level<R, 7, 256>(a, lv, s);
+    if (g == 3 && nt == 128) return launch_level<R, 3, 128>(a, lv, s);
     return fail(RG_ENOTSUP, "no hydro kernel for %d octs per group and %d threads", g, nt);
 }
 
-template <typename R, int NT> rg_status launch_sib(const LevelArgs &a, const int32_t *father, hipStream_t s)
+template <typename R, int NT>
+rg_status launch_sib(const LevelArgs &a, const LevelTab &lv, const int32_t *father, hipStream_t s)
 {
-    const unsigned blocks = static_cast<unsigned>(a.oct_end - a.oct_begin);
+    const unsigned blocks = static_cast<unsigned>(tab_items(lv));
     if (a.ghost)
-        k_hydro_sib<R, NT, true><<<blocks, NT, 0, s>>>(a, father);
+        k_hydro_sib<R, NT, true><<<blocks, NT, 0, s>>>(a, lv, father);
     else
-        k_hydro_sib<R, NT, false><<<blocks, NT, 0, s>>>(a, father);
+        k_hydro_sib<R, NT, false><<<blocks, NT, 0, s>>>(a, lv, father);
     return launch_status("sibling-group hydro");
 }
 
-template <typename R> rg_status launch_sib_form(const LevelArgs &a, const int32_t *father, const rg_tuning *tune,
-                                                hipStream_t s)
+template <typename R>
+rg_status launch_sib_form(const LevelArgs &a, const LevelTab &lv, const int32_t *father, const rg_tuning *tune,
+                          hipStream_t s)
 {
     const int nt = tune && tune->group_threads ? tune->group_threads : 320;
-    if (nt == 320) return launch_sib<R, 320>(a, father, s);
-    if (nt == 256) return launch_sib<R, 256>(a, father, s);
-    if (nt == 384) return launch_sib<R, 384>(a, father, s);
+    if (nt == 320) return launch_sib<R, 320>(a, lv, father, s);
+    if (nt == 256) return launch_sib<R, 256>(a, lv, father, s);
+    if (nt == 384) return launch_sib<R, 384>(a, lv, father, s);
     return fail(RG_ENOTSUP, "no sibling-group kernel for %d threads", nt);
-}
-
-LevelArgs level_args(const double *uold, double *unew, const int32_t *nbr27, const uint32_t *son,
-                     const int32_t *list, int64_t count, double *corr, int64_t corr_base, const double *dt, double dx,
-                     double gamma, double cfl, double *dt_next, int64_t first, const double *ucoarse, int corr_mode,
-                     int ghost, const double *ucoarse2)
-{
-    LevelArgs a;
-    a.corr_mode = corr_mode;
-    a.ghost = ghost;
-    a.ucoarse2 = ucoarse2 ? ucoarse2 : (ucoarse ? ucoarse : uold);
-    a.list = list;
-    a.uold = uold;
-    a.ucoarse = ucoarse ? ucoarse : uold;
-    a.unew = unew;
-    a.nbr27 = nbr27;
-    a.son = son;
-    a.corr = corr;
-    a.corr_base = corr_base;
-    a.oct_begin = list ? 0 : first;
-    a.oct_end = a.oct_begin + count;
-    a.dt = dt;
-    a.dx = dx;
-    a.gamma = gamma;
-    a.cfl = cfl;
-    a.dt_next = reinterpret_cast<unsigned long long *>(dt_next);
-    a.hdr = current_sink();
-    return a;
 }
 
 }  // namespace
 
-rg_status hydro_level(const LevelArgs &a, int form, const rg_tuning *tune, hipStream_t s)
+// the octs of the levels of lv (lists, or with no list the octs from
+// a.oct_begin on), one at a time
+rg_status hydro_octs(const LevelArgs &a, const LevelTab &lv, int form, const rg_tuning *tune, hipStream_t s)
 {
-    if (a.oct_end <= a.oct_begin) return RG_OK;
-    if (form == RG_FP64) return launch_form<double>(a, tune, s);
-    return launch_form<float>(a, tune, s);
+    if (lv.n == 0) return RG_OK;
+    if (form == RG_FP64) return launch_form<double>(a, lv, tune, s);
+    return launch_form<float>(a, lv, tune, s);
 }
 
-// octs list[0..count) (or first..first+count when list is null)
-rg_status hydro_level_list(const double *uold, double *unew, const int32_t *nbr27, const uint32_t *son,
-                           const int32_t *list, int64_t count, double *corr, int64_t corr_base, const double *dt,
-                           double dx, double gamma, int form, const rg_tuning *tune, double cfl, double *dt_next,
-                           hipStream_t s, int64_t first, const double *ucoarse, int corr_mode, int ghost,
-                           const double *ucoarse2)
-{
-    if (count <= 0) return RG_OK;
-    const LevelArgs a = level_args(uold, unew, nbr27, son, list, count, corr, corr_base, dt, dx, gamma, cfl, dt_next,
-                                   first, ucoarse, corr_mode, ghost, ucoarse2);
-    return hydro_level(a, form, tune, s);
-}
-
-// complete sibling groups whose first octs are list[0..count): octs
+// complete sibling groups of the levels of lv, by their first octs: octs
 // list[i] .. list[i] + 7, placed in the group by their father cells
-rg_status hydro_groups_list(const double *uold, double *unew, const int32_t *nbr27, const uint32_t *son,
-                            const int32_t *father, const int32_t *list, int64_t count, double *corr,
-                            int64_t corr_base, const double *dt, double dx, double gamma, int form,
-                            const rg_tuning *tune, double cfl, double *dt_next, hipStream_t s, const double *ucoarse,
-                            int corr_mode, int ghost, const double *ucoarse2)
+rg_status hydro_groups(const LevelArgs &a, const LevelTab &lv, const int32_t *father, int form, const rg_tuning *tune,
+                       hipStream_t s)
 {
-    if (count <= 0) return RG_OK;
-    const LevelArgs a = level_args(uold, unew, nbr27, son, list, count, corr, corr_base, dt, dx, gamma, cfl, dt_next,
-                                   0, ucoarse, corr_mode, ghost, ucoarse2);
-    if (form == RG_FP64) return launch_sib_form<double>(a, father, tune, s);
-    return launch_sib_form<float>(a, father, tune, s);
+    if (lv.n == 0) return RG_OK;
+    if (form == RG_FP64) return launch_sib_form<double>(a, lv, father, tune, s);
+    return launch_sib_form<float>(a, lv, father, tune, s);
 }
 
 // coarse-fine corrections of unew owed by octs [ob, oe) of tree t (list[ob..oe)
@@ -394,14 +366,17 @@ rg_status rg_hydro_step_level(double dx, const double *d_dt, double gamma, const
     a.corr = d_corr;
     a.corr_base = corr_base;
     a.oct_begin = oct_begin;
-    a.oct_end = oct_end;
     a.dt = d_dt;
     a.dx = dx;
     a.gamma = gamma;
     a.cfl = cfl;
     a.dt_next = reinterpret_cast<unsigned long long *>(d_dt_next);
     a.hdr = current_sink();
-    return hydro_level(a, form, tune, as_stream(stream));
+    LevelTab lv;
+    lv.n = 0;
+    lv.owes = 0;
+    add_level(lv, oct_end - oct_begin, 0, oct_end - oct_begin, dx, true);
+    return hydro_octs(a, lv, form, tune, as_stream(stream));
 }
 
 rg_status rg_apply_coarse_corrections(double *d_unew, const double *d_corr, int64_t corr_base, const int32_t *d_nbr27,

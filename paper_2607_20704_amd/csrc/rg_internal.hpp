@@ -389,6 +389,63 @@ __device__ inline void hash_insert_one(HashHeader *hdr, uint64_t *keys, int32_t 
     flag_error(hdr, RG_EFULL, i);
 }
 
+// what the per-oct and sibling-group kernels are given
+struct LevelArgs {
+    const int32_t *list;  // if set, the octs are the list's entries
+    const double *uold;
+    const double *ucoarse;   // coarse ghost cells (the coarser level's state; uold itself in a global step)
+    double *unew;
+    const int32_t *nbr27;
+    const uint32_t *son;
+    double *corr;
+    int64_t corr_base;
+    int corr_mode;        // 0: store the owed flux; 1: store 0 + flux; 2: add it (sums over substeps)
+    int ghost;            // coarse ghost cells: 0 injection, 1 minmod-limited linear interpolation
+    const double *ucoarse2;   // cells two levels down (neighbours of a coarse ghost cell's own coarse cell)
+    int64_t oct_begin;    // without a list: the first oct
+    const double *dt;     // device scalar
+    double dx;
+    double gamma;
+    double cfl;
+    unsigned long long *dt_next;   // if set: CFL limit of the new state folded in (bits of a positive double)
+    HashHeader *hdr;      // device-side errors: non-finite state, fluxes owed to a coarse cell with no buffer
+};
+
+// The levels served by one launch of a hydro kernel (a global step has one
+// time step, so its levels are independent; each launch of a small level
+// costs its own latency and its own partly empty last round).  Items
+// (bricks, groups of octs) of entry k are [item_end[k - 1], item_end[k]).
+struct LevelTab {
+    int n;
+    int32_t item_end[RG_MAX_LEVEL];
+    int32_t list0[RG_MAX_LEVEL];   // first entry of the level's list
+    int32_t count[RG_MAX_LEVEL];   // entries of the list
+    double dx[RG_MAX_LEVEL];
+    uint32_t owes;                 // bit k: the level is above lmin and records the fluxes it owes
+};
+
+inline void add_level(LevelTab &t, int64_t items, int64_t list0, int64_t count, double dx, bool owes)
+{
+    if (count <= 0) return;
+    const int k = t.n++;
+    t.item_end[k] = (k ? t.item_end[k - 1] : 0) + static_cast<int32_t>(items);
+    t.list0[k] = static_cast<int32_t>(list0);
+    t.count[k] = static_cast<int32_t>(count);
+    t.dx[k] = dx;
+    if (owes) t.owes |= 1u << k;
+}
+
+inline int64_t tab_items(const LevelTab &t) { return t.n ? t.item_end[t.n - 1] : 0; }
+
+// entry holding item i, and i made relative to its first item
+__device__ __forceinline__ int tab_entry(const LevelTab &t, int &i)
+{
+    int k = 0;
+    while (k + 1 < t.n && i >= t.item_end[k]) ++k;
+    if (k) i -= t.item_end[k - 1];
+    return k;
+}
+
 // ---------------------------------------------------------------------------
 // misc launches shared by several files
 // ---------------------------------------------------------------------------

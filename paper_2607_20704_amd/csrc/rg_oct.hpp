@@ -106,27 +106,6 @@ __device__ __forceinline__ int slot_of(int x) { return x < 0 ? -1 : (x > 1 ? 1 :
 // the level kernel
 // ---------------------------------------------------------------------------
 
-struct LevelArgs {
-    const int32_t *list;  // if set, the octs are list[oct_begin .. oct_end)
-    const double *uold;
-    const double *ucoarse;   // coarse ghost cells (the coarser level's state; uold itself in a global step)
-    double *unew;
-    const int32_t *nbr27;
-    const uint32_t *son;
-    double *corr;
-    int64_t corr_base;
-    int corr_mode;        // 0: store the owed flux; 1: store 0 + flux; 2: add it (sums over substeps)
-    int ghost;            // coarse ghost cells: 0 injection, 1 minmod-limited linear interpolation
-    const double *ucoarse2;   // cells two levels down (neighbours of a coarse ghost cell's own coarse cell)
-    int64_t oct_begin, oct_end;
-    const double *dt;     // device scalar
-    double dx;
-    double gamma;
-    double cfl;
-    unsigned long long *dt_next;   // if set: CFL limit of the new state folded in (bits of a positive double)
-    HashHeader *hdr;      // device-side errors: non-finite state, fluxes owed to a coarse cell with no buffer
-};
-
 // Values of the fine position at sub-cell (sx, sy, sz) of coarse cell C:
 // C's own (injection), or with ghost = 1 C's values plus a quarter of each
 // minmod slope, toward the position, taken from C's face neighbours (in C's

@@ -12,20 +12,14 @@
 #include "rg_internal.hpp"
 
 namespace rg {
-rg_status hydro_level_list(const double *uold, double *unew, const int32_t *nbr27, const uint32_t *son,
-                           const int32_t *list, int64_t count, double *corr, int64_t corr_base, const double *dt,
-                           double dx, double gamma, int form, const rg_tuning *tune, double cfl, double *dt_next,
-                           hipStream_t s, int64_t first = 0, const double *ucoarse = nullptr,
-                           int corr_mode = 0, int ghost = 0, const double *ucoarse2 = nullptr);
-rg_status hydro_groups_list(const double *uold, double *unew, const int32_t *nbr27, const uint32_t *son,
-                            const int32_t *father, const int32_t *list, int64_t count, double *corr,
-                            int64_t corr_base, const double *dt, double dx, double gamma, int form,
-                            const rg_tuning *tune, double cfl, double *dt_next, hipStream_t s, const double *ucoarse,
-                            int corr_mode, int ghost, const double *ucoarse2);
-rg_status hydro_bricks(const double *uold, double *unew, const int32_t *nbr27, const uint32_t *son,
-                       const uint64_t *keys, const int32_t *bricks, int64_t nbricks, const double *dt, double dx,
-                       double gamma, int outflow, int form, double cfl, double *dt_next, int waves, hipStream_t s,
-                       int64_t pair_first, int pair_level);
+rg_status hydro_octs(const LevelArgs &a, const LevelTab &lv, int form, const rg_tuning *tune, hipStream_t s);
+rg_status hydro_groups(const LevelArgs &a, const LevelTab &lv, const int32_t *father, int form, const rg_tuning *tune,
+                       hipStream_t s);
+rg_status hydro_bricks(const rg_tree *t, const double *uold, double *unew, const int32_t *list, const LevelTab &lv,
+                       const double *dt, double gamma, int form, double cfl, double *dt_next, int waves,
+                       hipStream_t s);
+rg_status hydro_columns(const rg_tree *t, int level, const double *uold, double *unew, const double *dt, double gamma,
+                        int form, double cfl, double *dt_next, int waves, hipStream_t s);
 }  // namespace rg
 
 using namespace rg;
@@ -39,52 +33,81 @@ constexpr int kFaceSlot[6] = {12, 14, 10, 16, 4, 22};
 
 namespace rg {
 
-// One level of tree t: with a schedule, its bricks by the brick kernel, its
-// complete sibling groups by the group kernel and the rest by the per-oct
-// kernel; without one, the whole level by the per-oct kernel.  Coarse ghost
-// cells are read from ucoarse (bricks have none).  The fluxes owed to coarse
-// cells go to corr (30 doubles per oct from the first oct above lmin):
-// stored (corr_mode 0), stored as 0 + flux (1) or added (2).
-rg_status hydro_tree_level(const rg_tree *t, const rg_schedule *sc, int level, const double *d_dt, double gamma,
-                           const double *d_uold, const double *d_ucoarse, double *d_unew, double cfl,
-                           double *d_dt_next, int form, const rg_tuning *tune, hipStream_t s, double *d_corr,
-                           int corr_mode, const double *d_ucoarse2)
+// Levels l0..l1 of tree t, which share the time step: with a schedule, their
+// bricks by the brick kernel, their complete sibling groups by the group
+// kernel and the rest by the per-oct kernel, one launch each; without one,
+// all octs by the per-oct kernel.  Coarse ghost cells are read from ucoarse
+// (bricks have none).  The fluxes owed to coarse cells go to corr (30 doubles
+// per oct from the first oct above lmin): stored (corr_mode 0), stored as 0 +
+// flux (1) or added (2).
+rg_status hydro_tree_levels(const rg_tree *t, const rg_schedule *sc, int l0, int l1, const double *d_dt, double gamma,
+                            const double *d_uold, const double *d_ucoarse, double *d_unew, double cfl,
+                            double *d_dt_next, int form, const rg_tuning *tune, hipStream_t s, double *d_corr,
+                            int corr_mode, const double *d_ucoarse2)
 {
     RG_REQUIRE(t->ghost == RG_GHOST_INJECT || t->ghost == RG_GHOST_LINEAR, "bad ghost mode %d", t->ghost);
-    const double dx = ldexp(1.0, -level);
-    const int64_t corr_base = t->level_begin[t->lmin + 1];
-    double *corr = level > t->lmin ? d_corr : nullptr;
-    const bool bricks = sc && !(tune && tune->no_bricks);
-    if (bricks) {
-        // a complete periodic level without split cells (the finest, with
-        // every oct in a brick): its bricks go two by two along z
-        const int64_t nl = t->level_begin[level + 1] - t->level_begin[level];
-        const bool pairs = !(tune && tune->no_pairs) && level >= 5 && level == t->lmax &&
-                           t->bc == RG_BC_PERIODIC && nl == (int64_t(1) << (3 * (level - 1))) &&
-                           sc->brick_count[level] * 512 == nl;
-        RG_TRY(hydro_bricks(d_uold, d_unew, t->d_nbr27, t->d_son_mask, t->d_keys, sc->d_list + sc->brick_begin[level],
-                            sc->brick_count[level], d_dt, dx, gamma, t->bc == RG_BC_OUTFLOW, form, cfl, d_dt_next,
-                            tune ? tune->brick_waves : 0, s, t->level_begin[level], pairs ? level : -1));
-        if (tune && tune->no_groups) {
-            RG_TRY(hydro_level_list(d_uold, d_unew, t->d_nbr27, t->d_son_mask, sc->d_list + sc->rest_begin[level],
-                                    sc->rest_count[level], corr, corr_base, d_dt, dx, gamma, form, tune, cfl,
-                                    d_dt_next, s, 0, d_ucoarse, corr_mode, t->ghost, d_ucoarse2));
-        } else {
-            RG_TRY(hydro_groups_list(d_uold, d_unew, t->d_nbr27, t->d_son_mask, t->d_father_cell,
-                                     sc->d_list + sc->group_begin[level], sc->group_count[level], corr, corr_base,
-                                     d_dt, dx, gamma, form, tune, cfl, d_dt_next, s, d_ucoarse, corr_mode, t->ghost,
-                                     d_ucoarse2));
-            RG_TRY(hydro_level_list(d_uold, d_unew, t->d_nbr27, t->d_son_mask, sc->d_list + sc->single_begin[level],
-                                    sc->single_count[level], corr, corr_base, d_dt, dx, gamma, form, tune, cfl,
-                                    d_dt_next, s, 0, d_ucoarse, corr_mode, t->ghost, d_ucoarse2));
+    RG_REQUIRE(!sc || sc->d_list, "schedule without a list");
+    LevelArgs a;
+    a.list = sc ? sc->d_list : nullptr;
+    a.uold = d_uold;
+    a.ucoarse = d_ucoarse;
+    a.unew = d_unew;
+    a.nbr27 = t->d_nbr27;
+    a.son = t->d_son_mask;
+    a.corr = d_corr;
+    a.corr_base = t->level_begin[t->lmin + 1];
+    a.corr_mode = corr_mode;
+    a.ghost = t->ghost;
+    a.ucoarse2 = d_ucoarse2;
+    a.oct_begin = 0;
+    a.dt = d_dt;
+    a.dx = 0.0;
+    a.gamma = gamma;
+    a.cfl = cfl;
+    a.dt_next = reinterpret_cast<unsigned long long *>(d_dt_next);
+    a.hdr = current_sink();
+    LevelTab bricks, groups, octs;
+    bricks.n = groups.n = octs.n = 0;
+    bricks.owes = groups.owes = octs.owes = 0;
+    const bool sched = sc && !(tune && tune->no_bricks);
+    int columns = -1;
+    for (int l = l0; l <= l1; ++l) {
+        const double dx = ldexp(1.0, -l);
+        const int64_t first = t->level_begin[l], n = t->level_begin[l + 1] - first;
+        const bool owes = l > t->lmin;
+        if (!sched) {
+            // octs in place, level by level (no list to go by)
+            LevelTab one;
+            one.n = 0;
+            one.owes = 0;
+            add_level(one, n, 0, n, dx, owes);
+            LevelArgs b = a;
+            b.list = nullptr;
+            b.oct_begin = first;
+            RG_TRY(hydro_octs(b, one, form, tune, s));
+            continue;
         }
-    } else {
-        RG_TRY(hydro_level_list(d_uold, d_unew, t->d_nbr27, t->d_son_mask, nullptr,
-                                t->level_begin[level + 1] - t->level_begin[level], corr, corr_base, d_dt, dx, gamma,
-                                form, tune, cfl, d_dt_next, s, t->level_begin[level], d_ucoarse, corr_mode, t->ghost,
-                                d_ucoarse2));
+        // a complete level without split cells (the finest, every oct in a
+        // brick) goes by columns
+        if (!(tune && tune->no_pairs) && l >= 4 && l == t->lmax && n == (int64_t(1) << (3 * (l - 1))) &&
+            sc->brick_count[l] * kBrickOcts == n)
+            columns = l;
+        else
+            add_level(bricks, sc->brick_count[l], sc->brick_begin[l], sc->brick_count[l], dx, false);
+        if (tune && tune->no_groups) {
+            add_level(octs, sc->rest_count[l], sc->rest_begin[l], sc->rest_count[l], dx, owes);
+        } else {
+            add_level(groups, sc->group_count[l], sc->group_begin[l], sc->group_count[l], dx, owes);
+            add_level(octs, sc->single_count[l], sc->single_begin[l], sc->single_count[l], dx, owes);
+        }
     }
-    return RG_OK;
+    if (!sched) return RG_OK;
+    const int waves = tune ? tune->brick_waves : 0;
+    if (columns >= 0)
+        RG_TRY(hydro_columns(t, columns, d_uold, d_unew, d_dt, gamma, form, cfl, d_dt_next, waves, s));
+    RG_TRY(hydro_bricks(t, d_uold, d_unew, sc->d_list, bricks, d_dt, gamma, form, cfl, d_dt_next, waves, s));
+    RG_TRY(hydro_groups(a, groups, t->d_father_cell, form, tune, s));
+    return hydro_octs(a, octs, form, tune, s);
 }
 
 }  // namespace rg
@@ -207,7 +230,7 @@ rg_status rg_hydro_step_scheduled(const rg_tree *t, const rg_schedule *sc, int l
     RG_REQUIRE(form == RG_FP64 || form == RG_MIXED, "bad form %d", form);
     RG_REQUIRE(gamma > 1, "bad gamma");
     RG_REQUIRE(!d_dt_next || (cfl > 0 && aligned(d_dt_next, 8)), "bad cfl or misaligned dt_next");
-    return hydro_tree_level(t, sc, level, d_dt, gamma, d_uold, d_uold, d_unew, cfl, d_dt_next, form, tune,
+    return hydro_tree_levels(t, sc, level, level, d_dt, gamma, d_uold, d_uold, d_unew, cfl, d_dt_next, form, tune,
                             as_stream(stream), t->d_corr, 0, d_uold);
 }
 
