@@ -51,7 +51,8 @@ struct Item {
     int64_t count;
 };
 
-constexpr int kT = 256;   // threads of every batched kernel
+constexpr int kT = 256;      // threads of the batched kernels
+constexpr int kSibT = 320;   // of the sibling-group kernel: one stencil cell each
 
 // Items of a persistent loop: workgroups are dealt round-robin to the eight
 // XCDs, so workgroup w serves a contiguous eighth of the item list (XCD
@@ -125,27 +126,34 @@ __global__ __launch_bounds__(kT) void k_batch_dt(const BTree *__restrict__ trees
     }
 }
 
-// One item per workgroup, same XCD-contiguous dealing (grid = 8 ceil(n/8)).
-__device__ __forceinline__ ItemRange xcd_item(int64_t nitems)
-{
-    const int64_t per_xcd = (nitems + 7) / 8;
-    ItemRange r;
-    r.begin = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    r.end = r.begin < nitems ? r.begin + 1 : r.begin;
-    r.stride = 1;
-    return r;
-}
-
 // hydro update, item tag a = 4 level + kind.  Bricks (kind 0: the brick
 // whose first oct is schedule list entry `first`) and oct groups (kind 1: up
 // to G octs listed at [first, first+count) of the schedule list; kind 2: the
-// octs first .. first+count-1) are separate kernels, so that each keeps the
-// register allocation of its single-tree twin.
+// octs first .. first+count-1; kind 3: the sibling group at list entry
+// `first`) are separate kernels, so that each keeps the register allocation
+// of its single-tree twin.
 // With P the grid is persistent and loops over the items; without, each
-// workgroup takes one item (no loop-carried registers).  FP64 bricks keep
-// each column's state in registers (two waves per SIMD); mixed bricks read
-// it again, at three waves: at four the loop spilled (72 scratch loads),
-// and the 64-box graph took 38.0 ms against 35.2 ms at three.
+// workgroup takes one item, with no loop around the body: the loop of at most
+// one round that stood here cost the compiler 170 registers instead of 90 in
+// the group kernel, two waves per SIMD instead of five.
+template <bool P, typename F> __device__ __forceinline__ void for_items(int64_t nitems, F body)
+{
+    if constexpr (P) {
+        const ItemRange r = xcd_items(nitems);
+        for (int64_t it = r.begin; it < r.end; it += r.stride) {
+            body(it);
+            __syncthreads();
+        }
+    } else {
+        const int64_t per_xcd = (nitems + 7) / 8;
+        const int64_t it = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+        if (it < nitems) body(it);
+    }
+}
+
+// FP64 bricks keep each column's state in registers (two waves per SIMD);
+// mixed bricks read it again, at three waves: at four the loop spilled (72
+// scratch loads), and the 64-box graph took 38.0 ms against 35.2 ms at three.
 template <typename R, bool P>
 __global__ __launch_bounds__(BT, sizeof(R) == 8 ? 2 : 3) void k_batch_bricks(const BTree *__restrict__ trees,
                                                                             const Item *__restrict__ items,
@@ -153,8 +161,7 @@ __global__ __launch_bounds__(BT, sizeof(R) == 8 ? 2 : 3) void k_batch_bricks(con
                                                                             const double *dt, double *dt_next)
 {
     __shared__ BrickSmem<R, 2> S;
-    const ItemRange r = P ? xcd_items(nitems) : xcd_item(nitems);
-    for (int64_t it = r.begin; it < r.end; it += r.stride) {
+    for_items<P>(nitems, [&](int64_t it) {
         const Item I = items[it];
         const BTree &T = trees[I.tree];
         BrickArgs a;
@@ -174,80 +181,61 @@ __global__ __launch_bounds__(BT, sizeof(R) == 8 ? 2 : 3) void k_batch_bricks(con
         a.dt_next = reinterpret_cast<unsigned long long *>(dt_next + I.tree);
         a.hdr = T.hdr;
         brick_body<R, sizeof(R) == 8>(a, T.list[I.first], I.first, 0, BC, S);
-        __syncthreads();
-    }
+    });
 }
 
-// registers as the compiler sees fit: a forced occupancy made the loop
-// spill (up to 45 registers in the mixed form)
+__device__ __forceinline__ LevelArgs level_args(const BTree &T, const Item &I, int parity, const double *dt,
+                                                double *dt_next)
+{
+    const int level = I.a >> 2;
+    LevelArgs a;
+    a.list = (I.a & 3) == 2 ? nullptr : T.list;
+    a.uold = T.u[parity];
+    a.ucoarse = T.u[parity];
+    a.unew = T.u[parity ^ 1];
+    a.nbr27 = T.nbr27;
+    a.son = T.son;
+    a.corr = level > T.lmin ? T.corr : nullptr;
+    a.corr_base = T.corr_base;
+    a.corr_mode = 0;
+    a.ghost = T.ghost;
+    a.ucoarse2 = T.u[parity];
+    a.oct_begin = 0;
+    a.dt = dt + I.tree;
+    a.dx = ldexp(1.0, -level);
+    a.gamma = T.gamma;
+    a.cfl = T.cfl;
+    a.dt_next = reinterpret_cast<unsigned long long *>(dt_next + I.tree);
+    a.hdr = T.hdr;
+    return a;
+}
+
 template <typename R, int G, bool P, bool GH>
 __global__ __launch_bounds__(kT) void k_batch_octs(const BTree *__restrict__ trees, const Item *__restrict__ items,
                                                    int64_t nitems, int parity, const double *dt, double *dt_next)
 {
     __shared__ Smem<R, G> S;
-    const ItemRange r = P ? xcd_items(nitems) : xcd_item(nitems);
-    for (int64_t it = r.begin; it < r.end; it += r.stride) {
+    for_items<P>(nitems, [&](int64_t it) {
         const Item I = items[it];
-        const BTree &T = trees[I.tree];
-        const int level = I.a >> 2;
-        LevelArgs a;
-        a.list = (I.a & 3) == 1 ? T.list : nullptr;
-        a.uold = T.u[parity];
-        a.ucoarse = T.u[parity];
-        a.unew = T.u[parity ^ 1];
-        a.nbr27 = T.nbr27;
-        a.son = T.son;
-        a.corr = level > T.lmin ? T.corr : nullptr;
-        a.corr_base = T.corr_base;
-        a.corr_mode = 0;
-        a.ghost = T.ghost;
-        a.ucoarse2 = T.u[parity];
-        a.oct_begin = 0;
-        a.dt = dt + I.tree;
-        a.dx = ldexp(1.0, -level);
-        a.gamma = T.gamma;
-        a.cfl = T.cfl;
-        a.dt_next = reinterpret_cast<unsigned long long *>(dt_next + I.tree);
-        a.hdr = T.hdr;
+        const LevelArgs a = level_args(trees[I.tree], I, parity, dt, dt_next);
         hydro_group<R, G, kT, GH>(a, I.first, static_cast<int>(I.count), S);
-        __syncthreads();
-    }
+    });
 }
 
 // complete sibling groups: item = one group, `first` its entry in the tree's
 // schedule list
 template <typename R, bool P, bool GH>
-__global__ __launch_bounds__(kT) void k_batch_groups(const BTree *__restrict__ trees, const Item *__restrict__ items,
-                                                     int64_t nitems, int parity, const double *dt, double *dt_next)
+__global__ __launch_bounds__(kSibT) void k_batch_groups(const BTree *__restrict__ trees,
+                                                        const Item *__restrict__ items, int64_t nitems, int parity,
+                                                        const double *dt, double *dt_next)
 {
     __shared__ SibSmem<R> S;
-    const ItemRange r = P ? xcd_items(nitems) : xcd_item(nitems);
-    for (int64_t it = r.begin; it < r.end; it += r.stride) {
+    for_items<P>(nitems, [&](int64_t it) {
         const Item I = items[it];
         const BTree &T = trees[I.tree];
-        const int level = I.a >> 2;
-        LevelArgs a;
-        a.list = T.list;
-        a.uold = T.u[parity];
-        a.ucoarse = T.u[parity];
-        a.unew = T.u[parity ^ 1];
-        a.nbr27 = T.nbr27;
-        a.son = T.son;
-        a.corr = level > T.lmin ? T.corr : nullptr;
-        a.corr_base = T.corr_base;
-        a.corr_mode = 0;
-        a.ghost = T.ghost;
-        a.ucoarse2 = T.u[parity];
-        a.oct_begin = 0;
-        a.dt = dt + I.tree;
-        a.dx = ldexp(1.0, -level);
-        a.gamma = T.gamma;
-        a.cfl = T.cfl;
-        a.dt_next = reinterpret_cast<unsigned long long *>(dt_next + I.tree);
-        a.hdr = T.hdr;
-        hydro_sib<R, kT, GH>(a, T.father, T.list[I.first], S);
-        __syncthreads();
-    }
+        const LevelArgs a = level_args(T, I, parity, dt, dt_next);
+        hydro_sib<R, kSibT, GH>(a, T.father, T.list[I.first], S);
+    });
 }
 
 __global__ __launch_bounds__(kT) void k_batch_corr(const BTree *__restrict__ trees, const Item *__restrict__ items,
@@ -488,16 +476,16 @@ rg_status launch_groups(bool gh, bool persistent, const BTree *trees, const Phas
     if (p.n == 0) return RG_OK;
     if (persistent) {
         if (gh) {
-            const int grid = persistent_grid(reinterpret_cast<const void *>(&k_batch_groups<R, true, true>), kT, p.n);
-            k_batch_groups<R, true, true><<<grid, kT, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
+            const int grid = persistent_grid(reinterpret_cast<const void *>(&k_batch_groups<R, true, true>), kSibT, p.n);
+            k_batch_groups<R, true, true><<<grid, kSibT, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
         } else {
-            const int grid = persistent_grid(reinterpret_cast<const void *>(&k_batch_groups<R, true, false>), kT, p.n);
-            k_batch_groups<R, true, false><<<grid, kT, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
+            const int grid = persistent_grid(reinterpret_cast<const void *>(&k_batch_groups<R, true, false>), kSibT, p.n);
+            k_batch_groups<R, true, false><<<grid, kSibT, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
         }
     } else if (gh) {
-        k_batch_groups<R, false, true><<<one_shot_grid(p.n), kT, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
+        k_batch_groups<R, false, true><<<one_shot_grid(p.n), kSibT, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
     } else {
-        k_batch_groups<R, false, false><<<one_shot_grid(p.n), kT, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
+        k_batch_groups<R, false, false><<<one_shot_grid(p.n), kSibT, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
     }
     return launch_status("batched sibling groups");
 }

@@ -38,12 +38,25 @@ __device__ __forceinline__ int enter_level(LevelArgs &a, const LevelTab &lv, int
     return i;
 }
 
+// Item of this workgroup: workgroups go to the eight XCDs in turn, so each
+// XCD takes a contiguous (Hilbert-ordered) eighth of the items, whose octs
+// read each other's cells as ghosts through its L2.  The grid has 8 ceil(n/8)
+// workgroups; -1 for the few beyond the last item.
+__device__ __forceinline__ int xcd_item(int n)
+{
+    const int per_xcd = (n + 7) / 8;
+    const int w = static_cast<int>(blockIdx.x % 8) * per_xcd + static_cast<int>(blockIdx.x / 8);
+    return w < n ? w : -1;
+}
+
 template <typename R, int G, int NT, bool GH>
 __global__ __launch_bounds__(NT) void k_hydro_level(LevelArgs a, LevelTab lv)
 {
     __shared__ Smem<R, G> S;
+    const int w = xcd_item(lv.item_end[lv.n - 1]);
+    if (w < 0) return;
     int count;
-    const int first = G * enter_level(a, lv, static_cast<int>(blockIdx.x), count);
+    const int first = G * enter_level(a, lv, w, count);
     hydro_group<R, G, NT, GH>(a, a.oct_begin + first, min(G, count - first), S);
 }
 
@@ -53,8 +66,10 @@ template <typename R, int NT, bool GH>
 __global__ __launch_bounds__(NT) void k_hydro_sib(LevelArgs a, LevelTab lv, const int32_t *__restrict__ father)
 {
     __shared__ SibSmem<R> S;
+    const int w = xcd_item(lv.item_end[lv.n - 1]);
+    if (w < 0) return;
     int count;
-    const int i = enter_level(a, lv, static_cast<int>(blockIdx.x), count);
+    const int i = enter_level(a, lv, w, count);
     hydro_sib<R, NT, GH>(a, father, a.list[i], S);
 }
 
@@ -203,7 +218,7 @@ template <typename R, int G, int NT> rg_status launch_level(const LevelArgs &a, 
 {
     LevelTab t = lv;   // items: groups of up to G octs of one level
     for (int k = 0, end = 0; k < t.n; ++k) t.item_end[k] = end += (t.count[k] + G - 1) / G;
-    const unsigned blocks = static_cast<unsigned>(tab_items(t));
+    const unsigned blocks = static_cast<unsigned>(8 * ((tab_items(t) + 7) / 8));
     if (a.ghost)
         k_hydro_level<R, G, NT, true><<<blocks, NT, 0, s>>>(a, t);
     else
@@ -226,7 +241,7 @@ template <typename R> rg_status launch_form(const LevelArgs &a, const LevelTab &
 template <typename R, int NT>
 rg_status launch_sib(const LevelArgs &a, const LevelTab &lv, const int32_t *father, hipStream_t s)
 {
-    const unsigned blocks = static_cast<unsigned>(tab_items(lv));
+    const unsigned blocks = static_cast<unsigned>(8 * ((tab_items(lv) + 7) / 8));
     if (a.ghost)
         k_hydro_sib<R, NT, true><<<blocks, NT, 0, s>>>(a, lv, father);
     else

@@ -24,17 +24,22 @@ namespace {
 constexpr int kSibW = 304;   // stencil cells
 constexpr int kSibR = 160;   // reconstructed cells: own, then face layer
 constexpr int kSibF = 240;   // faces: 3 axes x 5 planes x 16
+constexpr int kSibU = 8 * 8 * NV;   // values of the own cells
 
+// One word (or two) per item, read at the start of the kernel so that the
+// table's latency passes beside that of the octs and lists.  Own cells come
+// first, sibling by sibling (8 sib + c), which is the order of the state.
 struct SibTables {
-    int8_t wpos[kSibW][3];   // group-relative positions -2..5 (own cells first: x + 4y + 16z)
-    int8_t wsib[kSibW];      // sibling (x + 2y + 4z of its place in the group) whose tile holds the cell
-    int16_t tile2w[512];     // (x+2) + 8(y+2) + 64(z+2) -> index into wpos, -1 if unused
-    // the same, packed so that a thread reads one word per item:
-    // stencil cell: (x+2) | (y+2) << 3 | (z+2) << 6 | sibling << 9
+    // stencil cell: list entry 27 sib + slot (8 bits), cell within that oct
+    // (3), sibling whose 6^3 tile holds it (3), position in that tile + 2 (3
+    // bits per axis)
     uint32_t wcode[kSibW];
     // reconstructed cell: its neighbours' indices x-, x+, y-, y+, z-, z+
-    // (9 bits each), then x+2, y+2, z+2 (3 bits each) from bit 54
+    // (9 bits each)
     uint64_t rcode[kSibR];
+    // face-layer cell: the face it has a state for (8 bits), which side of it
+    // the state is (0 left, 1 right), axis (2 bits)
+    uint16_t fcode[kSibR - 64];
 };
 
 constexpr int sib_tile(int x, int y, int z) { return (x + 2) + 8 * (y + 2) + 64 * (z + 2); }
@@ -43,67 +48,64 @@ constexpr int sib_tile(int x, int y, int z) { return (x + 2) + 8 * (y + 2) + 64 
 // two) covers group position p along one axis
 constexpr int sib_place(int p) { return p < 0 ? 0 : (p > 3 ? 1 : p >> 1); }
 
-constexpr void sib_add(SibTables &t, int &n, int x, int y, int z)
-{
-    t.wpos[n][0] = static_cast<int8_t>(x);
-    t.wpos[n][1] = static_cast<int8_t>(y);
-    t.wpos[n][2] = static_cast<int8_t>(z);
-    t.wsib[n] = static_cast<int8_t>(sib_place(x) + 2 * sib_place(y) + 4 * sib_place(z));
-    t.tile2w[sib_tile(x, y, z)] = static_cast<int16_t>(n);
-    ++n;
-}
+// face on axis a between cells c-1 and c (c = 0..4) along a, at (t1, t2) on
+// the other two axes in increasing order
+__host__ __device__ constexpr int sib_face(int a, int c, int t1, int t2) { return 80 * a + 16 * c + t1 + 4 * t2; }
 
 constexpr SibTables make_sib_tables()
 {
     SibTables t{};
-    for (int i = 0; i < 512; ++i) t.tile2w[i] = -1;
+    int pos[kSibW][3] = {};
+    int16_t index[512] = {};
     int n = 0;
-    for (int z = 0; z < 4; ++z)
-        for (int y = 0; y < 4; ++y)
-            for (int x = 0; x < 4; ++x) sib_add(t, n, x, y, z);
+    for (int sib = 0; sib < 8; ++sib)
+        for (int c = 0; c < 8; ++c, ++n)
+            for (int a = 0; a < 3; ++a) pos[n][a] = 2 * ((sib >> a) & 1) + ((c >> a) & 1);
     // face layer (reconstructed), then outer layer, per axis and side
     for (int layer = 0; layer < 2; ++layer)
         for (int a = 0; a < 3; ++a)
             for (int side = 0; side < 2; ++side)
-                for (int q = 0; q < 16; ++q) {
-                    int p[3] = {0, 0, 0};
+                for (int q = 0; q < 16; ++q, ++n) {
                     const int t1 = a == 0 ? 1 : 0, t2 = a == 2 ? 1 : 2;
-                    p[a] = layer == 0 ? (side ? 4 : -1) : (side ? 5 : -2);
-                    p[t1] = q & 3;
-                    p[t2] = q >> 2;
-                    sib_add(t, n, p[0], p[1], p[2]);
+                    pos[n][a] = layer == 0 ? (side ? 4 : -1) : (side ? 5 : -2);
+                    pos[n][t1] = q & 3;
+                    pos[n][t2] = q >> 2;
+                    // the high-side state of a cell below is left of face 0,
+                    // the low-side state of a cell above right of face 4
+                    if (layer == 0)
+                        t.fcode[n - 64] = static_cast<uint16_t>(sib_face(a, side ? 4 : 0, q & 3, q >> 2) | side << 8 |
+                                                                a << 9);
                 }
     // edges: two coordinates in {-1, 4}, the third in 0..3
     for (int a = 0; a < 3; ++a)
-        for (int q = 0; q < 16; ++q) {
-            int p[3] = {0, 0, 0};
+        for (int q = 0; q < 16; ++q, ++n) {
             const int u = a == 0 ? 1 : 0, v = a == 2 ? 1 : 2;
-            p[a] = q & 3;
-            p[u] = (q >> 2) & 1 ? 4 : -1;
-            p[v] = (q >> 3) & 1 ? 4 : -1;
-            sib_add(t, n, p[0], p[1], p[2]);
+            pos[n][a] = q & 3;
+            pos[n][u] = (q >> 2) & 1 ? 4 : -1;
+            pos[n][v] = (q >> 3) & 1 ? 4 : -1;
         }
-    for (int i = 0; i < kSibW; ++i)
-        t.wcode[i] = static_cast<uint32_t>((t.wpos[i][0] + 2) | (t.wpos[i][1] + 2) << 3 | (t.wpos[i][2] + 2) << 6 |
-                                           t.wsib[i] << 9);
+    for (int i = 0; i < kSibW; ++i) {
+        index[sib_tile(pos[i][0], pos[i][1], pos[i][2])] = static_cast<int16_t>(i);
+        int sib = 0, slot = 13, cell = 0, where = 0;
+        for (int a = 0, step = 1; a < 3; ++a, step *= 3) {
+            const int place = sib_place(pos[i][a]), c = pos[i][a] - 2 * place;
+            sib |= place << a;
+            slot += c < 0 ? -step : (c > 1 ? step : 0);
+            cell |= (c & 1) << a;
+            where |= (c + 2) << (3 * a);
+        }
+        t.wcode[i] = static_cast<uint32_t>((27 * sib + slot) | cell << 8 | sib << 11 | where << 14);
+    }
     for (int i = 0; i < kSibR; ++i) {
-        const int x = t.wpos[i][0], y = t.wpos[i][1], z = t.wpos[i][2];
-        const int nb[6] = {t.tile2w[sib_tile(x - 1, y, z)], t.tile2w[sib_tile(x + 1, y, z)],
-                           t.tile2w[sib_tile(x, y - 1, z)], t.tile2w[sib_tile(x, y + 1, z)],
-                           t.tile2w[sib_tile(x, y, z - 1)], t.tile2w[sib_tile(x, y, z + 1)]};
-        uint64_t c = 0;
-        for (int k = 0; k < 6; ++k) c |= static_cast<uint64_t>(nb[k]) << (9 * k);
-        c |= static_cast<uint64_t>(x + 2) << 54 | static_cast<uint64_t>(y + 2) << 57 | static_cast<uint64_t>(z + 2) << 60;
-        t.rcode[i] = c;
+        const int x = pos[i][0], y = pos[i][1], z = pos[i][2];
+        const int nb[6] = {index[sib_tile(x - 1, y, z)], index[sib_tile(x + 1, y, z)], index[sib_tile(x, y - 1, z)],
+                           index[sib_tile(x, y + 1, z)], index[sib_tile(x, y, z - 1)], index[sib_tile(x, y, z + 1)]};
+        for (int k = 0; k < 6; ++k) t.rcode[i] |= static_cast<uint64_t>(nb[k]) << (9 * k);
     }
     return t;
 }
 
 __constant__ SibTables c_sib = make_sib_tables();
-
-// face on axis a between cells c-1 and c (c = 0..4) along a, at (t1, t2) on
-// the other two axes in increasing order
-__device__ __forceinline__ int sib_face(int a, int c, int t1, int t2) { return 80 * a + 16 * c + t1 + 4 * t2; }
 
 // neighbour-list slot of face side 2 * axis + high
 __device__ __forceinline__ int side_slot(int ax, int hi)
@@ -113,19 +115,23 @@ __device__ __forceinline__ int side_slot(int ax, int hi)
 }
 
 template <typename R> struct SibSmem {
-    int64_t oct[8];             // by place in the group
-    int32_t nb[8][27];
+    int32_t oct[8];             // by place in the group
+    int32_t nb[8 * 27];
     // son masks: [0, 8) the siblings; 8 + 4 side + q the neighbour across
     // side (2 axis + high) of the siblings on that face, q = their place
     // along the two other axes (lower axis first)
     uint32_t sm[32];
-    double u[64][NV];           // uold, then unew, of the own cells (x + 4y + 16z)
+    int32_t outside, coarse, split;   // some list entry outside the domain / a coarse cell; some son mask set
+    // the primitives are dead once the face states exist, the states once the
+    // fluxes do: fluxes over primitives, new state over face states
     union {
         R w[NV][kSibW];         // primitive variables of the stencil cells (planes, lds_get)
-        double g[kSibF][NV];    // G = F dt/dx per face
+        double g[NV][kSibF];    // G = F dt/dx per face
     };
-    R fs[2][NV][kSibF];         // face states: [0] left of the face, [1] right (planes)
-    double red[8];
+    union {
+        R fs[2][NV][kSibF];     // face states: [0] left of the face, [1] right (planes)
+        double u[kSibU];        // new state of the own cells
+    };
 };
 
 // son mask holding the cell at group position (x, y, z), one coordinate of
@@ -141,225 +147,247 @@ __device__ __forceinline__ uint32_t sib_mask_at(const uint32_t *sm, int x, int y
     return sm[(x >> 1) + 2 * (y >> 1) + 4 * (z >> 1)];
 }
 
+// What bounds it: latency and issue, not memory.  A group takes about 12 us
+// from its first load to its last store, most of it waiting for dependent
+// loads and barriers, and the chip holds as many groups as their LDS allows.
+// Of 3200 VALU instructions per FP64 group 1400 are the scheme's arithmetic;
+// the rest was index arithmetic, three divergent passes over the axes for
+// cells of the face layer, which have one state each, and tests for walls,
+// split cells and coarse neighbours in groups that have none.  Those are
+// decided once per group here, indices come from one table word per item, and
+// the state is kept once.
 template <typename R, int NT, bool GH>
 __device__ __forceinline__ void hydro_sib(const LevelArgs &a, const int32_t *__restrict__ father, int64_t first,
                                           SibSmem<R> &S)
 {
     const int tid = threadIdx.x;
     const double r = *a.dt / a.dx;
-    const double h64 = 0.5 * r;
-    const R h = static_cast<R>(h64);
+    const R h = static_cast<R>(0.5 * r);
     const R gam = static_cast<R>(a.gamma);
-    const double g1d = 1.0 / (a.gamma - 1.0);
-    const R g1 = static_cast<R>(g1d);
+    const R g1 = static_cast<R>(1.0 / (a.gamma - 1.0));
 
     // the siblings by place (the father cell's index in its oct), their
     // neighbour lists and son masks; the places of a consistent tree are a
     // permutation, and an inconsistent one still names octs of the group
-    if (tid < 8) S.oct[tid] = first + tid;
+    if (tid < 8) S.oct[tid] = static_cast<int32_t>(first) + tid;
+    if (tid == 0) S.outside = S.coarse = S.split = 0;
     __syncthreads();
-    if (tid < 8) {
-        const int64_t o = first + tid;
-        S.oct[father[o] & 7] = o;
-    }
+    if (tid < 8) S.oct[father[first + tid] & 7] = static_cast<int32_t>(first) + tid;
     __syncthreads();
     for (int it = tid; it < 8 * 27; it += NT) {
         const int g = it / 27, s = it - 27 * g;
-        S.nb[g][s] = a.nbr27[27 * S.oct[g] + s];
+        const int32_t e = a.nbr27[27 * int64_t(S.oct[g]) + s];
+        S.nb[it] = e;
+        if (e < 0) (e == RG_NBR_OUTSIDE ? S.outside : S.coarse) = 1;
     }
     __syncthreads();
-    for (int it = tid; it < 32; it += NT) {
+    // son masks, by lanes of the last wave, put down after the gather
+    uint32_t m = 0;
+    const int ms = tid - (NT - 64);
+    if (ms >= 0 && ms < 32) {
         int e;
-        if (it < 8) {
-            e = static_cast<int>(S.oct[it]);
+        if (ms < 8) {
+            e = S.oct[ms];
         } else {
-            const int side = (it - 8) >> 2, q = (it - 8) & 3;
+            const int side = (ms - 8) >> 2, q = (ms - 8) & 3;
             const int ax = side >> 1, hi = side & 1;
             const int t1 = ax == 0 ? 1 : 0, t2 = ax == 2 ? 1 : 2;
             const int sib = (hi << ax) | ((q & 1) << t1) | ((q >> 1) << t2);
-            e = S.nb[sib][side_slot(ax, hi)];
+            e = S.nb[27 * sib + side_slot(ax, hi)];
         }
-        S.sm[it] = e >= 0 ? a.son[e] : 0u;
+        if (e >= 0) m = a.son[e];
     }
 
     // A: gather uold for the stencil cells, primitive variables
+    const bool outside = S.outside != 0;
     for (int it = tid; it < kSibW; it += NT) {
         const uint32_t code = c_sib.wcode[it];
-        const int sib = static_cast<int>(code >> 9);
-        int c[3] = {static_cast<int>(code & 7) - 2 - 2 * (sib & 1), static_cast<int>((code >> 3) & 7) - 2 - 2 * ((sib >> 1) & 1),
-                    static_cast<int>((code >> 6) & 7) - 2 - 2 * (sib >> 2)};
-        int s[3] = {slot_of(c[0]), slot_of(c[1]), slot_of(c[2])};
+        int entry = code & 255, bit = (code >> 8) & 7;
+        const int sib = (code >> 11) & 7;
+        if (outside) {
+            int c[3], s[3];
 #pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            if (s[ax] != 0) {
-                const int fs = nslot(ax == 0 ? s[0] : 0, ax == 1 ? s[1] : 0, ax == 2 ? s[2] : 0);
-                if (S.nb[sib][fs] == RG_NBR_OUTSIDE) {
+            for (int ax = 0; ax < 3; ++ax) {
+                c[ax] = static_cast<int>((code >> (14 + 3 * ax)) & 7) - 2;
+                s[ax] = slot_of(c[ax]);
+            }
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax)
+                if (s[ax] != 0 &&
+                    S.nb[27 * sib + nslot(ax == 0 ? s[0] : 0, ax == 1 ? s[1] : 0, ax == 2 ? s[2] : 0)] == RG_NBR_OUTSIDE) {
                     c[ax] = s[ax] > 0 ? 1 : 0;
                     s[ax] = 0;
                 }
-            }
+            entry = 27 * sib + nslot(s[0], s[1], s[2]);
+            bit = (c[0] & 1) + 2 * (c[1] & 1) + 4 * (c[2] & 1);
         }
-        int e = S.nb[sib][nslot(s[0], s[1], s[2])];
-        if (e == RG_NBR_OUTSIDE) e = static_cast<int>(S.oct[sib]);
-        const int64_t cell = e >= 0 ? 8 * int64_t(e) + ((c[0] & 1) + 2 * (c[1] & 1) + 4 * (c[2] & 1))
-                                    : (-1 - int64_t(e));
+        int e = S.nb[entry];
+        if (e == RG_NBR_OUTSIDE) e = S.oct[sib];
         double U[NV], W[NV];
         if (e >= 0) {
+            const double *src = a.uold + NV * (8 * int64_t(e) + bit);
 #pragma unroll
-            for (int v = 0; v < NV; ++v) U[v] = a.uold[NV * cell + v];
+            for (int v = 0; v < NV; ++v) U[v] = src[v];
         } else if constexpr (GH) {
-            coarse_ghost(a, cell, c[0] & 1, c[1] & 1, c[2] & 1, U);
+            coarse_ghost(a, -1 - int64_t(e), bit & 1, (bit >> 1) & 1, bit >> 2, U);
         } else {
+            const double *src = a.ucoarse + NV * (-1 - int64_t(e));
 #pragma unroll
-            for (int v = 0; v < NV; ++v) U[v] = a.ucoarse[NV * cell + v];
+            for (int v = 0; v < NV; ++v) U[v] = src[v];
         }
         prim64(U, a.gamma, W);
 #pragma unroll
         for (int v = 0; v < NV; ++v) S.w[v][it] = static_cast<R>(W[v]);
-        if (it < 64) {
+    }
+    if (ms >= 0 && ms < 32) {
+        S.sm[ms] = m;
+        if (m) S.split = 1;
+    }
+    // the values this thread updates, in the order of the state
+    constexpr int kOwn = (kSibU + NT - 1) / NT;
+    double own[kOwn];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) S.u[it][v] = U[v];
-        }
+    for (int q = 0; q < kOwn; ++q) {
+        const int k = tid + q * NT, sib = k / (8 * NV);
+        own[q] = k < kSibU ? a.uold[8 * NV * int64_t(S.oct[sib]) + (k - 8 * NV * sib)] : 0.0;
     }
     __syncthreads();
 
     // B: slopes, predictor and face states of the own and face-layer cells
+    const bool split = S.split != 0;
     for (int it = tid; it < kSibR; it += NT) {
         const uint64_t code = c_sib.rcode[it];
-        const int x = static_cast<int>((code >> 54) & 7) - 2, y = static_cast<int>((code >> 57) & 7) - 2,
-                  z = static_cast<int>((code >> 60) & 7) - 2;
-        R dW[3][NV], Wp[NV];
+        R dW[3][NV], Wp[NV], st[NV];
         reconstruct<R>(ld5(S.w, it).v, ld5(S.w, code & 511).v, ld5(S.w, (code >> 9) & 511).v,
                        ld5(S.w, (code >> 18) & 511).v, ld5(S.w, (code >> 27) & 511).v, ld5(S.w, (code >> 36) & 511).v,
                        ld5(S.w, (code >> 45) & 511).v, h, gam, dW, Wp);
-        const int p[3] = {x, y, z};
+        if (it < 64) {
+            const int x = 2 * ((it >> 3) & 1) + (it & 1), y = 2 * ((it >> 4) & 1) + ((it >> 1) & 1),
+                      z = 2 * (it >> 5) + ((it >> 2) & 1);
+            const int f[3] = {sib_face(0, x, y, z), sib_face(1, y, x, z), sib_face(2, z, x, y)};
 #pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            const int t1 = ax == 0 ? 1 : 0, t2 = ax == 2 ? 1 : 2;
-            const bool inside_t = p[t1] >= 0 && p[t1] <= 3 && p[t2] >= 0 && p[t2] <= 3;
-            if (!inside_t) continue;
-#pragma unroll
-            for (int side = 0; side < 2; ++side) {
-                const int c = side ? p[ax] + 1 : p[ax];
-                if (c < 0 || c > 4) continue;
-                R st[NV];
-                face_state<R>(Wp, dW[ax], side != 0, st);
-                lds_put(S.fs[side ? 0 : 1], sib_face(ax, c, p[t1], p[t2]), st);
+            for (int ax = 0; ax < 3; ++ax) {
+                face_state<R>(Wp, dW[ax], false, st);
+                lds_put(S.fs[1], f[ax], st);
+                face_state<R>(Wp, dW[ax], true, st);
+                lds_put(S.fs[0], f[ax] + 16, st);
             }
+        } else {
+            const int fc = c_sib.fcode[it - 64];
+            const int side = (fc >> 8) & 1, ax = fc >> 9;
+            R d[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) d[v] = ax == 0 ? dW[0][v] : (ax == 1 ? dW[1][v] : dW[2][v]);
+            face_state<R>(Wp, d, side == 0, st);
+            R *to = &S.fs[0][0][0] + side * (NV * kSibF) + (fc & 255);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) to[v * kSibF] = st[v];
         }
     }
     __syncthreads();
 
     // C: HLLC on the 240 faces
     for (int f = tid; f < kSibF; f += NT) {
-        const int ax = f / 80, c = (f / 16) % 5, t1 = f & 3, t2 = (f >> 2) & 3;
+        const int ax = f >= 160 ? 2 : (f >= 80 ? 1 : 0);
         R L[NV], Rr[NV];
         lds_get(L, S.fs[0], f);
         lds_get(Rr, S.fs[1], f);
         bool zero = false;
+        if (split) {
+            const int c = (f - 80 * ax) >> 4, t1 = f & 3, t2 = (f >> 2) & 3;
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int pa = c - 1 + k;
-            const int px0 = ax == 0 ? pa : t1;
-            const int px1 = ax == 1 ? pa : (ax == 0 ? t1 : t2);
-            const int px2 = ax == 2 ? pa : t2;
-            const int bit = (px0 & 1) + 2 * (px1 & 1) + 4 * (px2 & 1);
-            zero = zero || ((sib_mask_at(S.sm, px0, px1, px2) >> bit) & 1u);
+            for (int k = 0; k < 2; ++k) {
+                const int pa = c - 1 + k;
+                const int px0 = ax == 0 ? pa : t1;
+                const int px1 = ax == 1 ? pa : (ax == 0 ? t1 : t2);
+                const int px2 = ax == 2 ? pa : t2;
+                const int bit = (px0 & 1) + 2 * (px1 & 1) + 4 * (px2 & 1);
+                zero = zero || ((sib_mask_at(S.sm, px0, px1, px2) >> bit) & 1u);
+            }
         }
         double gf[NV];
         face_flux<R>(L, Rr, ax, gam, g1, r, zero, gf);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) S.g[f][v] = gf[v];
+        lds_put(S.g, f, gf);
     }
     __syncthreads();
 
-    // D: update, sibling by sibling so that each writes its 40 values in order
-    for (int it = tid; it < 8 * 8 * NV; it += NT) {
-        const int sib = it / (8 * NV), k = it - 8 * NV * sib;
-        const int cidx = k / NV, v = k - NV * cidx;
-        const int x = 2 * (sib & 1) + (cidx & 1), y = 2 * ((sib >> 1) & 1) + ((cidx >> 1) & 1),
-                  z = 2 * (sib >> 2) + (cidx >> 2);
-        const int own = x + 4 * y + 16 * z;
-        const double gxm = S.g[sib_face(0, x, y, z)][v], gxp = S.g[sib_face(0, x + 1, y, z)][v];
-        const double gym = S.g[sib_face(1, y, x, z)][v], gyp = S.g[sib_face(1, y + 1, x, z)][v];
-        const double gzm = S.g[sib_face(2, z, x, y)][v], gzp = S.g[sib_face(2, z + 1, x, y)][v];
-        const double un = ((S.u[own][v] + (gxm - gxp)) + (gym - gyp)) + (gzm - gzp);
-        a.unew[8 * NV * S.oct[sib] + k] = un;
-        S.u[own][v] = un;
+    // D: update, each thread one value in the order of the state
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+        const int k = tid + q * NT;
+        if (k >= kSibU) break;
+        const int n = k / NV, v = k - NV * n, sib = n >> 3;
+        const int x = 2 * (sib & 1) + (n & 1), y = 2 * ((sib >> 1) & 1) + ((n >> 1) & 1),
+                  z = 2 * (sib >> 2) + ((n >> 2) & 1);
+        const double *g = S.g[v];
+        const int fx = sib_face(0, x, y, z), fy = sib_face(1, y, x, z), fz = sib_face(2, z, x, y);
+        const double un = ((own[q] + (g[fx] - g[fx + 16])) + (g[fy] - g[fy + 16])) + (g[fz] - g[fz + 16]);
+        a.unew[8 * NV * int64_t(S.oct[sib]) + (k - 8 * NV * sib)] = un;
+        S.u[k] = un;
     }
 
     // E: flux owed to coarse neighbours across the group's outer faces;
     // without a buffer there must be none (a coarse neighbour is reported)
-    if (!a.corr) {
-        for (int it = tid; it < 8 * 6; it += NT) {
-            const int sib = it / 6, side = it - 6 * sib;
-            const int ax = side >> 1, hi = side & 1;
-            if (((sib >> ax) & 1) != hi) continue;
-            const int e = S.nb[sib][side_slot(ax, hi)];
-            if (e < 0 && e != RG_NBR_OUTSIDE) flag_error(a.hdr, RG_EINVAL, S.oct[sib]);
-        }
-    } else {
-        for (int it = tid; it < 8 * 6 * NV; it += NT) {
-            const int sib = it / (6 * NV), k = it - 6 * NV * sib;
-            const int side = k / NV, v = k - NV * side;
-            const int ax = side >> 1, hi = side & 1;
-            if (((sib >> ax) & 1) != hi) continue;
-            const int e = S.nb[sib][side_slot(ax, hi)];
+    if (S.coarse) {
+        for (int it = tid; it < 8 * 3 * NV; it += NT) {
+            const int p = it / NV, v = it - NV * p;
+            const int sib = p / 3, ax = p - 3 * sib, hi = (sib >> ax) & 1;
+            const int e = S.nb[27 * sib + side_slot(ax, hi)];
             if (!(e < 0 && e != RG_NBR_OUTSIDE)) continue;
+            if (!a.corr) {
+                if (v == 0) flag_error(a.hdr, RG_EINVAL, S.oct[sib]);
+                continue;
+            }
             const int t1 = ax == 0 ? 1 : 0, t2 = ax == 2 ? 1 : 2;
-            const int b1 = 2 * ((sib >> t1) & 1), b2 = 2 * ((sib >> t2) & 1);
-            const int c = hi ? 4 : 0;
-            const double sum = (S.g[sib_face(ax, c, b1, b2)][v] + S.g[sib_face(ax, c, b1 + 1, b2)][v]) +
-                               (S.g[sib_face(ax, c, b1, b2 + 1)][v] + S.g[sib_face(ax, c, b1 + 1, b2 + 1)][v]);
+            const int f = sib_face(ax, hi ? 4 : 0, 2 * ((sib >> t1) & 1), 2 * ((sib >> t2) & 1));
+            const double sum = (S.g[v][f] + S.g[v][f + 1]) + (S.g[v][f + 4] + S.g[v][f + 5]);
             const double d = 0.125 * sum;
             const double val = hi ? d : -d;
-            double *dst = a.corr + 30 * (S.oct[sib] - a.corr_base) + k;
+            double *dst = a.corr + 30 * (S.oct[sib] - a.corr_base) + NV * (2 * ax + hi) + v;
             *dst = a.corr_mode == 0 ? val : (a.corr_mode == 1 ? 0.0 : *dst) + val;
         }
     }
 
     // F: fused CFL limit of the new state over the leaf cells that no
-    // coarse-fine correction will change (no split face neighbour)
+    // coarse-fine correction will change (no split face neighbour); the 64
+    // cells are one wave's
     if (a.dt_next) {
         __syncthreads();
-        double best = __longlong_as_double(0x7ff0000000000000ll);
-        double nf = 0.0;
-        for (int it = tid; it < 64; it += NT) {
-            const int x = it & 3, y = (it >> 2) & 3, z = it >> 4;
-            const int bit0 = (x & 1) + 2 * (y & 1) + 4 * (z & 1);
-            if ((S.sm[(x >> 1) + 2 * (y >> 1) + 4 * (z >> 1)] >> bit0) & 1u) continue;
-            bool touch = false;
+        if (tid < 64) {
+            double best = __longlong_as_double(0x7ff0000000000000ll);
+            double nf = 0.0;
+            bool take = true;
+            if (split) {
+                const int sib = tid >> 3;
+                const int x = 2 * (sib & 1) + (tid & 1), y = 2 * ((sib >> 1) & 1) + ((tid >> 1) & 1),
+                          z = 2 * (sib >> 2) + ((tid >> 2) & 1);
+                take = !((S.sm[sib] >> (tid & 7)) & 1u);
 #pragma unroll
-            for (int ax = 0; ax < 3; ++ax) {
-#pragma unroll
-                for (int side = 0; side < 2; ++side) {
-                    const int d = side ? 1 : -1;
+                for (int side = 0; side < 6; ++side) {
+                    const int ax = side >> 1, d = (side & 1) ? 1 : -1;
                     const int px = x + (ax == 0 ? d : 0), py = y + (ax == 1 ? d : 0), pz = z + (ax == 2 ? d : 0);
-                    const int bit = (px & 1) + 2 * (py & 1) + 4 * (pz & 1);
-                    touch = touch || ((sib_mask_at(S.sm, px, py, pz) >> bit) & 1u);
+                    const int bit = (tid & 7) ^ (1 << ax);
+                    take = take && !((sib_mask_at(S.sm, px, py, pz) >> bit) & 1u);
                 }
             }
-            if (touch) continue;
-            double W[NV];
-            prim64(S.u[it], a.gamma, W);
-            const double cs = sqrt_pos(div_pos(a.gamma * W[4], W[0]));
-            const double sp = ((fabs(W[1]) + fabs(W[2])) + fabs(W[3])) + 3.0 * cs;
-            const double cd = a.cfl * (a.dx / sp);
-            best = cd < best ? cd : best;
-            track_finite(nf, sp, S.u[it]);
-        }
-        best = nonfinite_limit(best, nf);
+            if (take) {
+                double U[NV], W[NV];
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            const double o = __shfl_xor(best, off, 64);
-            best = o < best ? o : best;
-        }
-        if ((tid & 63) == 0) S.red[tid >> 6] = best;
-        __syncthreads();
-        if (tid == 0) {
-            double m = S.red[0];
-            for (int k = 1; k < NT / 64; ++k) m = S.red[k] < m ? S.red[k] : m;
-            fold_min(a.dt_next, m, a.hdr);
+                for (int v = 0; v < NV; ++v) U[v] = S.u[NV * tid + v];
+                prim64(U, a.gamma, W);
+                const double cs = sqrt_pos(div_pos(a.gamma * W[4], W[0]));
+                const double sp = ((fabs(W[1]) + fabs(W[2])) + fabs(W[3])) + 3.0 * cs;
+                const double cd = a.cfl * (a.dx / sp);
+                best = cd < best ? cd : best;
+                track_finite(nf, sp, U);
+            }
+            best = nonfinite_limit(best, nf);
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                const double o = __shfl_xor(best, off, 64);
+                best = o < best ? o : best;
+            }
+            if (tid == 0) fold_min(a.dt_next, best, a.hdr);
         }
     }
 }
