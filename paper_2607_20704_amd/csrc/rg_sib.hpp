@@ -24,11 +24,10 @@ namespace {
 constexpr int kSibW = 304;   // stencil cells
 constexpr int kSibR = 160;   // reconstructed cells: own, then face layer
 constexpr int kSibF = 240;   // faces: 3 axes x 5 planes x 16
-constexpr int kSibU = 8 * 8 * NV;   // values of the own cells
 
-// One word (or two) per item, read at the start of the kernel so that the
-// table's latency passes beside that of the octs and lists.  Own cells come
-// first, sibling by sibling (8 sib + c), which is the order of the state.
+// One word (or two) per item.  Own cells come first, x + 4y + 16z: the lanes
+// of a wave then read neighbours in consecutive words (sibling by sibling, as
+// in memory, they met in the same LDS banks four at a time).
 struct SibTables {
     // stencil cell: list entry 27 sib + slot (8 bits), cell within that oct
     // (3), sibling whose 6^3 tile holds it (3), position in that tile + 2 (3
@@ -49,8 +48,13 @@ constexpr int sib_tile(int x, int y, int z) { return (x + 2) + 8 * (y + 2) + 64 
 constexpr int sib_place(int p) { return p < 0 ? 0 : (p > 3 ? 1 : p >> 1); }
 
 // face on axis a between cells c-1 and c (c = 0..4) along a, at (t1, t2) on
-// the other two axes in increasing order
-__host__ __device__ constexpr int sib_face(int a, int c, int t1, int t2) { return 80 * a + 16 * c + t1 + 4 * t2; }
+// the other two axes in increasing order; bit 3 of the place is flipped on
+// the planes c = 2, 3, which puts the faces of 32 consecutive cells in 32
+// different double words of the LDS banks for every axis
+__host__ __device__ constexpr int sib_face(int a, int c, int t1, int t2)
+{
+    return 80 * a + 16 * c + ((t1 + 4 * t2) ^ ((c & 2) << 2));
+}
 
 constexpr SibTables make_sib_tables()
 {
@@ -58,9 +62,8 @@ constexpr SibTables make_sib_tables()
     int pos[kSibW][3] = {};
     int16_t index[512] = {};
     int n = 0;
-    for (int sib = 0; sib < 8; ++sib)
-        for (int c = 0; c < 8; ++c, ++n)
-            for (int a = 0; a < 3; ++a) pos[n][a] = 2 * ((sib >> a) & 1) + ((c >> a) & 1);
+    for (; n < 64; ++n)
+        for (int a = 0; a < 3; ++a) pos[n][a] = (n >> (2 * a)) & 3;
     // face layer (reconstructed), then outer layer, per axis and side
     for (int layer = 0; layer < 2; ++layer)
         for (int a = 0; a < 3; ++a)
@@ -122,16 +125,12 @@ template <typename R> struct SibSmem {
     // along the two other axes (lower axis first)
     uint32_t sm[32];
     int32_t outside, coarse, split;   // some list entry outside the domain / a coarse cell; some son mask set
-    // the primitives are dead once the face states exist, the states once the
-    // fluxes do: fluxes over primitives, new state over face states
+    // the primitives are dead once the face states exist
     union {
         R w[NV][kSibW];         // primitive variables of the stencil cells (planes, lds_get)
         double g[NV][kSibF];    // G = F dt/dx per face
     };
-    union {
-        R fs[2][NV][kSibF];     // face states: [0] left of the face, [1] right (planes)
-        double u[kSibU];        // new state of the own cells
-    };
+    R fs[2][NV][kSibF];         // face states: [0] left of the face, [1] right (planes)
 };
 
 // son mask holding the cell at group position (x, y, z), one coordinate of
@@ -243,14 +242,6 @@ __device__ __forceinline__ void hydro_sib(const LevelArgs &a, const int32_t *__r
         S.sm[ms] = m;
         if (m) S.split = 1;
     }
-    // the values this thread updates, in the order of the state
-    constexpr int kOwn = (kSibU + NT - 1) / NT;
-    double own[kOwn];
-#pragma unroll
-    for (int q = 0; q < kOwn; ++q) {
-        const int k = tid + q * NT, sib = k / (8 * NV);
-        own[q] = k < kSibU ? a.uold[8 * NV * int64_t(S.oct[sib]) + (k - 8 * NV * sib)] : 0.0;
-    }
     __syncthreads();
 
     // B: slopes, predictor and face states of the own and face-layer cells
@@ -262,15 +253,15 @@ __device__ __forceinline__ void hydro_sib(const LevelArgs &a, const int32_t *__r
                        ld5(S.w, (code >> 18) & 511).v, ld5(S.w, (code >> 27) & 511).v, ld5(S.w, (code >> 36) & 511).v,
                        ld5(S.w, (code >> 45) & 511).v, h, gam, dW, Wp);
         if (it < 64) {
-            const int x = 2 * ((it >> 3) & 1) + (it & 1), y = 2 * ((it >> 4) & 1) + ((it >> 1) & 1),
-                      z = 2 * (it >> 5) + ((it >> 2) & 1);
-            const int f[3] = {sib_face(0, x, y, z), sib_face(1, y, x, z), sib_face(2, z, x, y)};
+            const int x = it & 3, y = (it >> 2) & 3, z = it >> 4;
+            const int lo[3] = {sib_face(0, x, y, z), sib_face(1, y, x, z), sib_face(2, z, x, y)};
+            const int hi[3] = {sib_face(0, x + 1, y, z), sib_face(1, y + 1, x, z), sib_face(2, z + 1, x, y)};
 #pragma unroll
             for (int ax = 0; ax < 3; ++ax) {
                 face_state<R>(Wp, dW[ax], false, st);
-                lds_put(S.fs[1], f[ax], st);
+                lds_put(S.fs[1], lo[ax], st);
                 face_state<R>(Wp, dW[ax], true, st);
-                lds_put(S.fs[0], f[ax] + 16, st);
+                lds_put(S.fs[0], hi[ax], st);
             }
         } else {
             const int fc = c_sib.fcode[it - 64];
@@ -294,7 +285,7 @@ __device__ __forceinline__ void hydro_sib(const LevelArgs &a, const int32_t *__r
         lds_get(Rr, S.fs[1], f);
         bool zero = false;
         if (split) {
-            const int c = (f - 80 * ax) >> 4, t1 = f & 3, t2 = (f >> 2) & 3;
+            const int c = (f - 80 * ax) >> 4, t = (f & 15) ^ ((c & 2) << 2), t1 = t & 3, t2 = t >> 2;
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const int pa = c - 1 + k;
@@ -309,27 +300,65 @@ __device__ __forceinline__ void hydro_sib(const LevelArgs &a, const int32_t *__r
         face_flux<R>(L, Rr, ax, gam, g1, r, zero, gf);
         lds_put(S.g, f, gf);
     }
+    // the own cells are the first wave's to update; their old state is on its
+    // way while the last faces are solved
+    const int x = tid & 3, y = (tid >> 2) & 3, z = (tid >> 4) & 3;
+    const int own_sib = (x >> 1) + 2 * (y >> 1) + 4 * (z >> 1), own_bit = (x & 1) + 2 * (y & 1) + 4 * (z & 1);
+    double U[NV];
+    int64_t own = 0;
+    if (tid < 64) {
+        own = 8 * int64_t(S.oct[own_sib]) + own_bit;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) U[v] = a.uold[NV * own + v];
+    }
     __syncthreads();
 
-    // D: update, each thread one value in the order of the state
-#pragma unroll
-    for (int q = 0; q < kOwn; ++q) {
-        const int k = tid + q * NT;
-        if (k >= kSibU) break;
-        const int n = k / NV, v = k - NV * n, sib = n >> 3;
-        const int x = 2 * (sib & 1) + (n & 1), y = 2 * ((sib >> 1) & 1) + ((n >> 1) & 1),
-                  z = 2 * (sib >> 2) + ((n >> 2) & 1);
-        const double *g = S.g[v];
+    // D: update and, fused, the CFL limit of the new state over the leaf cells
+    // that no coarse-fine correction will change (no split face neighbour)
+    if (tid < 64) {
         const int fx = sib_face(0, x, y, z), fy = sib_face(1, y, x, z), fz = sib_face(2, z, x, y);
-        const double un = ((own[q] + (g[fx] - g[fx + 16])) + (g[fy] - g[fy + 16])) + (g[fz] - g[fz + 16]);
-        a.unew[8 * NV * int64_t(S.oct[sib]) + (k - 8 * NV * sib)] = un;
-        S.u[k] = un;
-    }
-
-    // E: flux owed to coarse neighbours across the group's outer faces;
-    // without a buffer there must be none (a coarse neighbour is reported)
-    if (S.coarse) {
-        for (int it = tid; it < 8 * 3 * NV; it += NT) {
+        const int gx = sib_face(0, x + 1, y, z), gy = sib_face(1, y + 1, x, z), gz = sib_face(2, z + 1, x, y);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const double *g = S.g[v];
+            U[v] = ((U[v] + (g[fx] - g[gx])) + (g[fy] - g[gy])) + (g[fz] - g[gz]);
+            a.unew[NV * own + v] = U[v];
+        }
+        if (a.dt_next) {
+            double best = __longlong_as_double(0x7ff0000000000000ll);
+            double nf = 0.0;
+            bool take = true;
+            if (split) {
+                take = !((S.sm[own_sib] >> own_bit) & 1u);
+#pragma unroll
+                for (int side = 0; side < 6; ++side) {
+                    const int ax = side >> 1, d = (side & 1) ? 1 : -1;
+                    const int px = x + (ax == 0 ? d : 0), py = y + (ax == 1 ? d : 0), pz = z + (ax == 2 ? d : 0);
+                    take = take && !((sib_mask_at(S.sm, px, py, pz) >> (own_bit ^ (1 << ax))) & 1u);
+                }
+            }
+            if (take) {
+                double W[NV];
+                prim64(U, a.gamma, W);
+                const double cs = sqrt_pos(div_pos(a.gamma * W[4], W[0]));
+                const double sp = ((fabs(W[1]) + fabs(W[2])) + fabs(W[3])) + 3.0 * cs;
+                const double cd = a.cfl * (a.dx / sp);
+                best = cd < best ? cd : best;
+                track_finite(nf, sp, U);
+            }
+            best = nonfinite_limit(best, nf);
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                const double o = __shfl_xor(best, off, 64);
+                best = o < best ? o : best;
+            }
+            if (tid == 0) fold_min(a.dt_next, best, a.hdr);
+        }
+    } else if (S.coarse) {
+        // E: flux owed to coarse neighbours across the group's outer faces, by
+        // the other waves; without a buffer there must be none (a coarse
+        // neighbour is reported)
+        for (int it = tid - 64; it < 8 * 3 * NV; it += NT - 64) {
             const int p = it / NV, v = it - NV * p;
             const int sib = p / 3, ax = p - 3 * sib, hi = (sib >> ax) & 1;
             const int e = S.nb[27 * sib + side_slot(ax, hi)];
@@ -345,49 +374,6 @@ __device__ __forceinline__ void hydro_sib(const LevelArgs &a, const int32_t *__r
             const double val = hi ? d : -d;
             double *dst = a.corr + 30 * (S.oct[sib] - a.corr_base) + NV * (2 * ax + hi) + v;
             *dst = a.corr_mode == 0 ? val : (a.corr_mode == 1 ? 0.0 : *dst) + val;
-        }
-    }
-
-    // F: fused CFL limit of the new state over the leaf cells that no
-    // coarse-fine correction will change (no split face neighbour); the 64
-    // cells are one wave's
-    if (a.dt_next) {
-        __syncthreads();
-        if (tid < 64) {
-            double best = __longlong_as_double(0x7ff0000000000000ll);
-            double nf = 0.0;
-            bool take = true;
-            if (split) {
-                const int sib = tid >> 3;
-                const int x = 2 * (sib & 1) + (tid & 1), y = 2 * ((sib >> 1) & 1) + ((tid >> 1) & 1),
-                          z = 2 * (sib >> 2) + ((tid >> 2) & 1);
-                take = !((S.sm[sib] >> (tid & 7)) & 1u);
-#pragma unroll
-                for (int side = 0; side < 6; ++side) {
-                    const int ax = side >> 1, d = (side & 1) ? 1 : -1;
-                    const int px = x + (ax == 0 ? d : 0), py = y + (ax == 1 ? d : 0), pz = z + (ax == 2 ? d : 0);
-                    const int bit = (tid & 7) ^ (1 << ax);
-                    take = take && !((sib_mask_at(S.sm, px, py, pz) >> bit) & 1u);
-                }
-            }
-            if (take) {
-                double U[NV], W[NV];
-#pragma unroll
-                for (int v = 0; v < NV; ++v) U[v] = S.u[NV * tid + v];
-                prim64(U, a.gamma, W);
-                const double cs = sqrt_pos(div_pos(a.gamma * W[4], W[0]));
-                const double sp = ((fabs(W[1]) + fabs(W[2])) + fabs(W[3])) + 3.0 * cs;
-                const double cd = a.cfl * (a.dx / sp);
-                best = cd < best ? cd : best;
-                track_finite(nf, sp, U);
-            }
-            best = nonfinite_limit(best, nf);
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                const double o = __shfl_xor(best, off, 64);
-                best = o < best ? o : best;
-            }
-            if (tid == 0) fold_min(a.dt_next, best, a.hdr);
         }
     }
 }
