@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "rg_brick.hpp"
+#include "rg_corr.hpp"
 #include "rg_internal.hpp"
 #include "rg_math.hpp"
 #include "rg_nbr.hpp"
@@ -238,76 +239,36 @@ __global__ __launch_bounds__(kSibT) void k_batch_groups(const BTree *__restrict_
     });
 }
 
-__global__ __launch_bounds__(kT) void k_batch_corr(const BTree *__restrict__ trees, const Item *__restrict__ items,
-                                                    int64_t nitems, int parity, int side)
-{
-    const int ax = side >> 1, hi = side & 1;
-    const int slot = (ax == 0 ? (hi ? 2 : 0) : 1) + 3 * (ax == 1 ? (hi ? 2 : 0) : 1) + 9 * (ax == 2 ? (hi ? 2 : 0) : 1);
-    const ItemRange r = xcd_items(nitems);
-    for (int64_t it = r.begin; it < r.end; it += r.stride) {
-        const Item I = items[it];
-        const BTree &T = trees[I.tree];
-        double *unew = T.u[parity ^ 1];
-        for (int64_t k = threadIdx.x; k < I.count * NV; k += kT) {
-            const int64_t o = I.first + k / NV;
-            const int v = static_cast<int>(k % NV);
-            const int32_t e = T.nbr27[27 * o + slot];
-            if (!(e < 0 && e != RG_NBR_OUTSIDE)) continue;
-            const int64_t C = -1 - int64_t(e);
-            unew[NV * C + v] = unew[NV * C + v] + T.corr[30 * (o - T.corr_base) + NV * side + v];
-        }
-    }
-}
+// Coarse-fine corrections owed by the border octs listed at [first, first +
+// count) of the tree's schedule list, in one pass (see correct_cell), with the
+// corrected cells' CFL limits folded into the tree's next time step
+struct BatchCorr {
+    double *unew;
+    const double *corr;
+    int64_t corr_base;
+    const int32_t *nbr27;
+    const uint32_t *son;
+    const uint64_t *keys;
+    const int64_t *begin;
+    int lmin, lmax;
+    double gamma, cfl;
+};
 
-// CFL limit of the coarse cells the corrections changed (every coarse face
-// neighbour of the item's octs), folded into the tree's next time step
-__global__ __launch_bounds__(kT) void k_batch_corr_dt(const BTree *__restrict__ trees,
-                                                       const Item *__restrict__ items, int64_t nitems, int parity,
-                                                       double *dt_next)
+__global__ __launch_bounds__(kT) void k_batch_corr(const BTree *__restrict__ trees, const Item *__restrict__ items,
+                                                    int64_t nitems, int parity, double *dt_next)
 {
     __shared__ double s_min[kT / 64];
     const ItemRange r = xcd_items(nitems);
     for (int64_t it = r.begin; it < r.end; it += r.stride) {
         const Item I = items[it];
         const BTree &T = trees[I.tree];
-        const double *u = T.u[parity ^ 1];
+        const BatchCorr a{T.u[parity ^ 1], T.corr, T.corr_base, T.nbr27, T.son, T.keys, T.level_begin, T.lmin,
+                          T.lmax, T.gamma, T.cfl};
         double best = __longlong_as_double(0x7ff0000000000000ll);
         double nf = 0.0;
-        for (int64_t k = threadIdx.x; k < I.count * 6; k += kT) {
-            const int64_t o = I.first + k / 6;
-            const int side = static_cast<int>(k % 6);
-            const int ax = side >> 1, hi = side & 1;
-            const int slot = (ax == 0 ? (hi ? 2 : 0) : 1) + 3 * (ax == 1 ? (hi ? 2 : 0) : 1) +
-                             9 * (ax == 2 ? (hi ? 2 : 0) : 1);
-            const int32_t e = T.nbr27[27 * o + slot];
-            if (!(e < 0 && e != RG_NBR_OUTSIDE)) continue;
-            const int64_t C = -1 - int64_t(e);
-            int l = T.lmin;
-            while (l < T.lmax && o >= T.level_begin[l + 1]) ++l;
-            const double dx = ldexp(1.0, -(l - 1));
-            double U[NV], W[NV];
-#pragma unroll
-            for (int v = 0; v < NV; ++v) U[v] = u[NV * C + v];
-            prim64(U, T.gamma, W);
-            const double cs = sqrt_pos(div_pos(T.gamma * W[4], W[0]));
-            const double sp = ((fabs(W[1]) + fabs(W[2])) + fabs(W[3])) + 3.0 * cs;
-            const double cd = T.cfl * (dx / sp);
-            if (cd < best) best = cd;
-            track_finite(nf, sp, U);
-        }
-        best = nonfinite_limit(best, nf);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            double o = __shfl_xor(best, off, 64);
-            best = o < best ? o : best;
-        }
-        if ((threadIdx.x & 63) == 0) s_min[threadIdx.x >> 6] = best;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double m = s_min[0];
-            for (int k = 1; k < kT / 64; ++k) m = s_min[k] < m ? s_min[k] : m;
-            fold_min(reinterpret_cast<unsigned long long *>(dt_next + I.tree), m, T.hdr);
-        }
+        for (int k = threadIdx.x; k < 6 * static_cast<int>(I.count); k += kT)
+            correct_cell(a, T.list[I.first + k / 6], k % 6, true, best, nf);
+        fold_block(best, nf, s_min, kT, reinterpret_cast<unsigned long long *>(dt_next + I.tree), T.hdr);
         __syncthreads();
     }
 }
@@ -577,7 +538,10 @@ rg_status rg_batch_create(const rg_batch_tree *trees, int ntree, int form, int n
             }
         }
         chunk(it_dt, t, 0, 0, 8 * T->n_oct, 4096);
-        if (T->lmax > T->lmin) chunk(it_corr, t, 0, b.corr_base, T->n_oct - b.corr_base, 1024);
+        // the border lists of all levels above lmin follow each other
+        if (T->lmax > T->lmin)
+            chunk(it_corr, t, 0, sc->border_begin[T->lmin + 1],
+                  sc->border_begin[T->lmax] + sc->border_count[T->lmax] - sc->border_begin[T->lmin + 1], 128);
         maxdepth = std::max(maxdepth, T->lmax - T->lmin);
         chunk(it_clear, t, 0, 0, static_cast<int64_t>(cap), 65536);
         chunk(it_clear, t, 1, 0, T->n_oct, 65536);
@@ -712,11 +676,8 @@ rg_status rg_batch_create(const rg_batch_tree *trees, int ntree, int form, int n
                 break;
             }
         }
-        if (ph_corr.n) {
-            for (int side = 0; side < 6; ++side)
-                k_batch_corr<<<g_corr, kT, 0, cs>>>(d_trees, ph_corr.d_items, ph_corr.n, parity, side);
-            k_batch_corr_dt<<<g_corr, kT, 0, cs>>>(d_trees, ph_corr.d_items, ph_corr.n, parity, dt_next);
-        }
+        if (ph_corr.n)
+            k_batch_corr<<<g_corr, kT, 0, cs>>>(d_trees, ph_corr.d_items, ph_corr.n, parity, dt_next);
         for (int k = 0; k < maxdepth; ++k) {
             const Phase &p = phases[P_RESTRICT + k];
             if (p.n) k_batch_restrict<<<g_restrict[k], kT, 0, cs>>>(d_trees, p.d_items, p.n, parity);

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(NT) void k_hydro_level(LevelArgs a, LevelTab lv)
 // one complete sibling group per workgroup: the list's entry is the group's
 // first oct
 template <typename R, int NT, bool GH>
-__global__ __launch_bounds__(NT) void k_hydro_sib(LevelArgs a, LevelTab lv, const int32_t *__restrict__ father)
+__global__ __launch_bounds__(NT, 7) void k_hydro_sib(LevelArgs a, LevelTab lv, const int32_t *__restrict__ father)
 {
     __shared__ SibSmem<R> S;
     const int w = xcd_item(lv.item_end[lv.n - 1]);
