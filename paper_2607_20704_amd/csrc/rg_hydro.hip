@@ -63,7 +63,7 @@ __global__ __launch_bounds__(NT) void k_hydro_level(LevelArgs a, LevelTab lv)
 // one complete sibling group per workgroup: the list's entry is the group's
 // first oct
 template <typename R, int NT, bool GH>
-__global__ __launch_bounds__(NT, 7) void k_hydro_sib(LevelArgs a, LevelTab lv, const int32_t *__restrict__ father)
+__global__ __launch_bounds__(NT) void k_hydro_sib(LevelArgs a, LevelTab lv, const int32_t *__restrict__ father)
 {
     __shared__ SibSmem<R> S;
     const int w = xcd_item(lv.item_end[lv.n - 1]);
@@ -230,6 +230,8 @@ template <typename R> rg_status launch_form(const LevelArgs &a, const LevelTab &
 {
     const int g = tune && tune->octs_per_group ? tune->octs_per_group : 4;
     const int nt = tune && tune->threads ? tune->threads : 256;
+    if (g == 8 && nt == 320) return launch_level<R, 8, 320>(a, lv, s);
+    if (g == 4 && nt == 320) return launch_level<R, 4, 320>(a, lv, s);
     if (g == 4 && nt == 256) return launch_level<R, 4, 256>(a, lv, s);
     if (g == 2 && nt == 128) return launch_level<R, 2, 128>(a, lv, s);
     if (g == 8 && nt == 256) return launch_level<R, 8, 256>(a, lv, s);
