@@ -243,7 +243,7 @@ typedef struct rg_tuning {
     int32_t brick_waves;      /* brick kernel register budget: waves per SIMD it is compiled for
                                  (FP64: 2 or 3, mixed: 3 or 4; 0 = default: 2 for FP64, 3 mixed) */
     int32_t no_groups;        /* 1: scheduled updates leave complete sibling groups to the per-oct kernel */
-    int32_t group_threads;    /* sibling-group kernel workgroup size: 256, 320 or 384 (0 = default) */
+    int32_t group_threads;    /* sibling-group kernel workgroup size: 256, 320 or 384 (0 = by form and ghosts) */
     int32_t no_pairs;         /* 1: a complete finest level by its bricks, not by columns cut into
                                  segments of the length that fills the chip (the same bits either way) */
 } rg_tuning;
@@ -641,7 +641,7 @@ rg_status rg_mg_level_destroy(rg_mg_level *h);
  * device buffers they point to are used by every rg_batch_run.
  * tune: octs_per_group 2, 4 (default) or 8; no_bricks 1 runs every oct
  * through the per-oct body; no_groups 1 leaves complete sibling groups to
- * the per-oct body (the batched group kernel runs 256 threads); persistent
+ * the per-oct body (the batched group kernel has the default size); persistent
  * selects persistent grids.  Every choice gives the same bits.  Allocates one device table (work lists and
  * tree descriptors) and the graph; synchronises `stream` once. */
 typedef struct rg_batch_tree {

@@ -102,7 +102,7 @@ rg_status check_sink(int64_t *h_bad_index, hipStream_t s)
 rg_status hydro_tree_levels(const rg_tree *t, const rg_schedule *sc, int l0, int l1, const double *d_dt, double gamma,
                             const double *d_uold, const double *d_ucoarse, double *d_unew, double cfl,
                             double *d_dt_next, int form, const rg_tuning *tune, hipStream_t s, double *d_corr,
-                            int corr_mode, const double *d_ucoarse2);
+                            int corr_mode, const double *d_ucoarse2, bool skip_split);
 rg_status tree_corrections(const rg_tree *t, double *unew, const double *corr, const int32_t *list, int64_t ob,
                            int64_t oe, double gamma, double cfl, double *dt_next, hipStream_t s);
 
@@ -193,7 +193,7 @@ rg_status rg_step(const rg_tree *t, const double *d_uold, double *d_unew, double
     }
     const int64_t corr_base = t->level_begin[t->lmin + 1];
     RG_TRY(hydro_tree_levels(t, t->sched, t->lmin, t->lmax, d_dt, gamma, d_uold, d_uold, d_unew, cfl, dt_next, form,
-                             tune, s, t->d_corr, 0, d_uold));
+                             tune, s, t->d_corr, 0, d_uold, true));
     if (t->lmax > t->lmin) {
         if (t->d_keys) {
             // the border lists of all levels above lmin follow each other

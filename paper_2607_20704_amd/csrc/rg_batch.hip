@@ -53,7 +53,6 @@ struct Item {
 };
 
 constexpr int kT = 256;      // threads of the batched kernels
-constexpr int kSibT = 320;   // of the sibling-group kernel: one stencil cell each
 
 // Items of a persistent loop: workgroups are dealt round-robin to the eight
 // XCDs, so workgroup w serves a contiguous eighth of the item list (XCD
@@ -172,6 +171,7 @@ __global__ __launch_bounds__(BT, sizeof(R) == 8 ? 2 : 3) void k_batch_bricks(con
         a.son = T.son;
         a.keys = T.keys;
         a.bricks = nullptr;
+        a.skip_split = 1;
         a.first = 0;
         a.nb = 0;
         a.dt = dt + I.tree;
@@ -198,6 +198,7 @@ __device__ __forceinline__ LevelArgs level_args(const BTree &T, const Item &I, i
     a.son = T.son;
     a.corr = level > T.lmin ? T.corr : nullptr;
     a.corr_base = T.corr_base;
+    a.skip_split = 1;
     a.corr_mode = 0;
     a.ghost = T.ghost;
     a.ucoarse2 = T.u[parity];
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(kT) void k_batch_octs(const BTree *__restrict__ tre
 // complete sibling groups: item = one group, `first` its entry in the tree's
 // schedule list
 template <typename R, bool P, bool GH>
-__global__ __launch_bounds__(kSibT) void k_batch_groups(const BTree *__restrict__ trees,
+__global__ __launch_bounds__(sib_threads(sizeof(R) == 8, GH)) void k_batch_groups(const BTree *__restrict__ trees,
                                                         const Item *__restrict__ items, int64_t nitems, int parity,
                                                         const double *dt, double *dt_next)
 {
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(kSibT) void k_batch_groups(const BTree *__restrict_
         const Item I = items[it];
         const BTree &T = trees[I.tree];
         const LevelArgs a = level_args(T, I, parity, dt, dt_next);
-        hydro_sib<R, kSibT, GH>(a, T.father, T.list[I.first], S);
+        hydro_sib<R, sib_threads(sizeof(R) == 8, GH), GH>(a, T.father, T.list[I.first], S);
     });
 }
 
@@ -435,18 +436,19 @@ rg_status launch_groups(bool gh, bool persistent, const BTree *trees, const Phas
                         double *dt_next, hipStream_t s)
 {
     if (p.n == 0) return RG_OK;
+    const int nt = sib_threads(sizeof(R) == 8, gh);
     if (persistent) {
-        if (gh) {
-            const int grid = persistent_grid(reinterpret_cast<const void *>(&k_batch_groups<R, true, true>), kSibT, p.n);
-            k_batch_groups<R, true, true><<<grid, kSibT, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
-        } else {
-            const int grid = persistent_grid(reinterpret_cast<const void *>(&k_batch_groups<R, true, false>), kSibT, p.n);
-            k_batch_groups<R, true, false><<<grid, kSibT, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
-        }
+        const void *k = gh ? reinterpret_cast<const void *>(&k_batch_groups<R, true, true>)
+                           : reinterpret_cast<const void *>(&k_batch_groups<R, true, false>);
+        const int grid = persistent_grid(k, nt, p.n);
+        if (gh)
+            k_batch_groups<R, true, true><<<grid, nt, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
+        else
+            k_batch_groups<R, true, false><<<grid, nt, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
     } else if (gh) {
-        k_batch_groups<R, false, true><<<one_shot_grid(p.n), kSibT, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
+        k_batch_groups<R, false, true><<<one_shot_grid(p.n), nt, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
     } else {
-        k_batch_groups<R, false, false><<<one_shot_grid(p.n), kSibT, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
+        k_batch_groups<R, false, false><<<one_shot_grid(p.n), nt, 0, s>>>(trees, p.d_items, p.n, parity, dt, dt_next);
     }
     return launch_status("batched sibling groups");
 }

@@ -144,9 +144,10 @@ int wg_slots(int per_cu)
 }
 
 BrickArgs brick_args(const rg_tree *t, const double *uold, double *unew, const int32_t *bricks, const double *dt,
-                     double gamma, double cfl, double *dt_next)
+                     double gamma, double cfl, double *dt_next, bool skip_split)
 {
     BrickArgs a;
+    a.skip_split = skip_split;
     a.uold = uold;
     a.unew = unew;
     a.nbr27 = t->d_nbr27;
@@ -169,10 +170,10 @@ BrickArgs brick_args(const rg_tree *t, const double *uold, double *unew, const i
 
 rg_status hydro_bricks(const rg_tree *t, const double *uold, double *unew, const int32_t *list, const LevelTab &lv,
                        const double *dt, double gamma, int form, double cfl, double *dt_next, int waves,
-                       hipStream_t s)
+                       bool skip_split, hipStream_t s)
 {
     if (lv.n == 0) return RG_OK;
-    const BrickArgs a = brick_args(t, uold, unew, list, dt, gamma, cfl, dt_next);
+    const BrickArgs a = brick_args(t, uold, unew, list, dt, gamma, cfl, dt_next, skip_split);
     const int per_cu = wg_per_cu(form, waves);
     const int slabs = brick_slabs(tab_items(lv), wg_slots(per_cu), per_cu);
     const unsigned grid = static_cast<unsigned>(8 * ((tab_items(lv) * slabs + 7) / 8));
@@ -198,7 +199,7 @@ rg_status hydro_bricks(const rg_tree *t, const double *uold, double *unew, const
 rg_status hydro_columns(const rg_tree *t, int level, const double *uold, double *unew, const double *dt, double gamma,
                         int form, double cfl, double *dt_next, int waves, hipStream_t s)
 {
-    BrickArgs a = brick_args(t, uold, unew, nullptr, dt, gamma, cfl, dt_next);
+    BrickArgs a = brick_args(t, uold, unew, nullptr, dt, gamma, cfl, dt_next, false);
     a.dx = ldexp(1.0, -level);
     a.first = t->level_begin[level];
     a.nb = level - 1;

@@ -31,6 +31,7 @@ struct BrickArgs {
     double cfl;
     unsigned long long *dt_next;   // if set: CFL limit of the new state folded in (bits of a positive double)
     HashHeader *hdr;               // device-side errors (non-finite state)
+    int skip_split;                // 1: sweeps over split cells only are left out (a restriction follows)
     int64_t first;                 // columns of a complete level: its first oct and bits per oct coordinate
     int nb;
 };
@@ -144,6 +145,7 @@ template <typename R, int NB = 1, typename TAB = BrickTable> struct BrickSmem {
     uint8_t split[NB][PW * PW];     // split flags of the current plane's cells
     double red[8];                  // block minimum of the fused CFL limit, one per wave
     int32_t any_son;                // some slot oct in reach has a split cell
+    int32_t live;                   // some cell of the sweep is a leaf
     // mixed form with one buffer: each column's partial update of the
     // previous plane (its own slot, no sharing), kept here rather than in
     // registers
@@ -304,7 +306,7 @@ __device__ __forceinline__ bool brick_setup(const BrickArgs &a, int64_t base, in
         const int sc = (kk & 7) - c0;
         if (sc >= -1 && sc <= nc) T.slot[T.at(i & 7, j & 7, sc)] = static_cast<int32_t>(o);
     }
-    if (tid == 0) S.any_son = 0;
+    if (tid == 0) S.any_son = S.live = 0;
     {
         int32_t i, j, kk, l;
         key_coords(a.keys[base], i, j, kk, l);
@@ -333,6 +335,7 @@ __device__ __forceinline__ bool brick_setup(const BrickArgs &a, int64_t base, in
         const uint8_t m = e >= 0 ? static_cast<uint8_t>(a.son[e]) : 0;
         T.son[s] = m;
         if (m) S.any_son = 1;
+        if (out == 0 && m != 0xff) S.live = 1;
         if (out) T.slot[s] = e;
     }
     __syncthreads();
@@ -347,7 +350,9 @@ __device__ __forceinline__ void brick_body(const BrickArgs &a, int64_t base, int
                                            BrickSmem<R, NB, BrickTable> &S)
 {
     Geom g;
-    if (brick_setup<BT>(a, base, z0, nz, S, g))
+    const bool gen = brick_setup<BT>(a, base, z0, nz, S, g);
+    if (a.skip_split && !S.live) return;   // only split cells, which the restriction overwrites
+    if (gen)
         brick_sweep<R, KU, NB, true>(a, b, g, S, nz);
     else
         brick_sweep<R, KU, NB, false>(a, b, g, S, nz);

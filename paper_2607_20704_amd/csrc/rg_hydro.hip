@@ -230,8 +230,6 @@ template <typename R> rg_status launch_form(const LevelArgs &a, const LevelTab &
 {
     const int g = tune && tune->octs_per_group ? tune->octs_per_group : 4;
     const int nt = tune && tune->threads ? tune->threads : 256;
-    if (g == 8 && nt == 320) return launch_level<R, 8, 320>(a, lv, s);
-    if (g == 4 && nt == 320) return launch_level<R, 4, 320>(a, lv, s);
     if (g == 4 && nt == 256) return launch_level<R, 4, 256>(a, lv, s);
     if (g == 2 && nt == 128) return launch_level<R, 2, 128>(a, lv, s);
     if (g == 8 && nt == 256) return launch_level<R, 8, 256>(a, lv, s);
@@ -255,7 +253,7 @@ template <typename R>
 rg_status launch_sib_form(const LevelArgs &a, const LevelTab &lv, const int32_t *father, const rg_tuning *tune,
                           hipStream_t s)
 {
-    const int nt = tune && tune->group_threads ? tune->group_threads : 320;
+    const int nt = tune && tune->group_threads ? tune->group_threads : sib_threads(sizeof(R) == 8, a.ghost);
     if (nt == 320) return launch_sib<R, 320>(a, lv, father, s);
     if (nt == 256) return launch_sib<R, 256>(a, lv, father, s);
     if (nt == 384) return launch_sib<R, 384>(a, lv, father, s);
@@ -371,6 +369,7 @@ rg_status rg_hydro_step_level(double dx, const double *d_dt, double gamma, const
     RG_REQUIRE(!d_corr || corr_base <= oct_begin, "corr_base beyond the oct range");
     RG_REQUIRE(!d_dt_next || (cfl > 0 && aligned(d_dt_next, 8)), "bad cfl or misaligned dt_next");
     LevelArgs a;
+    a.skip_split = 0;
     a.corr_mode = 0;
     a.ghost = RG_GHOST_INJECT;
     a.ucoarse2 = d_uold;

@@ -399,6 +399,7 @@ struct LevelArgs {
     const uint32_t *son;
     double *corr;
     int64_t corr_base;
+    int skip_split;       // 1: octs of split cells only need no update (a restriction follows)
     int corr_mode;        // 0: store the owed flux; 1: store 0 + flux; 2: add it (sums over substeps)
     int ghost;            // coarse ghost cells: 0 injection, 1 minmod-limited linear interpolation
     const double *ucoarse2;   // cells two levels down (neighbours of a coarse ghost cell's own coarse cell)
@@ -452,7 +453,7 @@ __device__ __forceinline__ int tab_entry(const LevelTab &t, int &i)
 
 rg_status fill_u32(uint32_t *d, int64_t n, uint32_t v, hipStream_t s);
 // lmax: the tree's finest level; n_below_lmax: the octs before it (the ones
-// whose son masks are cleared first)
+// whose son masks are cleared first).
 rg_status neighbours_scheduled(void *d_ws, const uint64_t *d_keys, int64_t n, int lmin, int lmax, int64_t n_below_lmax,
                                int bc, const int32_t *bricks, int64_t nbricks, const int32_t *rest, int64_t nrest,
                                int32_t *d_nbr27, int32_t *d_father_cell, uint32_t *d_son_mask, hipStream_t s);

@@ -157,6 +157,7 @@ template <typename R, int G> struct Smem {
     int32_t nb[G][27];
     uint32_t sm[G][7];          // son masks: own, then sides x-, x+, y-, y+, z-, z+
     int32_t outside, coarse, split;   // some list entry outside the domain / a coarse cell; some son mask set
+    int32_t live;                     // some cell is a leaf, or split cells are wanted too
     // the stencil's primitives are dead once the face states exist (phase
     // B), before the fluxes are written (phase C): one LDS region serves both
     union {
@@ -183,8 +184,12 @@ __device__ __forceinline__ void hydro_group(const LevelArgs &a, int64_t first, i
 
     // oct indices, neighbour entries and son masks
     if (tid < G) S.oct[tid] = tid < count ? (a.list ? int64_t(a.list[first + tid]) : first + tid) : 0;
-    if (tid == 0) S.outside = S.coarse = S.split = 0;
+    if (tid == 0) {
+        S.outside = S.coarse = S.split = 0;
+        S.live = !a.skip_split;
+    }
     __syncthreads();
+    if (a.skip_split && tid < count && a.son[S.oct[tid]] != 0xffu) S.live = 1;
     for (int it = tid; it < count * 27; it += NT) {
         const int g = it / 27, s = it - 27 * g;
         const int32_t e = a.nbr27[27 * S.oct[g] + s];
@@ -192,6 +197,8 @@ __device__ __forceinline__ void hydro_group(const LevelArgs &a, int64_t first, i
         if (e < 0) (e == RG_NBR_OUTSIDE ? S.outside : S.coarse) = 1;
     }
     __syncthreads();
+    // only split cells, which the restriction overwrites: nothing to do
+    if (!S.live && !S.coarse) return;
     // by lanes of the last wave, put down after the gather
     uint32_t m = 0;
     const int ms = tid - (NT - 64), mg = ms / 7, mk = ms - 7 * mg;

@@ -17,7 +17,7 @@ rg_status hydro_groups(const LevelArgs &a, const LevelTab &lv, const int32_t *fa
                        hipStream_t s);
 rg_status hydro_bricks(const rg_tree *t, const double *uold, double *unew, const int32_t *list, const LevelTab &lv,
                        const double *dt, double gamma, int form, double cfl, double *dt_next, int waves,
-                       hipStream_t s);
+                       bool skip_split, hipStream_t s);
 rg_status hydro_columns(const rg_tree *t, int level, const double *uold, double *unew, const double *dt, double gamma,
                         int form, double cfl, double *dt_next, int waves, hipStream_t s);
 }  // namespace rg
@@ -39,11 +39,13 @@ namespace rg {
 // all octs by the per-oct kernel.  Coarse ghost cells are read from ucoarse
 // (bricks have none).  The fluxes owed to coarse cells go to corr (30 doubles
 // per oct from the first oct above lmin): stored (corr_mode 0), stored as 0 +
-// flux (1) or added (2).
+// flux (1) or added (2).  skip_split: octs whose cells are all split may be
+// left out (a step's restriction writes those cells; about a tenth of the
+// octs above the base of a deep tree).
 rg_status hydro_tree_levels(const rg_tree *t, const rg_schedule *sc, int l0, int l1, const double *d_dt, double gamma,
                             const double *d_uold, const double *d_ucoarse, double *d_unew, double cfl,
                             double *d_dt_next, int form, const rg_tuning *tune, hipStream_t s, double *d_corr,
-                            int corr_mode, const double *d_ucoarse2)
+                            int corr_mode, const double *d_ucoarse2, bool skip_split)
 {
     RG_REQUIRE(t->ghost == RG_GHOST_INJECT || t->ghost == RG_GHOST_LINEAR, "bad ghost mode %d", t->ghost);
     RG_REQUIRE(!sc || sc->d_list, "schedule without a list");
@@ -56,6 +58,7 @@ rg_status hydro_tree_levels(const rg_tree *t, const rg_schedule *sc, int l0, int
     a.son = t->d_son_mask;
     a.corr = d_corr;
     a.corr_base = t->level_begin[t->lmin + 1];
+    a.skip_split = skip_split;
     a.corr_mode = corr_mode;
     a.ghost = t->ghost;
     a.ucoarse2 = d_ucoarse2;
@@ -105,7 +108,8 @@ rg_status hydro_tree_levels(const rg_tree *t, const rg_schedule *sc, int l0, int
     const int waves = tune ? tune->brick_waves : 0;
     if (columns >= 0)
         RG_TRY(hydro_columns(t, columns, d_uold, d_unew, d_dt, gamma, form, cfl, d_dt_next, waves, s));
-    RG_TRY(hydro_bricks(t, d_uold, d_unew, sc->d_list, bricks, d_dt, gamma, form, cfl, d_dt_next, waves, s));
+    RG_TRY(hydro_bricks(t, d_uold, d_unew, sc->d_list, bricks, d_dt, gamma, form, cfl, d_dt_next, waves,
+                        skip_split, s));
     RG_TRY(hydro_groups(a, groups, t->d_father_cell, form, tune, s));
     return hydro_octs(a, octs, form, tune, s);
 }
@@ -231,7 +235,7 @@ rg_status rg_hydro_step_scheduled(const rg_tree *t, const rg_schedule *sc, int l
     RG_REQUIRE(gamma > 1, "bad gamma");
     RG_REQUIRE(!d_dt_next || (cfl > 0 && aligned(d_dt_next, 8)), "bad cfl or misaligned dt_next");
     return hydro_tree_levels(t, sc, level, level, d_dt, gamma, d_uold, d_uold, d_unew, cfl, d_dt_next, form, tune,
-                            as_stream(stream), t->d_corr, 0, d_uold);
+                            as_stream(stream), t->d_corr, 0, d_uold, false);
 }
 
 }  // extern "C"

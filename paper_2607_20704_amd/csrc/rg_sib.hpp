@@ -117,6 +117,13 @@ __device__ __forceinline__ int side_slot(int ax, int hi)
     return nslot(ax == 0 ? d : 0, ax == 1 ? d : 0, ax == 2 ? d : 0);
 }
 
+// Workgroup size: FP64 without interpolated ghosts, whose five groups per
+// compute unit are LDS-bound, one stencil cell per thread; otherwise four
+// waves, one per SIMD, which the registers allow more of (clumps of levels
+// 7-11, one step: FP64 869 us at 320 threads, 882 at 256; mixed 663 and 579;
+// FP64 with interpolated ghosts 1108 and 979; 192 threads 937, 608, 1048).
+__host__ __device__ constexpr int sib_threads(bool fp64, bool ghost) { return fp64 && !ghost ? 320 : 256; }
+
 template <typename R> struct SibSmem {
     int32_t oct[8];             // by place in the group
     int32_t nb[8 * 27];
@@ -125,6 +132,7 @@ template <typename R> struct SibSmem {
     // along the two other axes (lower axis first)
     uint32_t sm[32];
     int32_t outside, coarse, split;   // some list entry outside the domain / a coarse cell; some son mask set
+    int32_t live;                     // some cell is a leaf, or split cells are wanted too
     // the primitives are dead once the face states exist
     union {
         R w[NV][kSibW];         // primitive variables of the stencil cells (planes, lds_get)
@@ -169,9 +177,15 @@ __device__ __forceinline__ void hydro_sib(const LevelArgs &a, const int32_t *__r
     // neighbour lists and son masks; the places of a consistent tree are a
     // permutation, and an inconsistent one still names octs of the group
     if (tid < 8) S.oct[tid] = static_cast<int32_t>(first) + tid;
-    if (tid == 0) S.outside = S.coarse = S.split = 0;
+    if (tid == 0) {
+        S.outside = S.coarse = S.split = 0;
+        S.live = !a.skip_split;
+    }
     __syncthreads();
-    if (tid < 8) S.oct[father[first + tid] & 7] = static_cast<int32_t>(first) + tid;
+    if (tid < 8) {
+        S.oct[father[first + tid] & 7] = static_cast<int32_t>(first) + tid;
+        if (a.skip_split && a.son[first + tid] != 0xffu) S.live = 1;
+    }
     __syncthreads();
     for (int it = tid; it < 8 * 27; it += NT) {
         const int g = it / 27, s = it - 27 * g;
@@ -180,6 +194,8 @@ __device__ __forceinline__ void hydro_sib(const LevelArgs &a, const int32_t *__r
         if (e < 0) (e == RG_NBR_OUTSIDE ? S.outside : S.coarse) = 1;
     }
     __syncthreads();
+    // only split cells, which the restriction overwrites: nothing to do
+    if (!S.live && !S.coarse) return;
     // son masks, by lanes of the last wave, put down after the gather
     uint32_t m = 0;
     const int ms = tid - (NT - 64);

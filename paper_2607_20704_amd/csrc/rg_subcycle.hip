@@ -24,7 +24,7 @@ namespace rg {
 rg_status hydro_tree_levels(const rg_tree *t, const rg_schedule *sc, int l0, int l1, const double *d_dt, double gamma,
                             const double *d_uold, const double *d_ucoarse, double *d_unew, double cfl,
                             double *d_dt_next, int form, const rg_tuning *tune, hipStream_t s, double *d_corr,
-                            int corr_mode, const double *d_ucoarse2);
+                            int corr_mode, const double *d_ucoarse2, bool skip_split);
 rg_status restrict_level2(const double *src, double *dst, const int32_t *father, int64_t ob, int64_t oe,
                           hipStream_t s);
 rg_status tree_corrections(const rg_tree *t, double *unew, const double *corr, const int32_t *list, int64_t ob,
@@ -65,7 +65,7 @@ rg_status advance(Sub &c, int l, int sub)
     const double *coarse2 = l > t->lmin + 1 ? c.buf[c.cur[l - 2]] : coarse;
     if (oe > ob)
         RG_TRY(hydro_tree_levels(t, t->sched, l, l, c.dt + 1 + (l - t->lmin), c.gamma, own, coarse, out, 0.0, nullptr,
-                                 c.form, c.tune, c.s, c.acc, 1 + sub, coarse2));
+                                 c.form, c.tune, c.s, c.acc, 1 + sub, coarse2, true));
     if (l < t->lmax) {
         const int64_t fb = t->level_begin[l + 1], fe = t->level_begin[l + 2];
         for (int s2 = 0; s2 < 2; ++s2) RG_TRY(advance(c, l + 1, s2));
