@@ -330,7 +330,7 @@ __global__ __launch_bounds__(kT) void k_batch_nbr(const BTree *__restrict__ tree
                                                    int64_t nitems)
 {
     __shared__ union {
-        NbrGroup grp;
+        NbrChunk chunk;
         NbrBrick brick;
     } S;
     const ItemRange r = xcd_items(nitems);
@@ -338,11 +338,11 @@ __global__ __launch_bounds__(kT) void k_batch_nbr(const BTree *__restrict__ tree
         const Item I = items[it];
         const BTree &T = trees[I.tree];
         const NbrTable tab{T.keys, T.hdr, T.hkeys, T.hvals, T.hmask, T.nbr27, T.father, T.son, T.lmin, T.bc,
-                           RG_MAX_LEVEL + 1};
+                           RG_MAX_LEVEL + 1, T.n_oct};
         if (I.a == 0)
             nbr_brick_body(tab, T.list[I.first], S.brick);
         else
-            nbr_octs_body(tab, T.list, I.first, static_cast<int>(I.count), S.grp);
+            nbr_octs_body(tab, T.list, I.first, static_cast<int>(I.count), S.chunk);
         __syncthreads();
     }
 }
@@ -549,7 +549,7 @@ rg_status rg_batch_create(const rg_batch_tree *trees, int ntree, int form, int n
         chunk(it_clear, t, 1, 0, T->n_oct, 65536);
         chunk(it_insert, t, 0, 0, T->n_oct, 4096);
         for (int64_t k = 0; k < sc->nbr_brick_count; ++k) it_nbr.push_back(Item{t, 0, sc->nbr_brick_begin + k, 1});
-        chunk(it_nbr, t, 1, sc->nbr_rest_begin, sc->nbr_rest_count, kNbrOcts);
+        chunk(it_nbr, t, 1, sc->nbr_rest_begin, sc->nbr_rest_count, kNbrChunk);
     }
     it_restrict.resize(maxdepth);
     for (int k = 0; k < maxdepth; ++k)

@@ -12,8 +12,20 @@
 namespace rg {
 namespace {
 
-// Per-oct build: 27 threads per oct (one per offset), 9 octs per workgroup.
+// Octs outside the bricks, one by one: 27 threads per oct (one per offset), 9
+// octs per workgroup.
 constexpr int kNbrOcts = 9;
+
+// By sibling groups: this many list entries per workgroup of four waves, so
+// that a wave serves at most one group.
+constexpr int kNbrChunk = 32;
+
+// Lists longer than this go by sibling groups.  Both ways cost a launch of
+// latency where the list is short (0.03 M octs of a three-level tree: 13 us
+// one by one, whose chain of loads is the shorter one, 21 us by groups); long
+// lists pay per lookup (0.41 M octs outside the bricks of the clumps of levels
+// 7-11: 262 us one by one, 166 us by groups).
+constexpr int64_t kNbrByGroups = 40000;
 
 struct NbrTable {
     const uint64_t *okeys;     // the tree's sorted keys
@@ -28,16 +40,52 @@ struct NbrTable {
     // octs on this level have no children: their son masks are written as
     // 0 here rather than cleared beforehand (RG_MAX_LEVEL + 1: none are)
     int lmax_zero;
+    int64_t n;                 // the tree's octs
 };
 
-struct NbrGroup {
+// Key of the oct at (ni, nj, nk) of level l, wrapped as bc says; 0 (no key)
+// outside the domain.
+__device__ __forceinline__ uint64_t nbr_key(const NbrTable &T, int32_t &ni, int32_t &nj, int32_t &nk, int l)
+{
+    const int32_t N = 1 << (l - 1);
+    if (T.bc == RG_BC_PERIODIC) {
+        ni &= N - 1;
+        nj &= N - 1;
+        nk &= N - 1;
+    } else if (ni < 0 || nj < 0 || nk < 0 || ni >= N || nj >= N || nk >= N) {
+        return 0;
+    }
+    return oct_key(ni, nj, nk, l);
+}
+
+__device__ __forceinline__ int32_t nbr_find(const NbrTable &T, uint64_t key)
+{
+    return key ? hash_probe(T.keys, T.vals, T.mask, key) : -1;
+}
+
+// entry of the oct with key kn at (ni, nj, nk), found at e (or not: -1): the
+// oct, else the coarse cell under it; `own` is reported if there is neither
+__device__ __forceinline__ int32_t nbr_entry(const NbrTable &T, int32_t e, uint64_t kn, int32_t ni, int32_t nj,
+                                             int32_t nk, int l, int64_t own)
+{
+    if (kn == 0) return RG_NBR_OUTSIDE;
+    if (e >= 0) return e;
+    const int32_t f = (l > 1) ? hash_probe(T.keys, T.vals, T.mask, kn >> 3) : -1;
+    if (f < 0) {
+        flag_error(T.hdr, RG_EUNGRADED, own);
+        return 0;
+    }
+    return -1 - (8 * f + (ni & 1) + 2 * (nj & 1) + 4 * (nk & 1));
+}
+
+struct NbrOcts {
     int32_t c[kNbrOcts][4];
     int64_t o[kNbrOcts];
 };
 
 // octs list[first .. first+count) (or first .. first+count without a list)
-__device__ __forceinline__ void nbr_octs_body(const NbrTable &T, const int32_t *__restrict__ list, int64_t first,
-                                              int count, NbrGroup &grp)
+__device__ __forceinline__ void nbr_each_body(const NbrTable &T, const int32_t *__restrict__ list, int64_t first,
+                                              int count, NbrOcts &grp)
 {
     const int t = threadIdx.x;
     if (t < kNbrOcts && t < count) {
@@ -101,6 +149,138 @@ __device__ __forceinline__ void nbr_octs_body(const NbrTable &T, const int32_t *
                 T.nbr27[27 * o + slot] = e;
             }
         }
+    }
+}
+
+struct NbrChunk {
+    uint64_t lead_key[kNbrChunk], loose_key[kNbrChunk];
+    int32_t lead[kNbrChunk], loose[kNbrChunk];   // first octs of complete sibling groups; other octs
+    int32_t nlead, nloose;
+    int32_t slot[4][64];                 // per wave: the 4^3 octs around a group
+    int32_t place[4][8];                 // slot of the group's m-th oct
+};
+
+// Octs list[first .. first + count) (or first .. first + count without a
+// list).  The eight octs of a complete sibling group share a neighbourhood of
+// 4^3 octs, 56 of them outside the group: one wave looks these up, one per
+// lane, and expands the eight lists from them, where octs one at a time probe
+// the table 8 x 26 times.  A group's father has eight children, so its son
+// mask is stored whole.  A group that straddles two chunks belongs to the one
+// holding its first oct.  Other octs take half a wave each.
+__device__ __forceinline__ void nbr_octs_body(const NbrTable &T, const int32_t *__restrict__ list, int64_t first,
+                                              int count, NbrChunk &S)
+{
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    if (t < 64) {
+        bool lead = false, loose = false;
+        int64_t o = 0;
+        uint64_t k = 0;
+        if (t < count) {
+            o = list ? int64_t(list[first + t]) : first + t;
+            // the key a group's last oct would have, read beside its first one's
+            const uint64_t k7 = o + 7 < T.n ? T.okeys[o + 7] : 0;
+            k = T.okeys[o];
+            lead = k >= 8 && (k & 7) == 0 && k7 == k + 7;
+        }
+        // the other octs of a group follow its first one in the list, unless
+        // the chunk begins between them
+        const int r = static_cast<int>(k & 7), at = t - r < 0 ? 0 : t - r;
+        const bool same = __shfl(static_cast<int>(lead), at, 64) && __shfl(static_cast<int>(o), at, 64) == o - r;
+        if (t < count) {
+            bool whole = same;
+            if (t < r) {
+                const int64_t f = o - r;
+                whole = k >= 8 && f >= 0 && f + 7 < T.n && T.okeys[f] == k - uint64_t(r) &&
+                        T.okeys[f + 7] == k - uint64_t(r) + 7;
+            }
+            loose = !whole;
+        }
+        const uint64_t ml = __ballot(lead), mo = __ballot(loose), below = (uint64_t(1) << t) - 1;
+        if (lead) {
+            S.lead[__popcll(ml & below)] = static_cast<int32_t>(o);
+            S.lead_key[__popcll(ml & below)] = k;
+        }
+        if (loose) {
+            S.loose[__popcll(mo & below)] = static_cast<int32_t>(o);
+            S.loose_key[__popcll(mo & below)] = k;
+        }
+        if (t == 0) {
+            S.nlead = __popcll(ml);
+            S.nloose = __popcll(mo);
+        }
+    }
+    __syncthreads();
+    for (int g = wave; g < S.nlead; g += 4) {
+        const int64_t f = S.lead[g];
+        const uint64_t kf = S.lead_key[g];
+        int32_t i, j, k, l;
+        key_coords(kf >> 3, i, j, k, l);   // the father's; the group starts at twice them
+        ++l;
+        const int x = (lane & 3) - 1, y = ((lane >> 2) & 3) - 1, z = (lane >> 4) - 1;
+        const bool own = x >= 0 && x < 2 && y >= 0 && y < 2 && z >= 0 && z < 2;
+        int32_t ni = 2 * i + x, nj = 2 * j + y, nk = 2 * k + z;
+        const uint64_t kn = nbr_key(T, ni, nj, nk, l);
+        // the first oct's lane looks up the father while the lanes outside the
+        // group look up their octs
+        const int m = static_cast<int>(kn & 7);
+        const bool lead = own && m == 0;
+        int32_t e = nbr_find(T, own ? (lead && l > T.lmin ? kf >> 3 : 0) : kn);
+        const int32_t fo = __shfl(e, __ffsll(static_cast<unsigned long long>(__ballot(lead))) - 1, 64);
+        if (own) {
+            S.place[wave][m] = lane;
+            e = static_cast<int32_t>(f) + m;
+        } else {
+            e = nbr_entry(T, e, kn, ni, nj, nk, l, f);
+        }
+        S.slot[wave][lane] = e;
+        // one wave's LDS operations are done in order
+        __threadfence_block();
+        __builtin_amdgcn_wave_barrier();
+        for (int q = lane; q < 8 * 27; q += 64) {
+            const int m = q / 27, s = q - 27 * m;
+            const int sx = s % 3 - 1, sy = (s / 3) % 3 - 1, sz = s / 9 - 1;
+            T.nbr27[27 * f + q] = S.slot[wave][S.place[wave][m] + sx + 4 * sy + 16 * sz];
+        }
+        if (lane < 8) {
+            const int p = S.place[wave][lane];   // x, y, z of the place are 1 or 2
+            const int bit = (~p & 1) + 2 * (~(p >> 2) & 1) + 4 * (~(p >> 4) & 1);
+            T.father_cell[f + lane] = fo < 0 ? -1 : 8 * fo + bit;
+            if (l == T.lmax_zero) T.son_mask[f + lane] = 0u;
+        }
+        if (lane == 0 && l > T.lmin) {
+            if (fo < 0) flag_error(T.hdr, RG_EUNGRADED, f);
+            else T.son_mask[fo] = 0xffu;
+        }
+        __threadfence_block();
+        __builtin_amdgcn_wave_barrier();
+    }
+    const int half = t >> 5, slot = t & 31;
+    for (int g = half; g < S.nloose; g += 8) {
+        if (slot >= 27) continue;
+        const int64_t o = S.loose[g];
+        int32_t i, j, k, l;
+        const uint64_t key = S.loose_key[g];
+        key_coords(key, i, j, k, l);
+        int32_t ni = i + slot % 3 - 1, nj = j + (slot / 3) % 3 - 1, nk = k + slot / 9 - 1;
+        const uint64_t kn = nbr_key(T, ni, nj, nk, l);
+        const int32_t e = nbr_find(T, slot != 13 ? kn : (l > T.lmin ? key >> 3 : 0));
+        if (slot != 13) {
+            T.nbr27[27 * o + slot] = nbr_entry(T, e, kn, ni, nj, nk, l, o);
+            continue;
+        }
+        T.nbr27[27 * o + 13] = static_cast<int32_t>(o);
+        if (l == T.lmax_zero) T.son_mask[o] = 0u;
+        int32_t cell = -1;
+        if (l > T.lmin) {
+            if (e < 0) {
+                flag_error(T.hdr, RG_EUNGRADED, o);
+            } else {
+                const int bit = (i & 1) + 2 * (j & 1) + 4 * (k & 1);
+                cell = 8 * e + bit;
+                atomicOr(T.son_mask + e, 1u << bit);
+            }
+        }
+        T.father_cell[o] = cell;
     }
 }
 

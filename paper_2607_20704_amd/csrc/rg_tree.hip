@@ -422,16 +422,47 @@ __global__ void k_hash_lookup(const uint64_t *__restrict__ keys, const int32_t *
 
 // `list` (optional) maps positions 0..n-1 to oct indices
 __global__ __launch_bounds__(256) void k_neighbours(const uint64_t *__restrict__ okeys, const int32_t *__restrict__ list,
-                                                    int64_t n, int lmin, int bc, int lmax_zero, HashHeader *hdr,
-                                                    const uint64_t *__restrict__ keys, const int32_t *__restrict__ vals,
-                                                    uint64_t mask, int32_t *__restrict__ nbr27,
-                                                    int32_t *__restrict__ father_cell, uint32_t *__restrict__ son_mask)
+                                                    int64_t n, int64_t n_oct, int lmin, int bc, int lmax_zero,
+                                                    HashHeader *hdr, const uint64_t *__restrict__ keys,
+                                                    const int32_t *__restrict__ vals, uint64_t mask,
+                                                    int32_t *__restrict__ nbr27, int32_t *__restrict__ father_cell,
+                                                    uint32_t *__restrict__ son_mask)
 {
-    __shared__ NbrGroup grp;
+    __shared__ NbrOcts S;
     const int64_t first = int64_t(blockIdx.x) * kNbrOcts;
     const int64_t left = n - first;
-    const NbrTable tab{okeys, hdr, keys, vals, mask, nbr27, father_cell, son_mask, lmin, bc, lmax_zero};
-    nbr_octs_body(tab, list, first, left < kNbrOcts ? static_cast<int>(left) : kNbrOcts, grp);
+    const NbrTable tab{okeys, hdr, keys, vals, mask, nbr27, father_cell, son_mask, lmin, bc, lmax_zero, n_oct};
+    nbr_each_body(tab, list, first, left < kNbrOcts ? static_cast<int>(left) : kNbrOcts, S);
+}
+
+__global__ __launch_bounds__(256) void k_neighbours_groups(const uint64_t *__restrict__ okeys, const int32_t *__restrict__ list,
+                                                    int64_t n, int64_t n_oct, int lmin, int bc, int lmax_zero,
+                                                    HashHeader *hdr, const uint64_t *__restrict__ keys,
+                                                    const int32_t *__restrict__ vals, uint64_t mask,
+                                                    int32_t *__restrict__ nbr27, int32_t *__restrict__ father_cell,
+                                                    uint32_t *__restrict__ son_mask)
+{
+    __shared__ NbrChunk S;
+    const int64_t first = int64_t(blockIdx.x) * kNbrChunk;
+    const int64_t left = n - first;
+    const NbrTable tab{okeys, hdr, keys, vals, mask, nbr27, father_cell, son_mask, lmin, bc, lmax_zero, n_oct};
+    nbr_octs_body(tab, list, first, left < kNbrChunk ? static_cast<int>(left) : kNbrChunk, S);
+}
+
+rg_status launch_neighbours(const uint64_t *d_keys, const int32_t *list, int64_t n, int64_t n_oct, int lmin, int bc,
+                            int lmax_zero, const HashView &h, int32_t *d_nbr27, int32_t *d_father_cell,
+                            uint32_t *d_son_mask, hipStream_t s)
+{
+    const bool groups = n > kNbrByGroups;
+    const int chunk = groups ? kNbrChunk : kNbrOcts;
+    const unsigned blocks = static_cast<unsigned>((n + chunk - 1) / chunk);
+    if (groups)
+        k_neighbours_groups<<<blocks, 256, 0, s>>>(d_keys, list, n, n_oct, lmin, bc, lmax_zero, h.hdr, h.keys, h.vals,
+                                                   h.mask, d_nbr27, d_father_cell, d_son_mask);
+    else
+        k_neighbours<<<blocks, 256, 0, s>>>(d_keys, list, n, n_oct, lmin, bc, lmax_zero, h.hdr, h.keys, h.vals,
+                                            h.mask, d_nbr27, d_father_cell, d_son_mask);
+    return launch_status("neighbours");
 }
 
 __global__ __launch_bounds__(256) void k_neighbours_brick(const uint64_t *__restrict__ okeys,
@@ -447,7 +478,7 @@ __global__ __launch_bounds__(256) void k_neighbours_brick(const uint64_t *__rest
     const int64_t per_xcd = (nbricks + 7) / 8;
     const int64_t b = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
     if (b >= nbricks) return;
-    const NbrTable tab{okeys, hdr, keys, vals, mask, nbr27, father_cell, son_mask, lmin, bc, lmax_zero};
+    const NbrTable tab{okeys, hdr, keys, vals, mask, nbr27, father_cell, son_mask, lmin, bc, lmax_zero, 0};
     nbr_brick_body(tab, bricks[b], nb);
 }
 
@@ -471,11 +502,7 @@ rg_status neighbours_scheduled(void *d_ws, const uint64_t *d_keys, int64_t n, in
         RG_TRY(launch_status("brick neighbours"));
     }
     if (nrest > 0) {
-        const int64_t blocks = (nrest + kNbrOcts - 1) / kNbrOcts;
-        k_neighbours<<<static_cast<unsigned>(blocks), 256, 0, s>>>(d_keys, rest, nrest, lmin, bc, lmax, h.hdr,
-                                                                   h.keys, h.vals, h.mask, d_nbr27, d_father_cell,
-                                                                   d_son_mask);
-        RG_TRY(launch_status("neighbours"));
+        RG_TRY(launch_neighbours(d_keys, rest, nrest, n, lmin, bc, lmax, h, d_nbr27, d_father_cell, d_son_mask, s));
     }
     return RG_OK;
 }
@@ -760,11 +787,8 @@ rg_status rg_build_neighbours(void *d_ws, const uint64_t *d_keys, int64_t n, int
     HashView h = hash_view(d_ws, cap);
     hipStream_t s = as_stream(stream);
     RG_TRY(fill_u32(d_son_mask, n, 0u, s));
-    const int64_t blocks = (n + kNbrOcts - 1) / kNbrOcts;
-    k_neighbours<<<static_cast<unsigned>(blocks), 256, 0, s>>>(d_keys, nullptr, n, lmin, bc, RG_MAX_LEVEL + 1, h.hdr,
-                                                               h.keys, h.vals,
-                                                               h.mask, d_nbr27, d_father_cell, d_son_mask);
-    return launch_status("rg_build_neighbours");
+    return launch_neighbours(d_keys, nullptr, n, n, lmin, bc, RG_MAX_LEVEL + 1, h, d_nbr27, d_father_cell, d_son_mask,
+                             s);
 }
 
 }  // extern "C"

@@ -1,0 +1,82 @@
+"""The rebuild of a tree on the device at the sizes where its pieces meet,
+bit for bit against the oracle: neighbour lists of short lists (octs one by
+one) and, in a batch and in long lists, by sibling groups."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import say
+from oracle import oracle as O
+from paper_2607_20704_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def _holed(base, lmax, bc, seed):
+    """A graded tree whose finest level lacks about a third of its octs: groups
+    of one to eight octs, complete ones at every offset of a 64-entry chunk."""
+    ijkl = I.sphere_tree(base, lmax, (0.3, 0.45, 0.6), 0.2, bc)
+    drop = (ijkl[:, 3] == lmax) & (np.random.default_rng(seed).random(len(ijkl)) < 0.06)
+    return np.ascontiguousarray(ijkl[~drop])
+
+
+TREES = [
+    ("one_oct", lambda: I.uniform_tree(1), I.PERIODIC),
+    ("two_per_side_periodic", lambda: I.uniform_tree(2), I.PERIODIC),
+    ("two_per_side_walls", lambda: I.uniform_tree(2), I.OUTFLOW),
+    ("levels_1_3", lambda: np.concatenate([I.uniform_tree(1), I.uniform_tree(2), I.uniform_tree(3)]), I.PERIODIC),
+    ("levels_2_4_walls", lambda: np.concatenate([I.uniform_tree(l) for l in (2, 3, 4)]), I.OUTFLOW),
+    ("holes_3_5", lambda: _holed(3, 5, I.PERIODIC, 5), I.PERIODIC),
+    ("holes_3_6_walls", lambda: _holed(3, 6, I.OUTFLOW, 6), I.OUTFLOW),
+    ("holes_4_8", lambda: _holed(4, 8, I.PERIODIC, 7), I.PERIODIC),   # > 40000 octs outside bricks
+]
+
+
+def _tree(name):
+    mk, bc = next((t[1], t[2]) for t in TREES if t[0] == name)
+    return np.ascontiguousarray(mk(), dtype=np.int32), bc
+
+
+def _check_lists(D, T):
+    from paper_2607_20704_amd import api
+    assert api.check_ws(D.hash_ws)[0] == 0
+    assert np.array_equal(D.nbr27.cpu().numpy(), T.nbr27)
+    assert np.array_equal(D.father_cell.cpu().numpy(), T.father_cell)
+    assert np.array_equal(D.son_mask.cpu().numpy(), T.son_mask.astype(np.int32))
+
+
+@pytest.mark.parametrize("schedule", [False, True])
+@pytest.mark.parametrize("name", [t[0] for t in TREES])
+def test_neighbour_lists(name, schedule):
+    from paper_2607_20704_amd import api
+    ijkl, bc = _tree(name)
+    T = O.Tree(ijkl, bc)
+    D = api.DeviceTree(ijkl, bc, schedule=schedule)
+    say("neighbours:", name, len(ijkl), "outside bricks", D.sched.nbr_rest_count if schedule else D.n)
+    for again in (False, True):
+        if again:
+            for x in (D.nbr27, D.father_cell, D.son_mask):
+                x.fill_(-7)
+            D.prepare()
+        _check_lists(D, T)
+
+
+def test_neighbour_lists_of_a_batch():
+    from paper_2607_20704_amd import api
+    trees = [_tree(t[0]) for t in TREES]
+    D = [api.DeviceTree(*t) for t in trees]
+    u = []
+    for d in D:
+        x = torch.ones((8 * d.n, 5), dtype=torch.float64, device="cuda")
+        x[:, 4] = 2.5
+        u.append(x)
+    B = api.Batch(D, u, [1.4] * len(D), [0.8] * len(D), 1, rebuild=True)
+    for d in D:
+        for x in (d.nbr27, d.father_cell, d.son_mask):
+            x.fill_(-7)
+    B.run()
+    torch.cuda.synchronize()
+    for d, t in zip(D, trees):
+        say("batch:", len(t[0]))
+        _check_lists(d, O.Tree(*t))
+    B.close()
