@@ -510,8 +510,8 @@ rg_status rg_refine_flags(const rg_tree *t, const double *d_u, const rg_refine_p
  *   new state in d_u_new (key order of the new tree): kept octs copy their
  *   cells, a new oct's 8 cells take its father cell's values (injection, so
  *   leaf sums of volume * U are unchanged);
- *   keys, one radix sort, level ranges, hash table and neighbour lists of the
- *   new tree, written into t's buffers; t->n_oct, t->lmax and
+ *   keys, level ranges, hash table and neighbour lists of the new tree, in key
+ *   order, written into t's buffers; t->n_oct, t->lmax and
  *   t->level_begin are updated and t->sched is set to NULL (rebuild a
  *   schedule with rg_schedule_build if wanted).
  * Every per-oct buffer of t (keys, scratch keys, permutation, coordinates,
@@ -520,7 +520,7 @@ rg_status rg_refine_flags(const rg_tree *t, const double *d_u, const rg_refine_p
  * RG_EFULL, with t unchanged, if the new tree would not fit.  d_u and
  * d_u_new are 8 x capacity x 5 doubles and must not alias; d_ws is
  * rg_refine_workspace_bytes(capacity) bytes, 256-byte aligned.  Synchronises
- * `stream` twice (the new oct count and the level ranges are read back). */
+ * `stream` once (the new level ranges are read back). */
 rg_status rg_refine(rg_tree *t, const double *d_u, double *d_u_new, const rg_refine_params *p, void *d_ws,
                     size_t ws_bytes, void *stream);
 

@@ -453,10 +453,13 @@ __device__ __forceinline__ int tab_entry(const LevelTab &t, int &i)
 
 rg_status fill_u32(uint32_t *d, int64_t n, uint32_t v, hipStream_t s);
 // lmax: the tree's finest level; n_below_lmax: the octs before it (the ones
-// whose son masks are cleared first).
+// whose son masks are cleared first).  d_counts (device): the numbers of
+// bricks and other octs, whose list follows the bricks'; nbricks and nrest are
+// then upper bounds and rest is the bricks' list.
 rg_status neighbours_scheduled(void *d_ws, const uint64_t *d_keys, int64_t n, int lmin, int lmax, int64_t n_below_lmax,
                                int bc, const int32_t *bricks, int64_t nbricks, const int32_t *rest, int64_t nrest,
-                               int32_t *d_nbr27, int32_t *d_father_cell, uint32_t *d_son_mask, hipStream_t s);
+                               int32_t *d_nbr27, int32_t *d_father_cell, uint32_t *d_son_mask, hipStream_t s,
+                               const uint32_t *d_counts = nullptr);
 rg_status sort_keys_bits(const uint64_t *d_keys_in, int64_t n, uint64_t *d_keys_out, int32_t *d_perm, void *d_ws,
                          size_t ws_bytes, int end_bit, hipStream_t s);
 rg_status fill_u64(uint64_t *d, int64_t n, uint64_t v, hipStream_t s);

@@ -2,29 +2,30 @@
 //
 // Paper Sec. 2.2: every step the tree changes in four stages: new octs under
 // flagged cells, removal of the children of split cells that are no longer
-// flagged, a bucket sort by level and a Hilbert sort inside each level (one
-// radix sort of the level-major Hilbert keys here).  The paper does not give
-// the criterion or the grading rule; the ones used (density threshold or
-// density jump across a face; a flagged cell needs its 26 neighbours at its
-// own level, which flags the coarser cells under them, finest level first)
-// are restated in the header next to rg_refine.
+// flagged, a bucket sort by level and a Hilbert sort inside each level.  No
+// sort is needed here: the new tree's octs of a level are the children of the
+// old tree's octs of the level above (every flagged cell has one), in those
+// octs' order and along the curve inside each, so a prefix over the old octs
+// of the number of flagged cells gives every new oct its place.  The paper
+// does not give the criterion or the grading rule; the ones used (density
+// threshold or density jump across a face; a flagged cell needs its 26
+// neighbours at its own level, which flags the coarser cells under them,
+// finest level first) are restated in the header next to rg_refine.
 //
 // Everything runs on the device with the tree's own neighbour lists: the
 // criterion reads the six face neighbours through the 27-entry list, the
 // closure marks father cells through it (a missing neighbour oct's entry is
-// already the coarse cell under it), and the new oct list comes from a scan
-// over per-oct counts.  The host reads back two numbers (the new oct count
-// and the level ranges).
-#include <hipcub/hipcub.hpp>
-
+// already the coarse cell under it), and the new oct list comes from a prefix
+// over per-oct counts, whose values at the old level boundaries are the new
+// level ranges: the one thing the host reads back.
+#include "rg_compact.hpp"
 #include "rg_internal.hpp"
 
 namespace rg {
 
 size_t nbr_lists_ws_bytes(int64_t n);
 rg_status nbr_lists_device(const uint64_t *d_keys, int64_t n, const int64_t *h_level_begin, int lmin, int lmax,
-                           void *d_ws, size_t ws_bytes, const int32_t **list, int64_t *nbricks, int64_t *nrest,
-                           hipStream_t s);
+                           void *d_ws, size_t ws_bytes, const int32_t **list, const uint32_t **d_count, hipStream_t s);
 
 namespace {
 
@@ -95,38 +96,36 @@ __global__ void k_zero_u32(uint32_t *p, int64_t n)
     if (i < n) p[i] = 0;
 }
 
-// one thread per oct of one level: a flagged cell marks the father cell of
-// every level-l oct holding one of its 26 neighbours or itself.  A cell with
-// in-oct position c reaches, along each axis, its own oct and the neighbour
-// oct on its side (offset -1 for c = 0, +1 for c = 1), so the oct's flagged
-// cells need at most 27 neighbour octs; each target bit is set by an atomic
-// only if a plain read does not already show it (many octs mark the same
-// coarse cells).
+// 32 lanes per oct of one level (27 used): a flagged cell marks the father
+// cell of every level-l oct holding one of its 26 neighbours or itself.  A
+// cell with in-oct position c reaches, along each axis, its own oct and the
+// neighbour oct on its side (offset -1 for c = 0, +1 for c = 1): the oct's
+// list entry at offset d is needed if a flagged cell lies on d's side along
+// every axis where d is not zero.  Each lane takes one entry, so that an oct
+// costs one chain of loads (one thread per oct went through up to 27 of them:
+// 25 us a level); each target bit is set by an atomic only if a plain read
+// does not already show it (many octs mark the same coarse cells).
 __global__ void k_refine_closure(const int32_t *__restrict__ nbr27, const int32_t *__restrict__ father,
                                  int64_t ob, int64_t oe, uint32_t *flags, int whole)
 {
-    const int64_t o = ob + int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (o >= oe) return;
+    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t o = ob + (t >> 5);
+    const int slot = static_cast<int>(t & 31);
+    if (o >= oe || slot >= 27) return;
     const uint32_t m = flags[o] & 0xffu;
     if (!m) return;
-    uint32_t need = 0;   // bit (sx+1) + 3(sy+1) + 9(sz+1): neighbour oct offsets needed
-    for (int c = 0; c < 8; ++c) {
-        if (!((m >> c) & 1u)) continue;
-        const int ox = (c & 1) ? 1 : -1, oy = ((c >> 1) & 1) ? 1 : -1, oz = (c >> 2) ? 1 : -1;
-        for (int b = 0; b < 8; ++b) {
-            const int sx = (b & 1) ? ox : 0, sy = ((b >> 1) & 1) ? oy : 0, sz = (b >> 2) ? oz : 0;
-            need |= 1u << ((sx + 1) + 3 * (sy + 1) + 9 * (sz + 1));
-        }
-    }
-    for (int slot = 0; slot < 27; ++slot) {
-        if (!((need >> slot) & 1u)) continue;
-        const int32_t e = nbr27[27 * o + slot];
-        if (e == RG_NBR_OUTSIDE) continue;
-        const int64_t fc = e >= 0 ? int64_t(father[e]) : (-1 - int64_t(e));
-        if (fc < 0) continue;   // coarsest level: nothing to mark
-        const uint32_t bit = whole ? 0xffu : 1u << (fc & 7);
-        if ((flags[fc >> 3] & bit) != bit) atomicOr(&flags[fc >> 3], bit);
-    }
+    const int s[3] = {slot % 3 - 1, (slot / 3) % 3 - 1, slot / 9 - 1};
+    constexpr uint32_t high[3] = {0xaau, 0xccu, 0xf0u};   // cells on the high side of each axis
+    uint32_t reach = 0xffu;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) reach &= s[a] > 0 ? high[a] : (s[a] < 0 ? ~high[a] : 0xffu);
+    if (!(m & reach)) return;
+    const int32_t e = nbr27[27 * o + slot];
+    if (e == RG_NBR_OUTSIDE) return;
+    const int64_t fc = e >= 0 ? int64_t(father[e]) : (-1 - int64_t(e));
+    if (fc < 0) return;   // coarsest level: nothing to mark
+    const uint32_t bit = whole ? 0xffu : 1u << (fc & 7);
+    if ((flags[fc >> 3] & bit) != bit) atomicOr(&flags[fc >> 3], bit);
 }
 
 __device__ __forceinline__ bool kept(const uint32_t *flags, const int32_t *father, int64_t o, bool coarsest)
@@ -136,95 +135,208 @@ __device__ __forceinline__ bool kept(const uint32_t *flags, const int32_t *fathe
     return f >= 0 && ((flags[f >> 3] >> (f & 7)) & 1u);
 }
 
-// per oct: 1 if kept, plus one per flagged leaf cell (its new child)
-__global__ void k_refine_count(const uint32_t *__restrict__ flags, const int32_t *__restrict__ father,
-                               const uint32_t *__restrict__ son, int64_t n, int64_t coarse_end, int32_t *cnt)
+// children of old oct o in the new tree
+__device__ __forceinline__ uint32_t children(const uint32_t *flags, const int32_t *father, int64_t o, int64_t coarse_end)
 {
-    const int64_t o = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (o >= n) return;
-    const bool k = kept(flags, father, o, o < coarse_end);
-    cnt[o] = k ? 1 + __popc(flags[o] & ~son[o] & 0xffu) : 0;
+    return kept(flags, father, o, o < coarse_end) ? static_cast<uint32_t>(__popc(flags[o] & 0xffu)) : 0u;
 }
 
-__global__ void k_refine_emit(const uint32_t *__restrict__ flags, const int32_t *__restrict__ father,
-                              const uint32_t *__restrict__ son, const int32_t *__restrict__ ijkl, int64_t n,
-                              int64_t coarse_end, const int32_t *__restrict__ off, int32_t *new_ijkl, int32_t *src)
+__global__ __launch_bounds__(kItems) void k_refine_count(const uint32_t *__restrict__ flags,
+                                                         const int32_t *__restrict__ father, int64_t n,
+                                                         int64_t coarse_end, uint32_t *__restrict__ cnt)
 {
-    const int64_t o = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (o >= n) return;
-    if (!kept(flags, father, o, o < coarse_end)) return;
-    int64_t m = off[o];
-    const int32_t i = ijkl[4 * o], j = ijkl[4 * o + 1], k = ijkl[4 * o + 2], l = ijkl[4 * o + 3];
-    new_ijkl[4 * m] = i;
-    new_ijkl[4 * m + 1] = j;
-    new_ijkl[4 * m + 2] = k;
-    new_ijkl[4 * m + 3] = l;
-    src[m] = static_cast<int32_t>(o);
-    ++m;
-    const uint32_t fresh = flags[o] & ~son[o] & 0xffu;
-    for (int c = 0; c < 8; ++c) {
-        if (!((fresh >> c) & 1u)) continue;
-        new_ijkl[4 * m] = 2 * i + (c & 1);
-        new_ijkl[4 * m + 1] = 2 * j + ((c >> 1) & 1);
-        new_ijkl[4 * m + 2] = 2 * k + (c >> 2);
-        new_ijkl[4 * m + 3] = l + 1;
-        src[m] = static_cast<int32_t>(-1 - (8 * o + c));
-        ++m;
+    __shared__ uint32_t s[kItems / 64];
+    const int64_t o = int64_t(blockIdx.x) * kItems + threadIdx.x;
+    uint32_t total;
+    (void)block_prefix(o < n ? children(flags, father, o, coarse_end) : 0u, s, total);
+    if (threadIdx.x == 0) cnt[blockIdx.x] = total;
+}
+
+// off[o]: children of the octs before o; bound[j]: of those before marks.at[j]
+__global__ __launch_bounds__(kItems) void k_refine_offsets(const uint32_t *__restrict__ flags,
+                                                           const int32_t *__restrict__ father, int64_t n,
+                                                           int64_t coarse_end, const uint32_t *__restrict__ cnt,
+                                                           const uint32_t *__restrict__ all, Marks marks,
+                                                           uint32_t *__restrict__ off, int64_t *__restrict__ bound)
+{
+    __shared__ uint32_t s[kItems / 64];
+    const int64_t o = int64_t(blockIdx.x) * kItems + threadIdx.x;
+    uint32_t total;
+    const uint32_t first = cnt[blockIdx.x];
+    const uint32_t p = block_prefix(o < n ? children(flags, father, o, coarse_end) : 0u, s, total);
+    __shared__ uint32_t before[kItems];
+    before[threadIdx.x] = p;
+    if (o < n) off[o] = first + p;
+    __syncthreads();
+    if (static_cast<int>(threadIdx.x) < marks.n) {
+        const int64_t at = marks.at[threadIdx.x], q = at - int64_t(blockIdx.x) * kItems;
+        if (at >= n) {
+            if (blockIdx.x == 0) bound[threadIdx.x] = *all;
+        } else if (q >= 0 && q < kItems) {
+            bound[threadIdx.x] = first + before[q];
+        }
     }
 }
 
-// sorted position p: coordinates and state from emitted entry perm[p]; a kept
-// oct copies its 8 cells, a new one repeats its father cell
-__global__ void k_refine_gather(const int32_t *__restrict__ perm, const int32_t *__restrict__ new_ijkl,
-                                const int32_t *__restrict__ src, const double *__restrict__ u, int64_t m,
-                                int32_t *ijkl_out, double *u_out)
+// The eight cells of the oct with key K along the curve: the cell at place h
+// is c0 ^ (the Gray code of h with its three bits sent to a, b, c), so the
+// first three places give the rest.  K << 3 | h is the key of the child oct
+// under that cell, whose coordinates' low bits are the cell.
+struct CurveCells {
+    int c0, a, b, c;
+
+    __device__ __forceinline__ explicit CurveCells(uint64_t K)
+    {
+        int v[3];
+#pragma unroll
+        for (int h = 0; h < 3; ++h) {
+            int32_t i, j, k, l;
+            key_coords((K << 3) | uint64_t(h), i, j, k, l);
+            v[h] = (i & 1) + 2 * (j & 1) + 4 * (k & 1);
+        }
+        c0 = v[0];
+        a = v[0] ^ v[1];
+        b = v[1] ^ v[2];
+        c = 7 ^ a ^ b;
+    }
+
+    __device__ __forceinline__ int cell(int h) const
+    {
+        const int g = h ^ (h >> 1);
+        return c0 ^ ((g & 1) ? a : 0) ^ ((g & 2) ? b : 0) ^ ((g & 4) ? c : 0);
+    }
+};
+
+struct EmitArgs {
+    const uint32_t *flags, *son, *off;
+    const int32_t *father, *ijkl;
+    const uint64_t *keys;
+    int64_t n, coarse_end, cap;
+    int32_t *src, *new_ijkl;
+    uint64_t *new_keys;
+};
+
+// new oct p: its source (an old oct, or -1 - the cell it is under), key and
+// coordinates; places past the capacity are left out
+__device__ __forceinline__ void emit(const EmitArgs &a, int64_t p, int32_t src, uint64_t key, int i, int j, int k, int l)
 {
+    if (p >= a.cap) return;
+    a.src[p] = src;
+    a.new_keys[p] = key;
+    reinterpret_cast<int4 *>(a.new_ijkl)[p] = make_int4(i, j, k, l);
+}
+
+// every old oct: its own new place, if it is kept, and the new children under
+// its flagged leaf cells.  The coarsest level comes first and is kept whole.
+__global__ __launch_bounds__(256) void k_refine_emit(EmitArgs a)
+{
+    const int64_t o = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (o >= a.n) return;
+    if (!kept(a.flags, a.father, o, o < a.coarse_end)) return;
+    const uint64_t K = a.keys[o];
+    const int32_t i = a.ijkl[4 * o], j = a.ijkl[4 * o + 1], k = a.ijkl[4 * o + 2], l = a.ijkl[4 * o + 3];
+    int64_t p = o;
+    if (o >= a.coarse_end) {
+        // place among the father's flagged cells
+        const int64_t f = a.father[o] >> 3;
+        const uint32_t m = a.flags[f] & 0xffu;
+        const int h = static_cast<int>(K & 7);
+        int rank = h;
+        if (m != 0xffu) {
+            const CurveCells cells(K >> 3);
+            rank = 0;
+            for (int g = 0; g < h; ++g) rank += (m >> cells.cell(g)) & 1;
+        }
+        p = a.coarse_end + a.off[f] + rank;
+    }
+    emit(a, p, static_cast<int32_t>(o), K, i, j, k, l);
+    const uint32_t m = a.flags[o] & 0xffu;
+    if (!(m & ~a.son[o])) return;
+    const CurveCells cells(K);
+    int64_t q = a.coarse_end + a.off[o];
+    for (int h = 0; h < 8; ++h) {
+        const int c = cells.cell(h);
+        if (!((m >> c) & 1u)) continue;
+        if (!((a.son[o] >> c) & 1u))
+            emit(a, q, static_cast<int32_t>(-1 - (8 * o + c)), (K << 3) | uint64_t(h), 2 * i + (c & 1),
+                 2 * j + ((c >> 1) & 1), 2 * k + (c >> 2), l + 1);
+        ++q;
+    }
+}
+
+// new oct p: key, coordinates and state; a kept oct copies its 8 cells, a new
+// one repeats its father cell.  V: doubles per load and store (2 where both
+// states and the coordinates are 16-byte aligned).  The copy of the state is
+// what bounds it.
+template <int V>
+__global__ __launch_bounds__(256) void k_refine_gather(const int32_t *__restrict__ new_ijkl,
+                                                       const uint64_t *__restrict__ new_keys,
+                                                       const int32_t *__restrict__ src, const double *__restrict__ u,
+                                                       int64_t n, int64_t m, int32_t *__restrict__ ijkl_out,
+                                                       uint64_t *__restrict__ keys_out, double *__restrict__ u_out)
+{
+    constexpr int T = 40 / V;   // threads per oct
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t p = t / 40;
-    const int r = static_cast<int>(t - 40 * p);
+    const int64_t p = t / T;
+    const int r = static_cast<int>(t - T * p);
     if (p >= m) return;
-    const int32_t e = perm[p];
-    const int32_t s = src[e];
-    if (r < 4) ijkl_out[4 * p + r] = new_ijkl[4 * int64_t(e) + r];
-    const double v = s >= 0 ? u[40 * int64_t(s) + r] : u[NVR * (-1 - int64_t(s)) + (r % NVR)];
-    u_out[40 * p + r] = v;
+    // son masks and father cells that contradict each other leave places
+    // without a source: those read the first oct
+    int32_t s = src[p];
+    if (s >= n || -1 - int64_t(s) >= 8 * n) s = 0;
+    if (r == 0) keys_out[p] = new_keys[p];
+    if constexpr (V == 2) {
+        if (r == 1) reinterpret_cast<int4 *>(ijkl_out)[p] = reinterpret_cast<const int4 *>(new_ijkl)[p];
+        double2 v;
+        if (s >= 0) {
+            v = reinterpret_cast<const double2 *>(u + 40 * int64_t(s))[r];
+        } else {
+            const double *c = u + NVR * (-1 - int64_t(s));
+            v.x = c[(2 * r) % NVR];
+            v.y = c[(2 * r + 1) % NVR];
+        }
+        reinterpret_cast<double2 *>(u_out + 40 * p)[r] = v;
+    } else {
+        if (r < 4) ijkl_out[4 * p + r] = new_ijkl[4 * p + r];
+        u_out[40 * p + r] = s >= 0 ? u[40 * int64_t(s) + r] : u[NVR * (-1 - int64_t(s)) + (r % NVR)];
+    }
+}
+
+__global__ void k_refine_levels(int64_t *begin, Marks lb)
+{
+    if (threadIdx.x < RG_MAX_LEVEL + 2) begin[threadIdx.x] = lb.at[threadIdx.x];
 }
 
 struct RefineWs {
-    uint32_t *flags;
-    int32_t *cnt, *off, *src, *new_ijkl, *total;
-    void *temp;
-    size_t temp_bytes;
+    uint32_t *flags, *off, *cnt, *total;
+    int32_t *src, *new_ijkl;
+    int64_t *bound;
 };
 
 size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 
-size_t scan_temp_bytes(int64_t cap)
+size_t core_bytes(int64_t cap)
 {
-    size_t temp = 0;
-    hipcub::DeviceScan::ExclusiveSum(nullptr, temp, static_cast<const int32_t *>(nullptr),
-                                     static_cast<int32_t *>(nullptr), static_cast<int>(cap > 0 ? cap : 1));
-    return temp;
+    return 3 * al256(4 * cap) + al256(16 * cap) + al256(4 * item_blocks(cap)) + 512;
 }
 
 RefineWs carve(void *ws, int64_t cap)
 {
     char *p = static_cast<char *>(ws);
     RefineWs w;
+    w.total = reinterpret_cast<uint32_t *>(p);
+    p += 256;
+    w.bound = reinterpret_cast<int64_t *>(p);
+    p += 256;
     w.flags = reinterpret_cast<uint32_t *>(p);
     p += al256(4 * cap);
-    w.cnt = reinterpret_cast<int32_t *>(p);
-    p += al256(4 * cap);
-    w.off = reinterpret_cast<int32_t *>(p);
+    w.off = reinterpret_cast<uint32_t *>(p);
     p += al256(4 * cap);
     w.src = reinterpret_cast<int32_t *>(p);
     p += al256(4 * cap);
     w.new_ijkl = reinterpret_cast<int32_t *>(p);
     p += al256(16 * cap);
-    w.total = reinterpret_cast<int32_t *>(p);
-    p += 256;
-    w.temp = p;
-    w.temp_bytes = al256(scan_temp_bytes(cap));
+    w.cnt = reinterpret_cast<uint32_t *>(p);
     return w;
 }
 
@@ -262,10 +374,11 @@ rg_status flags_pass(const rg_tree *t, const double *d_u, const rg_refine_params
         }
     }
     if (closure) {
-        for (int l = t->lmax; l > t->lmin; --l) {
+        // no cell above ltop is flagged
+        for (int l = ltop; l > t->lmin; --l) {
             const int64_t ob = t->level_begin[l], oe = t->level_begin[l + 1];
             if (oe <= ob) continue;
-            k_refine_closure<<<grid_for(oe - ob, 256), 256, 0, s>>>(t->d_nbr27, t->d_father_cell, ob, oe, flags,
+            k_refine_closure<<<grid_for(32 * (oe - ob), 256), 256, 0, s>>>(t->d_nbr27, t->d_father_cell, ob, oe, flags,
                                                                     pr->nsubgrid == 4);
             RG_TRY(launch_status("refine closure"));
         }
@@ -283,8 +396,7 @@ extern "C" {
 size_t rg_refine_workspace_bytes(int64_t capacity)
 {
     const int64_t cap = capacity > 0 ? capacity : 1;
-    const size_t core = 4 * al256(4 * cap) + al256(16 * cap) + 256 + al256(scan_temp_bytes(cap)) + 256;
-    return core + al256(nbr_lists_ws_bytes(cap));
+    return core_bytes(cap) + al256(nbr_lists_ws_bytes(cap));
 }
 
 rg_status rg_refine_flags(const rg_tree *t, const double *d_u, const rg_refine_params *p, int closure,
@@ -315,51 +427,71 @@ rg_status rg_refine(rg_tree *t, const double *d_u, double *d_u_new, const rg_ref
     RefineWs w = carve(d_ws, cap);
     RG_TRY(flags_pass(t, d_u, p, 1, w.flags, s));
     const int64_t coarse_end = t->level_begin[t->lmin + 1];
-    k_refine_count<<<grid_for(n, 256), 256, 0, s>>>(w.flags, t->d_father_cell, t->d_son_mask, n, coarse_end, w.cnt);
-    RG_TRY(launch_status("refine count"));
-    size_t tb = w.temp_bytes;
-    if (hipcub::DeviceScan::ExclusiveSum(w.temp, tb, w.cnt, w.off, static_cast<int>(n), s) != hipSuccess)
-        return fail(RG_EHIP, "refine scan");
-    int32_t h_last[2] = {0, 0};
-    if (hipMemcpyAsync(&h_last[0], w.off + (n - 1), 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(&h_last[1], w.cnt + (n - 1), 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
+    // places of the new octs, and the new level ranges: the octs of level l + 1
+    // are the children of the old octs of level l
+    const unsigned blocks = static_cast<unsigned>(item_blocks(n));
+    Marks old;
+    old.n = RG_MAX_LEVEL + 2;
+    for (int l = 0; l < old.n; ++l) old.at[l] = l <= t->lmin ? 0 : (l <= t->lmax ? t->level_begin[l] : n);
+    k_refine_count<<<blocks, kItems, 0, s>>>(w.flags, t->d_father_cell, n, coarse_end, w.cnt);
+    k_scan_blocks<<<1, kItems, 0, s>>>(w.cnt, blocks, w.total);
+    k_refine_offsets<<<blocks, kItems, 0, s>>>(w.flags, t->d_father_cell, n, coarse_end, w.cnt, w.total, old, w.off,
+                                               w.bound);
+    RG_TRY(launch_status("refine offsets"));
+    EmitArgs a;
+    a.flags = w.flags;
+    a.son = t->d_son_mask;
+    a.off = w.off;
+    a.father = t->d_father_cell;
+    a.ijkl = t->d_ijkl;
+    a.keys = t->d_keys;
+    a.n = n;
+    a.coarse_end = coarse_end;
+    a.cap = cap;
+    a.src = w.src;
+    a.new_ijkl = w.new_ijkl;
+    a.new_keys = t->d_keys_scratch;
+    k_refine_emit<<<grid_for(n, 256), 256, 0, s>>>(a);
+    RG_TRY(launch_status("refine emit"));
+    int64_t h[RG_MAX_LEVEL + 2];
+    if (hipMemcpyAsync(h, w.bound, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return fail(RG_EHIP, "refine count readback");
-    const int64_t m = int64_t(h_last[0]) + h_last[1];
+    const int64_t m = coarse_end + h[RG_MAX_LEVEL + 1];
     if (m > cap)
         return fail(RG_EFULL, "refined tree needs %lld octs, capacity %lld", static_cast<long long>(m),
                     static_cast<long long>(cap));
-    k_refine_emit<<<grid_for(n, 256), 256, 0, s>>>(w.flags, t->d_father_cell, t->d_son_mask, t->d_ijkl, n,
-                                                   coarse_end, w.off, w.new_ijkl, w.src);
-    RG_TRY(launch_status("refine emit"));
-    // stage 3-4: keys of the new octs, one radix sort (level-major, Hilbert inside a level)
-    const int lnew = t->lmax + 1 < p->lmax ? t->lmax + 1 : p->lmax;
-    RG_TRY(rg_encode_keys(w.new_ijkl, m, t->d_keys_scratch, stream));
-    RG_TRY(sort_keys_bits(t->d_keys_scratch, m, t->d_keys, t->d_perm, t->d_sort_ws, t->sort_ws_bytes, 3 * lnew, s));
-    k_refine_gather<<<grid_for(40 * m, 256), 256, 0, s>>>(t->d_perm, w.new_ijkl, w.src, d_u, m,
-                                                         t->d_ijkl, d_u_new);
+    Marks lb;
+    lb.n = RG_MAX_LEVEL + 2;
+    for (int l = 0; l < lb.n; ++l) lb.at[l] = l <= t->lmin ? 0 : coarse_end + h[l - 1];
+    const bool wide = aligned(d_u, 16) && aligned(d_u_new, 16) && aligned(t->d_ijkl, 16);
+    if (wide)
+        k_refine_gather<2><<<grid_for(20 * m, 256), 256, 0, s>>>(w.new_ijkl, t->d_keys_scratch, w.src, d_u, n, m, t->d_ijkl,
+                                                                t->d_keys, d_u_new);
+    else
+        k_refine_gather<1><<<grid_for(40 * m, 256), 256, 0, s>>>(w.new_ijkl, t->d_keys_scratch, w.src, d_u, n, m, t->d_ijkl,
+                                                                t->d_keys, d_u_new);
     RG_TRY(launch_status("refine gather"));
-    RG_TRY(rg_level_ranges(t->d_keys, m, t->d_level_begin, stream));
-    int64_t lb[RG_MAX_LEVEL + 2];
-    if (hipMemcpyAsync(lb, t->d_level_begin, sizeof(lb), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return fail(RG_EHIP, "refine level readback");
+    k_refine_levels<<<1, 64, 0, s>>>(t->d_level_begin, lb);
+    RG_TRY(launch_status("refine levels"));
     int lmax = t->lmin;
     for (int l = t->lmin; l <= RG_MAX_LEVEL; ++l)
-        if (lb[l + 1] > lb[l]) lmax = l;
-    for (int l = 0; l < RG_MAX_LEVEL + 2; ++l) t->level_begin[l] = lb[l];
+        if (lb.at[l + 1] > lb.at[l]) lmax = l;
+    for (int l = 0; l < RG_MAX_LEVEL + 2; ++l) t->level_begin[l] = lb.at[l];
     t->n_oct = m;
     t->lmax = lmax;
     t->sched = nullptr;
     RG_TRY(rg_hash_build(t->d_keys, m, t->d_hash_ws, t->hash_ws_bytes, stream));
-    // neighbour lists brick by brick: the complete bricks follow from the keys
-    const size_t core = 4 * al256(4 * cap) + al256(16 * cap) + 256 + al256(scan_temp_bytes(cap)) + 256;
+    // neighbour lists brick by brick: the complete bricks follow from the
+    // keys; the lists' lengths stay on the device, the grids hold as many as
+    // there could be
+    const size_t core = core_bytes(cap);
     const int32_t *lst = nullptr;
-    int64_t nb = 0, nr = 0;
+    const uint32_t *d_count = nullptr;
     RG_TRY(nbr_lists_device(t->d_keys, m, t->level_begin, t->lmin, t->lmax, static_cast<char *>(d_ws) + core,
-                            ws_bytes - core, &lst, &nb, &nr, s));
+                            ws_bytes - core, &lst, &d_count, s));
     return neighbours_scheduled(t->d_hash_ws, t->d_keys, m, t->lmin, t->lmax, t->level_begin[t->lmax], t->bc, lst,
-                                nb, lst + nb, nr, t->d_nbr27, t->d_father_cell, t->d_son_mask, s);
+                                m / 512, lst, m, t->d_nbr27, t->d_father_cell, t->d_son_mask, s, d_count);
 }
 
 }  // extern "C"

@@ -5,14 +5,13 @@
 // brick and the other octs for the neighbour build; per level above lmin the
 // octs with a coarse cell across a face; per level the complete sibling
 // groups outside the bricks and the octs outside bricks and groups), found
-// without copying the tree to the host: one pass marks complete bricks and
-// the bricks that touch a coarse cell, a second pass evaluates the seven
-// membership tests per oct, seven scans give every oct its place, and a
-// scatter writes the lists in key order.  The host reads back only the
-// per-level list lengths.  A tree that changes every step (refinement) keeps
-// its brick kernel this way.
-#include <hipcub/hipcub.hpp>
-
+// without copying the tree to the host: one pass over the neighbour lists
+// notes which octs have a coarse entry and marks their bricks, a second pass
+// evaluates the seven membership tests per oct, and the lists are written in
+// key order (rg_compact.hpp).  The host reads back only the per-level list
+// lengths.  A tree that changes every step (refinement) keeps its brick kernel
+// this way.
+#include "rg_compact.hpp"
 #include "rg_internal.hpp"
 
 namespace rg {
@@ -65,104 +64,95 @@ __device__ __forceinline__ int64_t group_first(const SchedArgs &a, int64_t o, in
 
 __device__ __forceinline__ bool coarse_entry(int32_t v) { return v < 0 && v != RG_NBR_OUTSIDE; }
 
-__global__ void k_sched_zero(uint32_t *p, int64_t n)
+__global__ void k_sched_zero(uint8_t *p, int64_t n)
 {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0;
 }
 
-// a complete brick with a coarse entry anywhere in its octs' lists is marked
-__global__ void k_sched_mark(SchedArgs a, uint32_t *bad)
+// Bit 0: some list entry of the oct is a coarse cell; bit 1: one across a
+// face.  A complete brick with a coarse entry anywhere in its octs' lists is
+// marked in bad[(first oct) / 512] (complete bricks start 512 octs apart at
+// least).  The workgroup reads its 256 octs' lists as one stretch, entry
+// after entry: 27 words per thread, whole lines (an oct per thread read 108
+// bytes apart: 90 us for 1.04 M octs).
+__global__ __launch_bounds__(256) void k_sched_mark(SchedArgs a, uint8_t *__restrict__ coarse,
+                                                    uint8_t *__restrict__ bad)
 {
-    const int64_t o = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (o >= a.n) return;
-    const int l = level_of(a, o);
-    const int64_t f = brick_first(a, o, l);
-    if (f < 0) return;
-    bool coarse = false;
-    for (int j = 0; j < 27; ++j) coarse = coarse || coarse_entry(a.nbr27[27 * o + j]);
-    if (coarse) atomicOr(&bad[f], 1u);
-}
-
-__global__ void k_sched_pred(SchedArgs a, const uint32_t *__restrict__ bad, int32_t *pred)
-{
-    const int64_t o = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (o >= a.n) return;
-    const int l = level_of(a, o);
-    const int64_t f = brick_first(a, o, l);
-    const bool complete = f >= 0;
-    const bool covered = complete && bad[f] == 0;
-    bool border = false;
-    if (l > a.lmin) {
-        const int slots[6] = {12, 14, 10, 16, 4, 22};
-        for (int s = 0; s < 6; ++s) border = border || coarse_entry(a.nbr27[27 * o + slots[s]]);
-    }
-    pred[0 * a.n + o] = covered && f == o;
-    pred[1 * a.n + o] = !covered;
-    pred[2 * a.n + o] = complete && f == o;
-    pred[3 * a.n + o] = !complete;
-    pred[4 * a.n + o] = border;
-    const int64_t g = covered ? -1 : group_first(a, o, l);
-    pred[5 * a.n + o] = g >= 0 && g == o;
-    pred[6 * a.n + o] = !covered && g < 0;
-}
-
-// per list and level boundary: the number of list members before the
-// boundary (the last boundary gives the list's length)
-__global__ void k_sched_bounds(SchedArgs a, const int32_t *__restrict__ pred, const int32_t *__restrict__ pos,
-                               int64_t *out)
-{
+    __shared__ uint32_t s[256];
     const int t = threadIdx.x;
-    if (t >= kLists * kLB) return;
-    const int k = t / kLB, l = t - kLB * k;
-    const int64_t b = a.begin[l] < a.n ? a.begin[l] : a.n;
-    const int32_t *p = pos + int64_t(k) * a.n;
-    const int32_t *q = pred + int64_t(k) * a.n;
-    out[t] = b < a.n ? int64_t(p[b]) : int64_t(p[a.n - 1]) + q[a.n - 1];
+    const int64_t first = int64_t(blockIdx.x) * 256;
+    const int64_t left = 27 * (a.n - first);
+    s[t] = 0;
+    __syncthreads();
+    const int32_t *p = a.nbr27 + 27 * first;
+    int k = t / 27, e = t - 27 * (t / 27);   // oct and entry, stepped: 256 = 9 * 27 + 13
+#pragma unroll 9
+    for (int i = 0; i < 27; ++i) {
+        const int q = t + 256 * i;
+        const int32_t v = q < left ? p[q] : 0;
+        if (coarse_entry(v)) {
+            const bool face = e == 4 || e == 10 || e == 12 || e == 14 || e == 16 || e == 22;
+            atomicOr(&s[k], face ? 3u : 1u);
+        }
+        k += 9;
+        e += 13;
+        if (e >= 27) {
+            e -= 27;
+            ++k;
+        }
+    }
+    __syncthreads();
+    const int64_t o = first + t;
+    if (o >= a.n) return;
+    coarse[o] = static_cast<uint8_t>(s[t]);
+    if (s[t]) {
+        const int64_t f = brick_first(a, o, level_of(a, o));
+        if (f >= 0) bad[f / kBrick] = 1;
+    }
 }
 
-struct Bases {
-    int64_t base[kLists];
+struct SchedMember {
+    SchedArgs a;
+    const uint8_t *coarse, *bad;
+
+    __device__ __forceinline__ uint32_t operator()(int64_t o) const
+    {
+        const int l = level_of(a, o);
+        const int64_t f = brick_first(a, o, l);
+        const bool complete = f >= 0;
+        const bool covered = complete && bad[f / kBrick] == 0;
+        const int64_t g = covered ? -1 : group_first(a, o, l);
+        const bool border = l > a.lmin && (coarse[o] & 2);
+        return (covered && f == o ? 1u : 0u) | (covered ? 0u : 2u) | (complete && f == o ? 4u : 0u) |
+               (complete ? 0u : 8u) | (border ? 16u : 0u) | (g >= 0 && g == o ? 32u : 0u) |
+               (!covered && g < 0 ? 64u : 0u);
+    }
 };
 
-__global__ void k_sched_scatter(int64_t n, const int32_t *__restrict__ pred, const int32_t *__restrict__ pos,
-                                Bases b, int32_t *list)
-{
-    const int64_t o = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (o >= n) return;
-#pragma unroll
-    for (int k = 0; k < kLists; ++k)
-        if (pred[int64_t(k) * n + o]) list[b.base[k] + pos[int64_t(k) * n + o]] = static_cast<int32_t>(o);
-}
+// keys only: first octs of complete bricks (list 0) and octs outside complete
+// bricks (list 1), for the brick-wise neighbour build
+struct NbrMember {
+    SchedArgs a;
 
-// keys only: first octs of complete bricks (pred[0]) and octs outside
-// complete bricks (pred[1]), for the brick-wise neighbour build
-__global__ void k_nbr_pred(SchedArgs a, int32_t *pred)
-{
-    const int64_t o = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (o >= a.n) return;
-    const int64_t f = brick_first(a, o, level_of(a, o));
-    pred[o] = f >= 0 && f == o;
-    pred[a.n + o] = f < 0;
-}
-
-__global__ void k_nbr_scatter(int64_t n, const int32_t *__restrict__ pred, const int32_t *__restrict__ pos,
-                              int64_t base1, int32_t *list)
-{
-    const int64_t o = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (o >= n) return;
-    if (pred[o]) list[pos[o]] = static_cast<int32_t>(o);
-    if (pred[n + o]) list[base1 + pos[n + o]] = static_cast<int32_t>(o);
-}
+    __device__ __forceinline__ uint32_t operator()(int64_t o) const
+    {
+        const int64_t f = brick_first(a, o, level_of(a, o));
+        return (f >= 0 && f == o ? 1u : 0u) | (f < 0 ? 2u : 0u);
+    }
+};
 
 size_t al(size_t b) { return (b + 255) & ~size_t(255); }
 
-size_t scan_bytes(int64_t n)
+SchedArgs sched_args(const uint64_t *keys, const int32_t *nbr27, int64_t n, const int64_t *begin, int lmin, int lmax)
 {
-    size_t temp = 0;
-    hipcub::DeviceScan::ExclusiveSum(nullptr, temp, static_cast<const int32_t *>(nullptr),
-                                     static_cast<int32_t *>(nullptr), static_cast<int>(n > 0 ? n : 1));
-    return temp;
+    SchedArgs a;
+    a.keys = keys;
+    a.nbr27 = nbr27;
+    a.n = n;
+    for (int l = 0; l < kLB; ++l) a.begin[l] = l <= lmax ? begin[l] : n;
+    a.lmin = lmin;
+    return a;
 }
 
 }  // namespace
@@ -170,52 +160,34 @@ size_t scan_bytes(int64_t n)
 size_t nbr_lists_ws_bytes(int64_t n)
 {
     n = n > 0 ? n : 1;
-    return 2 * al(8 * n) + al(4 * n + 4 * (n / kBrick) + 4) + al(scan_bytes(n)) + 256;
+    return al(n) + al(8 * item_blocks(n)) + al(4 * n + 4 * (n / kBrick) + 4) + 256;
 }
 
 // The neighbour-build lists of a tree from its keys and level ranges alone
 // (complete bricks, then the other octs, in key order) into the workspace;
-// *list points at them.  Synchronises once for the two lengths.
+// *list points at them, d_count at the two lengths (device).
 rg_status nbr_lists_device(const uint64_t *d_keys, int64_t n, const int64_t *h_level_begin, int lmin, int lmax,
-                           void *d_ws, size_t ws_bytes, const int32_t **list, int64_t *nbricks, int64_t *nrest,
-                           hipStream_t s)
+                           void *d_ws, size_t ws_bytes, const int32_t **list, const uint32_t **d_count, hipStream_t s)
 {
     RG_REQUIRE(ws_bytes >= nbr_lists_ws_bytes(n) && aligned(d_ws, 256), "neighbour-list workspace too small");
     char *p = static_cast<char *>(d_ws);
-    int32_t *pred = reinterpret_cast<int32_t *>(p);
-    p += al(8 * n);
-    int32_t *pos = reinterpret_cast<int32_t *>(p);
-    p += al(8 * n);
+    uint32_t *total = reinterpret_cast<uint32_t *>(p);
+    p += 256;
+    uint8_t *bits = reinterpret_cast<uint8_t *>(p);
+    p += al(n);
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(p);
+    p += al(8 * item_blocks(n));
     int32_t *lst = reinterpret_cast<int32_t *>(p);
-    p += al(4 * n + 4 * (n / kBrick) + 4);
-    void *temp = p;
-    SchedArgs a;
-    a.keys = d_keys;
-    a.nbr27 = nullptr;
-    a.n = n;
-    for (int l = 0; l < kLB; ++l) a.begin[l] = h_level_begin[l];
-    for (int l = lmax + 1; l < kLB; ++l) a.begin[l] = n;
-    a.lmin = lmin;
-    k_nbr_pred<<<grid_for(n, 256), 256, 0, s>>>(a, pred);
+    const NbrMember m{sched_args(d_keys, nullptr, n, h_level_begin, lmin, lmax)};
+    const unsigned blocks = static_cast<unsigned>(item_blocks(n));
+    k_members_count<2><<<blocks, kItems, 0, s>>>(n, m, bits, cnt);
+    k_scan_blocks<<<2, kItems, 0, s>>>(cnt, blocks, total);
+    Marks none;
+    none.n = 0;
+    k_members_scatter<2><<<blocks, kItems, 0, s>>>(n, bits, cnt, total, n + n / kBrick + 1, lst, none, nullptr);
     RG_TRY(launch_status("neighbour lists"));
-    for (int k = 0; k < 2; ++k) {
-        size_t tb = al(scan_bytes(n));
-        if (hipcub::DeviceScan::ExclusiveSum(temp, tb, pred + k * n, pos + k * n, static_cast<int>(n), s) !=
-            hipSuccess)
-            return fail(RG_EHIP, "neighbour-list scan");
-    }
-    int32_t h[4];
-    if (hipMemcpyAsync(&h[0], pos + (n - 1), 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(&h[1], pred + (n - 1), 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(&h[2], pos + (2 * n - 1), 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(&h[3], pred + (2 * n - 1), 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return fail(RG_EHIP, "neighbour-list readback");
-    *nbricks = int64_t(h[0]) + h[1];
-    *nrest = int64_t(h[2]) + h[3];
-    k_nbr_scatter<<<grid_for(n, 256), 256, 0, s>>>(n, pred, pos, *nbricks, lst);
-    RG_TRY(launch_status("neighbour-list scatter"));
     *list = lst;
+    *d_count = total;
     return RG_OK;
 }
 
@@ -228,7 +200,7 @@ extern "C" {
 size_t rg_schedule_workspace_bytes(int64_t n_oct)
 {
     const int64_t n = n_oct > 0 ? n_oct : 1;
-    return al(4 * n) + 2 * al(4 * kLists * n) + al(8 * kLists * kLB) + al(scan_bytes(n)) + 256;
+    return 2 * al(n) + al(n / kBrick + 1) + al(4 * kLists * item_blocks(n)) + al(8 * kLists * kLB) + 512;
 }
 
 rg_status rg_schedule_build_device(const rg_tree *t, int32_t *d_list, int64_t capacity, void *d_ws, size_t ws_bytes,
@@ -244,53 +216,45 @@ rg_status rg_schedule_build_device(const rg_tree *t, int32_t *d_list, int64_t ca
     const int64_t n = t->n_oct;
     hipStream_t s = as_stream(stream);
     char *p = static_cast<char *>(d_ws);
-    uint32_t *bad = reinterpret_cast<uint32_t *>(p);
-    p += al(4 * n);
-    int32_t *pred = reinterpret_cast<int32_t *>(p);
-    p += al(4 * kLists * n);
-    int32_t *pos = reinterpret_cast<int32_t *>(p);
-    p += al(4 * kLists * n);
+    uint32_t *lengths = reinterpret_cast<uint32_t *>(p);
+    p += 256;
+    uint8_t *coarse = reinterpret_cast<uint8_t *>(p);
+    p += al(n);
+    uint8_t *bits = reinterpret_cast<uint8_t *>(p);
+    p += al(n);
+    uint8_t *bad = reinterpret_cast<uint8_t *>(p);
+    p += al(n / kBrick + 1);
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(p);
+    p += al(4 * kLists * item_blocks(n));
     int64_t *bounds = reinterpret_cast<int64_t *>(p);
-    p += al(8 * kLists * kLB);
-    void *temp = p;
-    const size_t temp_bytes = al(scan_bytes(n));
 
-    SchedArgs a;
-    a.keys = t->d_keys;
-    a.nbr27 = t->d_nbr27;
-    a.n = n;
-    for (int l = 0; l < kLB; ++l) a.begin[l] = t->level_begin[l];
-    for (int l = t->lmax + 1; l < kLB; ++l) a.begin[l] = n;
-    a.lmin = t->lmin;
-    k_sched_zero<<<grid_for(n, 256), 256, 0, s>>>(bad, n);
-    RG_TRY(launch_status("schedule clear"));
-    k_sched_mark<<<grid_for(n, 256), 256, 0, s>>>(a, bad);
+    const SchedArgs a = sched_args(t->d_keys, t->d_nbr27, n, t->level_begin, t->lmin, t->lmax);
+    k_sched_zero<<<grid_for(n / kBrick + 1, 256), 256, 0, s>>>(bad, n / kBrick + 1);
+    k_sched_mark<<<grid_for(n, 256), 256, 0, s>>>(a, coarse, bad);
     RG_TRY(launch_status("schedule bricks"));
-    k_sched_pred<<<grid_for(n, 256), 256, 0, s>>>(a, bad, pred);
-    RG_TRY(launch_status("schedule tests"));
-    for (int k = 0; k < kLists; ++k) {
-        size_t tb = temp_bytes;
-        if (hipcub::DeviceScan::ExclusiveSum(temp, tb, pred + k * n, pos + k * n, static_cast<int>(n), s) !=
-            hipSuccess)
-            return fail(RG_EHIP, "schedule scan");
-    }
-    static_assert(kLists * kLB <= 256, "one thread per list and level");
-    k_sched_bounds<<<1, 256, 0, s>>>(a, pred, pos, bounds);
-    RG_TRY(launch_status("schedule bounds"));
+    const SchedMember m{a, coarse, bad};
+    const unsigned blocks = static_cast<unsigned>(item_blocks(n));
+    k_members_count<kLists><<<blocks, kItems, 0, s>>>(n, m, bits, cnt);
+    k_scan_blocks<<<kLists, kItems, 0, s>>>(cnt, blocks, lengths);
+    Marks marks;
+    marks.n = kLB;
+    for (int l = 0; l < kLB; ++l) marks.at[l] = a.begin[l] < n ? a.begin[l] : n;
+    k_members_scatter<kLists><<<blocks, kItems, 0, s>>>(n, bits, cnt, lengths, capacity, d_list, marks, bounds);
+    RG_TRY(launch_status("schedule lists"));
     int64_t h[kLists * kLB];
     if (hipMemcpyAsync(h, bounds, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return fail(RG_EHIP, "schedule readback");
     auto at = [&](int k, int l) { return h[k * kLB + l]; };
-    Bases b;
+    struct {
+        int64_t base[kLists];
+    } b;
     int64_t total = 0;
     for (int k = 0; k < kLists; ++k) {
         b.base[k] = total;
         total += at(k, kLB - 1);
     }
     if (total > capacity) return fail(RG_EINVAL, "schedule exceeds list capacity");
-    k_sched_scatter<<<grid_for(n, 256), 256, 0, s>>>(n, pred, pos, b, d_list);
-    RG_TRY(launch_status("schedule scatter"));
     for (int l = 0; l < kLB; ++l)
         out->brick_begin[l] = out->brick_count[l] = out->rest_begin[l] = out->rest_count[l] = out->border_begin[l] =
             out->border_count[l] = out->group_begin[l] = out->group_count[l] = out->single_begin[l] =

@@ -426,10 +426,16 @@ __global__ __launch_bounds__(256) void k_neighbours(const uint64_t *__restrict__
                                                     HashHeader *hdr, const uint64_t *__restrict__ keys,
                                                     const int32_t *__restrict__ vals, uint64_t mask,
                                                     int32_t *__restrict__ nbr27, int32_t *__restrict__ father_cell,
-                                                    uint32_t *__restrict__ son_mask)
+                                                    uint32_t *__restrict__ son_mask,
+                                                    const uint32_t *__restrict__ counts)
 {
     __shared__ NbrOcts S;
     const int64_t first = int64_t(blockIdx.x) * kNbrOcts;
+    if (counts) {   // the list's place and length are on the device only
+        list += counts[0];
+        n = counts[1];
+        if (first >= n) return;
+    }
     const int64_t left = n - first;
     const NbrTable tab{okeys, hdr, keys, vals, mask, nbr27, father_cell, son_mask, lmin, bc, lmax_zero, n_oct};
     nbr_each_body(tab, list, first, left < kNbrOcts ? static_cast<int>(left) : kNbrOcts, S);
@@ -440,10 +446,16 @@ __global__ __launch_bounds__(256) void k_neighbours_groups(const uint64_t *__res
                                                     HashHeader *hdr, const uint64_t *__restrict__ keys,
                                                     const int32_t *__restrict__ vals, uint64_t mask,
                                                     int32_t *__restrict__ nbr27, int32_t *__restrict__ father_cell,
-                                                    uint32_t *__restrict__ son_mask)
+                                                    uint32_t *__restrict__ son_mask,
+                                                    const uint32_t *__restrict__ counts)
 {
     __shared__ NbrChunk S;
     const int64_t first = int64_t(blockIdx.x) * kNbrChunk;
+    if (counts) {   // the list's place and length are on the device only
+        list += counts[0];
+        n = counts[1];
+        if (first >= n) return;
+    }
     const int64_t left = n - first;
     const NbrTable tab{okeys, hdr, keys, vals, mask, nbr27, father_cell, son_mask, lmin, bc, lmax_zero, n_oct};
     nbr_octs_body(tab, list, first, left < kNbrChunk ? static_cast<int>(left) : kNbrChunk, S);
@@ -451,17 +463,17 @@ __global__ __launch_bounds__(256) void k_neighbours_groups(const uint64_t *__res
 
 rg_status launch_neighbours(const uint64_t *d_keys, const int32_t *list, int64_t n, int64_t n_oct, int lmin, int bc,
                             int lmax_zero, const HashView &h, int32_t *d_nbr27, int32_t *d_father_cell,
-                            uint32_t *d_son_mask, hipStream_t s)
+                            uint32_t *d_son_mask, const uint32_t *d_counts, hipStream_t s)
 {
     const bool groups = n > kNbrByGroups;
     const int chunk = groups ? kNbrChunk : kNbrOcts;
     const unsigned blocks = static_cast<unsigned>((n + chunk - 1) / chunk);
     if (groups)
         k_neighbours_groups<<<blocks, 256, 0, s>>>(d_keys, list, n, n_oct, lmin, bc, lmax_zero, h.hdr, h.keys, h.vals,
-                                                   h.mask, d_nbr27, d_father_cell, d_son_mask);
+                                                   h.mask, d_nbr27, d_father_cell, d_son_mask, d_counts);
     else
         k_neighbours<<<blocks, 256, 0, s>>>(d_keys, list, n, n_oct, lmin, bc, lmax_zero, h.hdr, h.keys, h.vals,
-                                            h.mask, d_nbr27, d_father_cell, d_son_mask);
+                                            h.mask, d_nbr27, d_father_cell, d_son_mask, d_counts);
     return launch_status("neighbours");
 }
 
@@ -472,12 +484,14 @@ __global__ __launch_bounds__(256) void k_neighbours_brick(const uint64_t *__rest
                                                           const int32_t *__restrict__ vals, uint64_t mask,
                                                           int32_t *__restrict__ nbr27,
                                                           int32_t *__restrict__ father_cell,
-                                                          uint32_t *__restrict__ son_mask)
+                                                          uint32_t *__restrict__ son_mask,
+                                                          const uint32_t *__restrict__ counts)
 {
     __shared__ NbrBrick nb;
+    if (counts) nbricks = counts[0];   // the grid is sized for as many as there could be
     const int64_t per_xcd = (nbricks + 7) / 8;
     const int64_t b = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    if (b >= nbricks) return;
+    if (blockIdx.x / 8 >= per_xcd || b >= nbricks) return;
     const NbrTable tab{okeys, hdr, keys, vals, mask, nbr27, father_cell, son_mask, lmin, bc, lmax_zero, 0};
     nbr_brick_body(tab, bricks[b], nb);
 }
@@ -486,7 +500,8 @@ __global__ __launch_bounds__(256) void k_neighbours_brick(const uint64_t *__rest
 
 rg_status neighbours_scheduled(void *d_ws, const uint64_t *d_keys, int64_t n, int lmin, int lmax, int64_t n_below_lmax,
                                int bc, const int32_t *bricks, int64_t nbricks, const int32_t *rest, int64_t nrest,
-                               int32_t *d_nbr27, int32_t *d_father_cell, uint32_t *d_son_mask, hipStream_t s)
+                               int32_t *d_nbr27, int32_t *d_father_cell, uint32_t *d_son_mask, hipStream_t s,
+                               const uint32_t *d_counts)
 {
     const uint64_t cap = hash_capacity(n);
     HashView h = hash_view(d_ws, cap);
@@ -498,11 +513,11 @@ rg_status neighbours_scheduled(void *d_ws, const uint64_t *d_keys, int64_t n, in
     if (nbricks > 0) {
         k_neighbours_brick<<<static_cast<unsigned>(8 * ((nbricks + 7) / 8)), 256, 0, s>>>(
             d_keys, bricks, nbricks, lmin, bc, lmax, h.hdr, h.keys, h.vals, h.mask, d_nbr27, d_father_cell,
-            d_son_mask);
+            d_son_mask, d_counts);
         RG_TRY(launch_status("brick neighbours"));
     }
     if (nrest > 0) {
-        RG_TRY(launch_neighbours(d_keys, rest, nrest, n, lmin, bc, lmax, h, d_nbr27, d_father_cell, d_son_mask, s));
+        RG_TRY(launch_neighbours(d_keys, rest, nrest, n, lmin, bc, lmax, h, d_nbr27, d_father_cell, d_son_mask, d_counts, s));
     }
     return RG_OK;
 }
@@ -788,7 +803,7 @@ rg_status rg_build_neighbours(void *d_ws, const uint64_t *d_keys, int64_t n, int
     hipStream_t s = as_stream(stream);
     RG_TRY(fill_u32(d_son_mask, n, 0u, s));
     return launch_neighbours(d_keys, nullptr, n, n, lmin, bc, RG_MAX_LEVEL + 1, h, d_nbr27, d_father_cell, d_son_mask,
-                             s);
+                             nullptr, s);
 }
 
 }  // extern "C"

@@ -1,6 +1,8 @@
 """The rebuild of a tree on the device at the sizes where its pieces meet,
 bit for bit against the oracle: neighbour lists of short lists (octs one by
-one) and, in a batch and in long lists, by sibling groups."""
+one) and, in a batch and in long lists, by sibling groups; schedules; refined
+trees whose flags leave any subset of an oct's cells, states and coordinates at
+any alignment their types allow."""
 import numpy as np
 import pytest
 import torch
@@ -80,3 +82,53 @@ def test_neighbour_lists_of_a_batch():
         say("batch:", len(t[0]))
         _check_lists(d, O.Tree(*t))
     B.close()
+
+
+@pytest.mark.parametrize("name", [t[0] for t in TREES])
+def test_device_schedule_equals_host(name):
+    from paper_2607_20704_amd import api
+    D = api.DeviceTree(*_tree(name))
+    dev = D.schedule_lists()
+    D.build_schedule(on_host=True)
+    host = D.schedule_lists()
+    say("schedule:", name, D.schedule_counts())
+    assert dev.keys() == host.keys()
+    for k in dev:
+        for a, b in zip(dev[k], host[k]):
+            assert np.array_equal(a, b), (name, k)
+
+
+@pytest.mark.parametrize("odd", [False, True])
+@pytest.mark.parametrize("share", [0.02, 0.3, 1.0])
+@pytest.mark.parametrize("name", [t[0] for t in TREES[1:-1]])
+def test_refine(name, share, odd):
+    """A share of the cells above the density threshold, in no order; odd: both
+    states 8 bytes and the coordinates 4 bytes past a 16-byte boundary."""
+    from paper_2607_20704_amd import api
+    ijkl, bc = _tree(name)
+    T = O.Tree(ijkl, bc)
+    rng = np.random.default_rng(len(ijkl))
+    ref = rng.random((8 * T.n, 5)) + 0.5
+    ref[:, 0] = np.where(rng.random(8 * T.n) < share, 2.0, 1.0) * (0.9 + 0.2 * rng.random(8 * T.n))
+    lmax = min(T.lmax + 1, 6)
+    _, ni, nu = T.refine(ref, 1.5, 0.0, lmax)
+    T2 = O.Tree(ni, bc)
+    say("refine:", name, T.n, "->", T2.n)
+    D = api.DeviceTree(ijkl, bc, capacity=9 * T.n)
+    shift = 1 if odd else 0
+    u = torch.empty(40 * D.capacity + 1, dtype=torch.float64, device="cuda")[shift:shift + 40 * T.n].view(-1, 5)
+    out = torch.empty(40 * D.capacity + 1, dtype=torch.float64, device="cuda")[shift:shift + 40 * D.capacity]
+    u.copy_(torch.as_tensor(ref))
+    if odd:
+        buf = torch.empty(4 * D.capacity + 1, dtype=torch.int32, device="cuda")[1:].view(-1, 4)
+        buf[:D.n] = D.ijkl_sorted
+        D._ijkl = buf
+        D._desc.d_ijkl = buf.data_ptr()
+    got = D.refine(u, 1.5, 0.0, lmax, out=out.view(-1, 5))
+    torch.cuda.synchronize()
+    assert D.n == T2.n and np.array_equal(D.keys.cpu().numpy(), T2.keys)
+    assert np.array_equal(D.ijkl_sorted.cpu().numpy(), T2.ijkl)
+    assert [int(x) for x in D.level_begin] == [int(x) for x in D.level_begin_dev.cpu()]
+    assert all(int(D.level_begin[l]) == T2.level_begin[l] for l in range(T2.lmin, T2.lmax + 2))
+    assert np.array_equal(got.cpu().numpy(), T2.permute_cells(nu))
+    _check_lists(D, T2)
