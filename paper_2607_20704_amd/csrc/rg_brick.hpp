@@ -438,19 +438,24 @@ __device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const
             lds_put(S.hw[2], lane, Wh);
         }
     }
-    // FP64: ghost-ring cells are loaded one plane ahead of their use, so that
-    // no wave waits for memory right before a barrier (the face-layer lanes
-    // hold plane rz+1 for step 1 of iteration rz, the outer-ring and corner
-    // lanes plane rz for step 2).  The mixed form keeps the registers this
-    // costs: it runs more waves per SIMD instead.
-    constexpr bool PF = sizeof(R) == 8;
+    // PF (with KU): every cell is loaded one plane ahead of its use, so that no
+    // wave waits for memory between two barriers (the column holds plane rz+1
+    // for step 1 of iteration rz, the face-layer lanes plane rz+1 too, the
+    // outer-ring and corner lanes plane rz for step 2).  All that was loaded in
+    // the last iteration is used before any load of this one is issued: a
+    // wave's loads are counted, not named, so a use behind newer loads would
+    // wait for those as well, and the ring's wave, with every other wave
+    // behind it at the barrier, then spends a memory round trip per plane.
+    // The four-wave variant has no registers for it.
+    constexpr bool PF = KU;
     int rx = 0, ry = 0;
     const bool ring_role = do_outer || do_corner;
     if (do_corner) ring_pos(3, lane, rx, ry);
     else if (do_outer) ring_pos(2, lane, rx, ry);
-    double Upf[NV];
+    double Upf[NV], Unn[NV];
     if constexpr (PF) {
         bool sdummy;
+        load_u(a.uold, source_cell<GEN>(S.tab, g, x, y, 0, sdummy), Unn);
         if (do_face) load_u(a.uold, source_cell<GEN>(S.tab, g, hx, hy, 0, sdummy), Upf);
         if (ring_role) load_u(a.uold, source_cell<GEN>(S.tab, g, rx, ry, 0, sdummy), Upf);
     }
@@ -480,26 +485,14 @@ __device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const
         BrickFaces<R> &FB = S.u_[fb];
         uint8_t *spl = S.split[fb];
         double Un[NV];                               // conserved variables of plane rz+1, own column
-        sp_next = false;
-        load_u(a.uold, source_cell<GEN>(S.tab, g, x, y, rz + 1, sp_next), Un);
-        // 1. the reconstructed ghost ring: primitive variables of plane rz+1
+        double invp = 0.0;
         bool hsplit = false;
-        if (do_face) {
-            if (rz + 1 <= nz) {
-                R Wh[NV];
-                bool sdummy;
-                if constexpr (PF) {
-                    to_prim(Upf, a.gamma, Wh);
-                    if (rz + 2 <= nz) load_u(a.uold, source_cell<GEN>(S.tab, g, hx, hy, rz + 2, sdummy), Upf);
-                } else {
-                    double U[NV];
-                    load_u(a.uold, source_cell<GEN>(S.tab, g, hx, hy, rz + 1, sdummy), U);
-                    to_prim(U, a.gamma, Wh);
-                }
-                lds_put(S.hw[(rz + 4) % 3], lane, Wh);
-            }
-            (void)source_cell<GEN>(S.tab, g, hx, hy, rz, hsplit);
-        }
+        sp_next = false;
+        (void)source_cell<GEN>(S.tab, g, x, y, rz + 1, sp_next);
+        if (do_face) (void)source_cell<GEN>(S.tab, g, hx, hy, rz, hsplit);
+        // 1. what was loaded ahead: the primitive variables of the own column
+        //    and of the reconstructed ghost ring in plane rz+1, of the outer
+        //    ring in plane rz (at rz = nz the ring's are not needed any more)
         // 2. plane rz into LDS: W and split flags
         {
             lds_put(S.w, (x + 2) + PW * (y + 2), W0);
@@ -509,18 +502,42 @@ __device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const
             lds_put(S.w, (hx + 2) + PW * (hy + 2), ld5(S.hw[(rz + 3) % 3], lane).v);
             if constexpr (GEN) spl[(hx + 2) + PW * (hy + 2)] = hsplit;
         }
-        if (ring_role && inner) {
-            R Wr[NV];
+        if constexpr (PF) {
             bool sdummy;
-            if constexpr (PF) {
+            copy5(Un, Unn);
+            invp = to_prim(Un, a.gamma, Wp);
+            if (do_face) {
+                R Wh[NV];
+                to_prim(Upf, a.gamma, Wh);
+                lds_put(S.hw[(rz + 4) % 3], lane, Wh);
+                __builtin_amdgcn_sched_barrier(0);
+                load_u(a.uold, source_cell<GEN>(S.tab, g, hx, hy, min(rz + 2, nz), sdummy), Upf);
+            }
+            if (ring_role && inner) {
+                R Wr[NV];
                 to_prim(Upf, a.gamma, Wr);
-                if (rz + 1 < nz) load_u(a.uold, source_cell<GEN>(S.tab, g, rx, ry, rz + 1, sdummy), Upf);
-            } else {
-                double U[NV];
+                lds_put(S.w, (rx + 2) + PW * (ry + 2), Wr);
+                __builtin_amdgcn_sched_barrier(0);
+                load_u(a.uold, source_cell<GEN>(S.tab, g, rx, ry, min(rz + 1, nz - 1), sdummy), Upf);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            load_u(a.uold, source_cell<GEN>(S.tab, g, x, y, min(rz + 2, nz + 1), sdummy), Unn);
+        } else {
+            bool sdummy;
+            double U[NV];
+            load_u(a.uold, source_cell<GEN>(S.tab, g, x, y, rz + 1, sdummy), Un);
+            if (do_face && rz + 1 <= nz) {
+                R Wh[NV];
+                load_u(a.uold, source_cell<GEN>(S.tab, g, hx, hy, rz + 1, sdummy), U);
+                to_prim(U, a.gamma, Wh);
+                lds_put(S.hw[(rz + 4) % 3], lane, Wh);
+            }
+            if (ring_role && inner) {
+                R Wr[NV];
                 load_u(a.uold, source_cell<GEN>(S.tab, g, rx, ry, rz, sdummy), U);
                 to_prim(U, a.gamma, Wr);
+                lds_put(S.w, (rx + 2) + PW * (ry + 2), Wr);
             }
-            lds_put(S.w, (rx + 2) + PW * (ry + 2), Wr);
         }
         __syncthreads();
         // the next plane of octs of a column, by the waves that hold no
@@ -548,9 +565,8 @@ __device__ __forceinline__ void brick_sweep(const BrickArgs &a, int64_t b, const
         }
         R sxm[NV], sym[NV];
         double gz[NV];
-        double invp;
         {
-            invp = to_prim(Un, a.gamma, Wp);
+            if constexpr (!PF) invp = to_prim(Un, a.gamma, Wp);
             R dW[3][NV], Wq[NV], st[NV], szm[NV];
             const int c = (x + 2) + PW * (y + 2);
             nxy_cur = GEN && (spl[c - 1] || spl[c + 1] || spl[c - PW] || spl[c + PW]);
