@@ -151,6 +151,13 @@ template <bool P, typename F> __device__ __forceinline__ void for_items(int64_t 
     }
 }
 
+// 2^-level, formed in scalar registers (ldexp is a vector instruction, and two
+// more vector registers cost the FP64 group kernel a seventh of its waves)
+__device__ __forceinline__ double level_dx(int level)
+{
+    return __longlong_as_double(static_cast<long long>(1023 - level) << 52);
+}
+
 // FP64 bricks keep each column's state in registers (two waves per SIMD);
 // mixed bricks read it again, at three waves: at four the loop spilled (72
 // scratch loads), and the 64-box graph took 38.0 ms against 35.2 ms at three.
@@ -175,7 +182,7 @@ __global__ __launch_bounds__(BT, sizeof(R) == 8 ? 2 : 3) void k_batch_bricks(con
         a.first = 0;
         a.nb = 0;
         a.dt = dt + I.tree;
-        a.dx = ldexp(1.0, -(I.a >> 2));
+        a.dx = level_dx(I.a >> 2);
         a.gamma = T.gamma;
         a.outflow = T.bc == RG_BC_OUTFLOW;
         a.cfl = T.cfl;
@@ -204,7 +211,7 @@ __device__ __forceinline__ LevelArgs level_args(const BTree &T, const Item &I, i
     a.ucoarse2 = T.u[parity];
     a.oct_begin = 0;
     a.dt = dt + I.tree;
-    a.dx = ldexp(1.0, -level);
+    a.dx = level_dx(level);
     a.gamma = T.gamma;
     a.cfl = T.cfl;
     a.dt_next = reinterpret_cast<unsigned long long *>(dt_next + I.tree);

@@ -176,22 +176,31 @@ __device__ __forceinline__ void hydro_sib(const LevelArgs &a, const int32_t *__r
     // the siblings by place (the father cell's index in its oct), their
     // neighbour lists and son masks; the places of a consistent tree are a
     // permutation, and an inconsistent one still names octs of the group
+    // lists of the group are read in key order together with the places they
+    // belong to, not after them: one memory round trip less
+    int32_t e0 = 0, f0 = 0;
+    uint32_t m0 = 0xffu;
+    static_assert(NT >= 8 * 27, "one thread per list entry");
+    const int g0 = tid / 27, s0 = tid - 27 * g0;
+    if (tid < 8 * 27) {
+        e0 = a.nbr27[27 * first + tid];
+        f0 = father[first + g0];
+        if (s0 == 0 && a.skip_split) m0 = a.son[first + g0];
+        S.nb[tid] = RG_NBR_OUTSIDE;
+    }
     if (tid < 8) S.oct[tid] = static_cast<int32_t>(first) + tid;
     if (tid == 0) {
         S.outside = S.coarse = S.split = 0;
         S.live = !a.skip_split;
     }
     __syncthreads();
-    if (tid < 8) {
-        S.oct[father[first + tid] & 7] = static_cast<int32_t>(first) + tid;
-        if (a.skip_split && a.son[first + tid] != 0xffu) S.live = 1;
-    }
-    __syncthreads();
-    for (int it = tid; it < 8 * 27; it += NT) {
-        const int g = it / 27, s = it - 27 * g;
-        const int32_t e = a.nbr27[27 * int64_t(S.oct[g]) + s];
-        S.nb[it] = e;
-        if (e < 0) (e == RG_NBR_OUTSIDE ? S.outside : S.coarse) = 1;
+    if (tid < 8 * 27) {
+        S.nb[27 * (f0 & 7) + s0] = e0;
+        if (e0 < 0) (e0 == RG_NBR_OUTSIDE ? S.outside : S.coarse) = 1;
+        if (s0 == 0) {
+            S.oct[f0 & 7] = static_cast<int32_t>(first) + g0;
+            if (m0 != 0xffu) S.live = 1;
+        }
     }
     __syncthreads();
     // only split cells, which the restriction overwrites: nothing to do
