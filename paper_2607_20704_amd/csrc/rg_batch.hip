@@ -223,7 +223,7 @@ template <typename R, int G, bool P, bool GH>
 __global__ __launch_bounds__(kT) void k_batch_octs(const BTree *__restrict__ trees, const Item *__restrict__ items,
                                                    int64_t nitems, int parity, const double *dt, double *dt_next)
 {
-    __shared__ Smem<R, G> S;
+    __shared__ Smem<R, G, GH> S;
     for_items<P>(nitems, [&](int64_t it) {
         const Item I = items[it];
         const LevelArgs a = level_args(trees[I.tree], I, parity, dt, dt_next);
@@ -234,16 +234,16 @@ __global__ __launch_bounds__(kT) void k_batch_octs(const BTree *__restrict__ tre
 // complete sibling groups: item = one group, `first` its entry in the tree's
 // schedule list
 template <typename R, bool P, bool GH>
-__global__ __launch_bounds__(sib_threads(sizeof(R) == 8, GH)) void k_batch_groups(const BTree *__restrict__ trees,
+__global__ __launch_bounds__(sib_threads(sizeof(R) == 8)) void k_batch_groups(const BTree *__restrict__ trees,
                                                         const Item *__restrict__ items, int64_t nitems, int parity,
                                                         const double *dt, double *dt_next)
 {
-    __shared__ SibSmem<R> S;
+    __shared__ SibSmem<R, GH> S;
     for_items<P>(nitems, [&](int64_t it) {
         const Item I = items[it];
         const BTree &T = trees[I.tree];
         const LevelArgs a = level_args(T, I, parity, dt, dt_next);
-        hydro_sib<R, sib_threads(sizeof(R) == 8, GH), GH>(a, T.father, T.list[I.first], S);
+        hydro_sib<R, sib_threads(sizeof(R) == 8), GH>(a, T.father, T.list[I.first], S);
     });
 }
 
@@ -443,7 +443,7 @@ rg_status launch_groups(bool gh, bool persistent, const BTree *trees, const Phas
                         double *dt_next, hipStream_t s)
 {
     if (p.n == 0) return RG_OK;
-    const int nt = sib_threads(sizeof(R) == 8, gh);
+    const int nt = sib_threads(sizeof(R) == 8);
     if (persistent) {
         const void *k = gh ? reinterpret_cast<const void *>(&k_batch_groups<R, true, true>)
                            : reinterpret_cast<const void *>(&k_batch_groups<R, true, false>);

@@ -52,7 +52,7 @@ __device__ __forceinline__ int xcd_item(int n)
 template <typename R, int G, int NT, bool GH>
 __global__ __launch_bounds__(NT) void k_hydro_level(LevelArgs a, LevelTab lv)
 {
-    __shared__ Smem<R, G> S;
+    __shared__ Smem<R, G, GH> S;
     const int w = xcd_item(lv.item_end[lv.n - 1]);
     if (w < 0) return;
     int count;
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(NT) void k_hydro_level(LevelArgs a, LevelTab lv)
 template <typename R, int NT, bool GH>
 __global__ __launch_bounds__(NT) void k_hydro_sib(LevelArgs a, LevelTab lv, const int32_t *__restrict__ father)
 {
-    __shared__ SibSmem<R> S;
+    __shared__ SibSmem<R, GH> S;
     const int w = xcd_item(lv.item_end[lv.n - 1]);
     if (w < 0) return;
     int count;
@@ -253,7 +253,7 @@ template <typename R>
 rg_status launch_sib_form(const LevelArgs &a, const LevelTab &lv, const int32_t *father, const rg_tuning *tune,
                           hipStream_t s)
 {
-    const int nt = tune && tune->group_threads ? tune->group_threads : sib_threads(sizeof(R) == 8, a.ghost);
+    const int nt = tune && tune->group_threads ? tune->group_threads : sib_threads(sizeof(R) == 8);
     if (nt == 320) return launch_sib<R, 320>(a, lv, father, s);
     if (nt == 256) return launch_sib<R, 256>(a, lv, father, s);
     if (nt == 384) return launch_sib<R, 384>(a, lv, father, s);

@@ -100,59 +100,76 @@ __constant__ StencilTables c_tab = make_tables();
 // the level kernel
 // ---------------------------------------------------------------------------
 
-// Values of the fine position at sub-cell (sx, sy, sz) of coarse cell C:
-// C's own (injection), or with ghost = 1 C's values plus a quarter of each
-// minmod slope, toward the position, taken from C's face neighbours (in C's
-// oct, in the neighbouring oct, the coarser cell covering it, or C itself
-// outside the domain).  Along each axis one neighbour lies in C's oct and the
-// other across it; the three list entries, then the seven cells, are loaded
-// together, two memory round trips in all (axis by axis it was six).
-__device__ __forceinline__ void coarse_ghost(const LevelArgs &a, int64_t C, int sx, int sy, int sz, double *U)
+// Variable v at the fine position of sub-cell `sub` of coarse cell C: C's
+// value plus a quarter of each minmod slope, toward the position, taken from
+// C's face neighbours (in C's oct, in the neighbouring oct, the coarser cell
+// covering it, or C itself outside the domain).  Along each axis one neighbour
+// lies in C's oct and the other across it; the three list entries, then the
+// seven cells, are loaded together, two memory round trips in all.
+__device__ __forceinline__ double coarse_ghost(const LevelArgs &a, int64_t C, int sub, int v)
 {
     const int64_t P = C >> 3;
     const int q = static_cast<int>(C & 7);
-    if (!a.ghost) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) U[v] = a.ucoarse[NV * C + v];
-        return;
-    }
     int32_t e[3];
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
         const int step = ax == 0 ? 1 : (ax == 1 ? 3 : 9);
         e[ax] = a.nbr27[27 * P + 13 + (((q >> ax) & 1) ? step : -step)];
     }
-    double uc[NV], in[3][NV], over[3][NV];
+    const double uc = a.ucoarse[NV * C + v];
+    double in[3], over[3];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) uc[v] = a.ucoarse[NV * C + v];
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) in[ax][v] = a.ucoarse[NV * (8 * P + (q ^ (1 << ax))) + v];
+    for (int ax = 0; ax < 3; ++ax) in[ax] = a.ucoarse[NV * (8 * P + (q ^ (1 << ax))) + v];
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
         const double *src = e[ax] < 0 && e[ax] != RG_NBR_OUTSIDE ? a.ucoarse2 : a.ucoarse;
         const int64_t cell = e[ax] == RG_NBR_OUTSIDE ? C
                                                      : (e[ax] >= 0 ? 8 * int64_t(e[ax]) + (q ^ (1 << ax))
                                                                    : -1 - int64_t(e[ax]));
-#pragma unroll
-        for (int v = 0; v < NV; ++v) over[ax][v] = src[NV * cell + v];
+        over[ax] = src[NV * cell + v];
     }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) U[v] = uc[v];
+    double u = uc;
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
         const bool up = (q >> ax) & 1;   // C on its oct's high side: the neighbour across is the high one
-        const double qq = (ax == 0 ? sx : (ax == 1 ? sy : sz)) ? 0.25 : -0.25;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            const double lo = up ? in[ax][v] : over[ax][v], hi = up ? over[ax][v] : in[ax][v];
-            U[v] = U[v] + qq * minmod<double>(uc[v] - lo, hi - uc[v]);
-        }
+        const double qq = ((sub >> ax) & 1) ? 0.25 : -0.25;
+        const double lo = up ? in[ax] : over[ax], hi = up ? over[ax] : in[ax];
+        u = u + qq * minmod<double>(uc - lo, hi - uc);
     }
+    return u;
 }
 
-template <typename R, int G> struct Smem {
+// Interpolated ghost cells of a workgroup's stencil: noted while the other
+// cells are gathered, then formed one variable per thread, then turned into
+// primitive variables.  Formed where the gather met them, five variables at
+// once, they took 88 registers and every wave with one such lane through the
+// whole interpolation (a subcycled step of the clumps of levels 6-9, mixed:
+// 1566 us; like this 1388).
+template <int N> struct GhostCells {
+    double u[NV][N];            // their values
+    int32_t n;
+    int16_t cell[N];            // stencil index, sub-cell of the coarse cell above its 10 bits
+    int32_t coarse[N];          // list entry of the coarse cell
+
+    __device__ __forceinline__ void note(int it, int sub, int32_t e)
+    {
+        const uint64_t m = __ballot(1);
+        const int rank = __popcll(m & ((uint64_t(1) << (threadIdx.x & 63)) - 1));
+        int base = 0;
+        if (rank == 0) base = atomicAdd(&n, __popcll(m));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (base + rank < N) {   // own cells are never ghosts
+            cell[base + rank] = static_cast<int16_t>(it | sub << 10);
+            coarse[base + rank] = e;
+        }
+    }
+};
+
+template <> struct GhostCells<0> {};
+
+constexpr int kOctGhosts = kOctW - 8;   // stencil cells that may be ghosts
+
+template <typename R, int G, bool GH = false> struct Smem {
     int64_t oct[G];
     int32_t nb[G][27];
     uint32_t sm[G][7];          // son masks: own, then sides x-, x+, y-, y+, z-, z+
@@ -164,18 +181,22 @@ template <typename R, int G> struct Smem {
         R w[G][NV][kOctW];      // primitive variables of the stencil cells (planes, lds_get)
         double g[G][NV][kOctF]; // G = F dt/dx per face
     };
-    R fs[G][2][NV][kOctF];      // face states: [0] left of the face, [1] right (planes)
+    union {
+        R fs[G][2][NV][kOctF];      // face states: [0] left of the face, [1] right (planes)
+        GhostCells<GH ? G * kOctGhosts : 0> ghost;   // before there are face states
+    };
 };
 
-// GH: compiled with the interpolating coarse-ghost path (whose registers
-// would otherwise lower every launch's occupancy); a.ghost then selects it.
+// GH: compiled with the interpolating coarse-ghost path; a.ghost then selects
+// it.
 // Bound like the sibling group (see hydro_sib) by the latency of its phases:
 // table words, walls, split cells and coarse neighbours looked at only if the
 // workgroup's octs have any, the update and the time step by the first wave.
 template <typename R, int G, int NT, bool GH = false>
-__device__ __forceinline__ void hydro_group(const LevelArgs &a, int64_t first, int count, Smem<R, G> &S)
+__device__ __forceinline__ void hydro_group(const LevelArgs &a, int64_t first, int count, Smem<R, G, GH> &S)
 {
     static_assert(8 * G <= 64, "the own cells are updated by one wave");
+    static_assert(G * kOctW <= 1024, "see GhostCells");
     const int tid = threadIdx.x;
     const double r = *a.dt / a.dx;
     const R h = static_cast<R>(0.5 * r);
@@ -187,6 +208,7 @@ __device__ __forceinline__ void hydro_group(const LevelArgs &a, int64_t first, i
     if (tid == 0) {
         S.outside = S.coarse = S.split = 0;
         S.live = !a.skip_split;
+        if constexpr (GH) S.ghost.n = 0;
     }
     __syncthreads();
     if (a.skip_split && tid < count && a.son[S.oct[tid]] != 0xffu) S.live = 1;
@@ -239,21 +261,37 @@ __device__ __forceinline__ void hydro_group(const LevelArgs &a, int64_t first, i
         // a consistent list never leaves an outside slot here; an
         // inconsistent one reads the oct itself rather than stray memory
         if (e == RG_NBR_OUTSIDE) e = static_cast<int>(S.oct[g]);
-        double U[NV], W[NV];
-        if (e >= 0) {
-            const double *src = a.uold + NV * (8 * int64_t(e) + bit);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) U[v] = src[v];
-        } else if constexpr (GH) {
-            coarse_ghost(a, -1 - int64_t(e), bit & 1, (bit >> 1) & 1, bit >> 2, U);
-        } else {
-            const double *src = a.ucoarse + NV * (-1 - int64_t(e));
-#pragma unroll
-            for (int v = 0; v < NV; ++v) U[v] = src[v];
+        if constexpr (GH) {
+            if (a.ghost && e < 0) {
+                S.ghost.note(it, bit, e);
+                continue;
+            }
         }
+        const double *src = e >= 0 ? a.uold + NV * (8 * int64_t(e) + bit) : a.ucoarse + NV * (-1 - int64_t(e));
+        double U[NV], W[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) U[v] = src[v];
         prim64(U, a.gamma, W);
 #pragma unroll
         for (int v = 0; v < NV; ++v) S.w[g][v][wc] = static_cast<R>(W[v]);
+    }
+    if constexpr (GH) {
+        if (a.ghost && S.coarse) {
+            __syncthreads();
+            const int n = min(S.ghost.n, G * kOctGhosts);
+            for (int k = tid; k < n * NV; k += NT) {
+                const int i = k / NV, v = k - NV * i;
+                S.ghost.u[v][i] = coarse_ghost(a, -1 - int64_t(S.ghost.coarse[i]), S.ghost.cell[i] >> 10, v);
+            }
+            __syncthreads();
+            for (int i = tid; i < n; i += NT) {
+                const int it = S.ghost.cell[i] & 1023, g = it / kOctW;
+                double W[NV];
+                prim64(ld5(S.ghost.u, i).v, a.gamma, W);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) S.w[g][v][it - kOctW * g] = static_cast<R>(W[v]);
+            }
+        }
     }
     if (mine) {
         S.sm[mg][mk] = m;

@@ -117,14 +117,13 @@ __device__ __forceinline__ int side_slot(int ax, int hi)
     return nslot(ax == 0 ? d : 0, ax == 1 ? d : 0, ax == 2 ? d : 0);
 }
 
-// Workgroup size: FP64 without interpolated ghosts, whose five groups per
-// compute unit are LDS-bound, one stencil cell per thread; otherwise four
-// waves, one per SIMD, which the registers allow more of (clumps of levels
-// 7-11, one step: FP64 869 us at 320 threads, 882 at 256; mixed 663 and 579;
-// FP64 with interpolated ghosts 1108 and 979; 192 threads 937, 608, 1048).
-__host__ __device__ constexpr int sib_threads(bool fp64, bool ghost) { return fp64 && !ghost ? 320 : 256; }
+// Workgroup size: FP64, whose five groups per compute unit are LDS-bound, one
+// stencil cell per thread; mixed four waves, one per SIMD (clumps of levels
+// 7-11, one step: FP64 830 us at 320 threads, 840 at 256; mixed 634 and 562;
+// with interpolated ghosts FP64 947 and 966, mixed 719 and 662).
+__host__ __device__ constexpr int sib_threads(bool fp64) { return fp64 ? 320 : 256; }
 
-template <typename R> struct SibSmem {
+template <typename R, bool GH = false> struct SibSmem {
     int32_t oct[8];             // by place in the group
     int32_t nb[8 * 27];
     // son masks: [0, 8) the siblings; 8 + 4 side + q the neighbour across
@@ -138,7 +137,10 @@ template <typename R> struct SibSmem {
         R w[NV][kSibW];         // primitive variables of the stencil cells (planes, lds_get)
         double g[NV][kSibF];    // G = F dt/dx per face
     };
-    R fs[2][NV][kSibF];         // face states: [0] left of the face, [1] right (planes)
+    union {
+        R fs[2][NV][kSibF];         // face states: [0] left of the face, [1] right (planes)
+        GhostCells<GH ? kSibW - 64 : 0> ghost;   // before there are face states
+    };
 };
 
 // son mask holding the cell at group position (x, y, z), one coordinate of
@@ -165,7 +167,7 @@ __device__ __forceinline__ uint32_t sib_mask_at(const uint32_t *sm, int x, int y
 // the state is kept once.
 template <typename R, int NT, bool GH>
 __device__ __forceinline__ void hydro_sib(const LevelArgs &a, const int32_t *__restrict__ father, int64_t first,
-                                          SibSmem<R> &S)
+                                          SibSmem<R, GH> &S)
 {
     const int tid = threadIdx.x;
     const double r = *a.dt / a.dx;
@@ -192,6 +194,7 @@ __device__ __forceinline__ void hydro_sib(const LevelArgs &a, const int32_t *__r
     if (tid == 0) {
         S.outside = S.coarse = S.split = 0;
         S.live = !a.skip_split;
+        if constexpr (GH) S.ghost.n = 0;
     }
     __syncthreads();
     if (tid < 8 * 27) {
@@ -247,21 +250,36 @@ __device__ __forceinline__ void hydro_sib(const LevelArgs &a, const int32_t *__r
         }
         int e = S.nb[entry];
         if (e == RG_NBR_OUTSIDE) e = S.oct[sib];
-        double U[NV], W[NV];
-        if (e >= 0) {
-            const double *src = a.uold + NV * (8 * int64_t(e) + bit);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) U[v] = src[v];
-        } else if constexpr (GH) {
-            coarse_ghost(a, -1 - int64_t(e), bit & 1, (bit >> 1) & 1, bit >> 2, U);
-        } else {
-            const double *src = a.ucoarse + NV * (-1 - int64_t(e));
-#pragma unroll
-            for (int v = 0; v < NV; ++v) U[v] = src[v];
+        if constexpr (GH) {
+            if (a.ghost && e < 0) {
+                S.ghost.note(it, bit, e);
+                continue;
+            }
         }
+        const double *src = e >= 0 ? a.uold + NV * (8 * int64_t(e) + bit) : a.ucoarse + NV * (-1 - int64_t(e));
+        double U[NV], W[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) U[v] = src[v];
         prim64(U, a.gamma, W);
 #pragma unroll
         for (int v = 0; v < NV; ++v) S.w[v][it] = static_cast<R>(W[v]);
+    }
+    if constexpr (GH) {
+        if (a.ghost && S.coarse) {
+            __syncthreads();
+            const int n = min(S.ghost.n, kSibW - 64);
+            for (int k = tid; k < n * NV; k += NT) {
+                const int i = k / NV, v = k - NV * i;
+                S.ghost.u[v][i] = coarse_ghost(a, -1 - int64_t(S.ghost.coarse[i]), S.ghost.cell[i] >> 10, v);
+            }
+            __syncthreads();
+            for (int i = tid; i < n; i += NT) {
+                double W[NV];
+                prim64(ld5(S.ghost.u, i).v, a.gamma, W);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) S.w[v][S.ghost.cell[i] & 1023] = static_cast<R>(W[v]);
+            }
+        }
     }
     if (ms >= 0 && ms < 32) {
         S.sm[ms] = m;
