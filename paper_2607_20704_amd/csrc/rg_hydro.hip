@@ -49,8 +49,12 @@ __device__ __forceinline__ int xcd_item(int n)
     return w < n ? w : -1;
 }
 
+// FP64, four octs: registers for the six workgroups that the LDS holds (86
+// registers hold five; a handful spill for the sixth): a step of the clumps of
+// levels 7-11 846 -> 835 us, with interpolated ghosts 950 -> 934 us.  The mixed
+// form has registers to spare.
 template <typename R, int G, int NT, bool GH>
-__global__ __launch_bounds__(NT) void k_hydro_level(LevelArgs a, LevelTab lv)
+__global__ __launch_bounds__(NT, G == 4 && sizeof(R) == 8 ? 6 : 1) void k_hydro_level(LevelArgs a, LevelTab lv)
 {
     __shared__ Smem<R, G, GH> S;
     const int w = xcd_item(lv.item_end[lv.n - 1]);
