@@ -146,9 +146,8 @@ rg_status rg_prepare_tree(const rg_tree *t, unsigned flags, void *stream)
     if (flags & RG_STEP_REKEY) {
         RG_REQUIRE(t->d_ijkl && t->d_keys_scratch && t->d_perm && t->d_sort_ws && t->d_level_begin,
                    "RG_STEP_REKEY needs coordinates, scratch keys, permutation, sort workspace and level ranges");
-        RG_TRY(rg_encode_keys(t->d_ijkl, t->n_oct, t->d_keys_scratch, stream));
-        RG_TRY(sort_keys_bits(t->d_keys_scratch, t->n_oct, t->d_keys, t->d_perm, t->d_sort_ws, t->sort_ws_bytes,
-                              3 * t->lmax, as_stream(stream)));
+        RG_TRY(rekey(t->d_ijkl, t->n_oct, t->d_keys_scratch, t->d_keys, t->d_perm, t->d_sort_ws, t->sort_ws_bytes,
+                     3 * t->lmax, as_stream(stream)));
         RG_TRY(rg_level_ranges(t->d_keys, t->n_oct, t->d_level_begin, stream));
     }
     if (flags & RG_STEP_REBUILD) {

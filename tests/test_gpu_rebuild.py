@@ -2,7 +2,7 @@
 bit for bit against the oracle: neighbour lists of short lists (octs one by
 one) and, in a batch and in long lists, by sibling groups; schedules; refined
 trees whose flags leave any subset of an oct's cells, states and coordinates at
-any alignment their types allow."""
+any alignment their types allow; keys of octs in any order."""
 import numpy as np
 import pytest
 import torch
@@ -132,3 +132,40 @@ def test_refine(name, share, odd):
     assert all(int(D.level_begin[l]) == T2.level_begin[l] for l in range(T2.lmin, T2.lmax + 2))
     assert np.array_equal(got.cpu().numpy(), T2.permute_cells(nu))
     _check_lists(D, T2)
+
+
+@pytest.mark.parametrize("how", ["sorted", "one_swap", "repeats", "shuffled"])
+@pytest.mark.parametrize("level", [1, 2, 5, 6, 7, 8, 9])
+def test_rekey(level, how):
+    """Keys and places of octs in any order: one tile of 1024 keys and
+    several, whole and in part (of 4096 beyond 524288 keys, of two parts
+    beyond 2097152), one to three passes of 8 bits, equal keys in
+    the order they came."""
+    from paper_2607_20704_amd import api, _lib as L
+    if level == 7:   # 4096-key tiles: complete levels 6 and 7 and a part of level 8
+        ijkl = np.concatenate([I.uniform_tree(6), I.uniform_tree(7), I.uniform_tree(8)[:8 * 40001]])
+    elif level == 9:
+        ijkl = np.concatenate([I.uniform_tree(8), I.uniform_tree(9)[:8 * 1001]])
+    else:
+        ijkl = _tree("holes_4_8")[0] if level == 8 else I.uniform_tree(level)
+    D = api.DeviceTree(ijkl, I.PERIODIC)
+    rng = np.random.default_rng(level)
+    c = D.ijkl_sorted.cpu().numpy()
+    if how == "one_swap" and D.n > 1:
+        at = min(254, D.n - 2)   # the last key of one workgroup's stretch and the first of the next
+        c[[at, at + 1]] = c[[at + 1, at]]
+    elif how == "repeats":
+        c = c[rng.integers(0, D.n, D.n)]
+    elif how == "shuffled":
+        c = c[rng.permutation(D.n)]
+    D._ijkl[:D.n] = torch.as_tensor(np.ascontiguousarray(c))
+    want = O.keys(c)
+    order = np.argsort(want, kind="stable")
+    for _ in range(2):
+        D.keys.view(torch.int64).fill_(-1)
+        D.perm_scratch.fill_(-1)
+        D.prepare(L.RG_STEP_REKEY)
+        torch.cuda.synchronize()
+        assert np.array_equal(D.keys_scratch[:D.n].cpu().numpy(), want)
+        assert np.array_equal(D.keys.cpu().numpy(), want[order])
+        assert np.array_equal(D.perm_scratch[:D.n].cpu().numpy(), order)
