@@ -414,7 +414,7 @@ rg_status rg_hydro_step_scheduled(const rg_tree *t, const rg_schedule *sched, in
                                   int form, const rg_tuning *tune, void *stream);
 
 #define RG_STEP_REBUILD 1u    /* rebuild the hash table and neighbour lists first */
-#define RG_STEP_REKEY 2u      /* recompute keys from d_ijkl, radix-sort them, level ranges */
+#define RG_STEP_REKEY 2u      /* recompute keys from d_ijkl, sort them, level ranges */
 #define RG_STEP_CHAIN_DT 4u   /* d_dt[0] holds this step's dt; the next step's goes to d_dt[1] */
 
 /* The tree bookkeeping of a step (Sec. 2.1-2.3; Table 1 "refine"/"cache"

@@ -224,13 +224,15 @@ __device__ __forceinline__ void nbr_octs_body(const NbrTable &T, const int32_t *
         // group look up their octs
         const int m = static_cast<int>(kn & 7);
         const bool lead = own && m == 0;
+        // the sibling next to the lane's oct, named if that oct is missing
+        const int sib = __shfl(m, (min(max(x, 0), 1) + 1) + 4 * (min(max(y, 0), 1) + 1) + 16 * (min(max(z, 0), 1) + 1), 64);
         int32_t e = nbr_find(T, own ? (lead && l > T.lmin ? kf >> 3 : 0) : kn);
         const int32_t fo = __shfl(e, __ffsll(static_cast<unsigned long long>(__ballot(lead))) - 1, 64);
         if (own) {
             S.place[wave][m] = lane;
             e = static_cast<int32_t>(f) + m;
         } else {
-            e = nbr_entry(T, e, kn, ni, nj, nk, l, f);
+            e = nbr_entry(T, e, kn, ni, nj, nk, l, f + sib);
         }
         S.slot[wave][lane] = e;
         // one wave's LDS operations are done in order

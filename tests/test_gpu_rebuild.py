@@ -169,3 +169,24 @@ def test_rekey(level, how):
         assert np.array_equal(D.keys_scratch[:D.n].cpu().numpy(), want)
         assert np.array_equal(D.keys.cpu().numpy(), want[order])
         assert np.array_equal(D.perm_scratch[:D.n].cpu().numpy(), order)
+
+
+def test_ungraded_group_is_reported():
+    """A complete sibling group on level 9 whose outside neighbours exist
+    neither there nor on level 8, behind enough octs for the lists to go by
+    groups: reported, naming an oct of the group."""
+    from paper_2607_20704_amd import api, _lib as L
+
+    def group(at, level):
+        return np.array([[at + i, at + j, at + k, level] for i in range(2) for j in range(2) for k in range(2)])
+
+    tree = np.concatenate([I.uniform_tree(7), group(64, 8), group(128, 9)]).astype(np.int32)
+    tree = tree[O.tree_order(tree)]
+    st_o, bad_o, *_ = O.neighbours(tree, I.PERIODIC)
+    keys = torch.as_tensor(O.keys(tree).astype(np.int64)).cuda().view(torch.uint64)
+    ws = api.hash_build(keys)
+    api.build_neighbours(ws, keys, 7, I.PERIODIC)
+    st, bad = api.check_ws(ws)
+    say("ungraded group: oct named", bad, "by the oracle", bad_o)
+    assert st == L.RG_EUNGRADED == st_o
+    assert tree[bad, 3] == 9
