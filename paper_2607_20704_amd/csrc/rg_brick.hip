@@ -56,9 +56,9 @@ int brick_slabs(int64_t nbricks, int slots, int waves)
 }
 
 // Planes per segment of a column of `side` planes: 256^3, FP64 128 planes (512
-// workgroups, one round of the chip; 708 us against 757 in 16-plane bricks),
-// mixed 86 (768 workgroups; 506 against 554 us); 128^3, 16 (93 us) and 12 (62
-// us); 32^3, 2 planes (16 us against 64 us for 8 whole bricks).
+// workgroups, one round of the chip; 694 us against 741 in 16-plane bricks),
+// mixed 86 (768 workgroups; 504 against 536 us); 128^3, 16 (93 us) and 12 (62
+// us); 32^3, 2 planes (15 us against 64 us for 8 whole bricks).
 int column_planes(int64_t columns, int side, int slots, int waves)
 {
     int best = side;
