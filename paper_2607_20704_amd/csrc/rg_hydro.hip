@@ -232,8 +232,16 @@ template <typename R, int G, int NT> rg_status launch_level(const LevelArgs &a, 
 
 template <typename R> rg_status launch_form(const LevelArgs &a, const LevelTab &lv, const rg_tuning *tune, hipStream_t s)
 {
-    const int g = tune && tune->octs_per_group ? tune->octs_per_group : 4;
-    const int nt = tune && tune->threads ? tune->threads : 256;
+    // Mixed without interpolated ghosts, whose registers and LDS are few: 96
+    // reconstructions and 108 faces of 3 octs fill 128 threads better than the
+    // 128 and 144 of 4 octs fill 256 (clumps of levels 7-11: 551 against 563
+    // us, a 256^3 box by octs 1563 against 1744).  Few octs take what ends
+    // sooner (3224 of them: 4).  FP64 (831 us either way) and interpolated
+    // ghosts (mixed 678 against 661) keep 4.
+    const bool three = sizeof(R) == 4 && !a.ghost && tab_items(lv) > 8192 &&
+                       !(tune && (tune->octs_per_group || tune->threads));
+    const int g = three ? 3 : (tune && tune->octs_per_group ? tune->octs_per_group : 4);
+    const int nt = three ? 128 : (tune && tune->threads ? tune->threads : 256);
     if (g == 4 && nt == 256) return launch_level<R, 4, 256>(a, lv, s);
     if (g == 2 && nt == 128) return launch_level<R, 2, 128>(a, lv, s);
     if (g == 8 && nt == 256) return launch_level<R, 8, 256>(a, lv, s);

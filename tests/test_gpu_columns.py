@@ -86,3 +86,17 @@ def test_levels_in_one_launch(base, lmax, centre, radius, bc, form):
         api.restrict_level(parts, D.father_cell, int(D.level_begin[l]), int(D.level_begin[l + 1]))
     assert torch.equal(parts, want)
     assert np.array_equal(nxt.cpu().numpy(), dt[1:].cpu().numpy())
+
+
+@pytest.mark.parametrize("level", [5, 6])
+@pytest.mark.parametrize("form", [0, 1])
+def test_per_oct_default_shape(level, form):
+    """The per-oct kernel as the library shapes it by form and number of octs
+    (32768 octs, mixed: three octs to 128 threads, the last workgroup two)
+    against four octs to 256 threads: the same bits."""
+    from paper_2607_20704_amd import api
+    D = api.DeviceTree(I.uniform_tree(level), I.OUTFLOW)
+    u = _state(D, 1.4, 60 + level)
+    want, dt = _step(D, u, 1.4, form, PER_OCT)
+    got, d = _step(D, u, 1.4, form, (0, 0, 1))
+    assert torch.equal(got, want) and torch.equal(d, dt)
