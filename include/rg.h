@@ -170,9 +170,10 @@ size_t rg_hash_workspace_bytes(int64_t n_keys);
 
 /* Clears the table and inserts (d_keys[i], i) for i < n: slot = FNV-1a-64
  * over the 8 little-endian key bytes, masked by capacity - 1, then linear
- * probing.  Built segment by segment: keys are bucketed by the 4096-slot
- * segment of their home slot (a counting sort: per-chunk counts, their
- * prefix, a scatter), each segment is filled in LDS with 64-bit
+ * probing.  Up to 262144 keys are inserted with global 64-bit
+ * compare-and-swap; more are built segment by segment: keys are bucketed by
+ * the 4096-slot segment of their home slot (a counting sort: per-chunk counts,
+ * their prefix, a scatter), each segment is filled in LDS with 64-bit
  * compare-and-swap and written out whole, and the few probe sequences that
  * leave their segment are finished with global compare-and-swap.  Keys must
  * be non-zero and unique; violations are flagged in the header (rg_check).

@@ -190,3 +190,31 @@ def test_ungraded_group_is_reported():
     say("ungraded group: oct named", bad, "by the oracle", bad_o)
     assert st == L.RG_EUNGRADED == st_o
     assert tree[bad, 3] == 9
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("n", [1, 262144, 262145])
+def test_hash_table(n, noalloc):
+    """Tables on either side of the size from which segments are built in LDS:
+    every key found at its index, others absent, a repeated key reported."""
+    from paper_2607_20704_amd import api, _lib as L
+    ijkl = np.concatenate([I.uniform_tree(7), [[0, 0, 0, 8]]]).astype(np.int32)[:n]
+    hk = O.keys(ijkl).astype(np.int64)
+    keys = torch.as_tensor(hk).cuda().view(torch.uint64)
+
+    def build(k):
+        if not noalloc:
+            return api.hash_build(k)
+        table = torch.empty(api.hash_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+        api.hash_build_noalloc(k, table)
+        return table
+
+    ws = build(keys)
+    assert api.check_ws(ws) == (L.RG_OK, -1)
+    assert np.array_equal(api.hash_lookup(ws, keys).cpu().numpy(), np.arange(n))
+    absent = torch.as_tensor(np.concatenate([8 * hk + 7, [0]])).cuda().view(torch.uint64)
+    assert np.all(api.hash_lookup(ws, absent).cpu().numpy() == -1)
+    if n > 1:
+        hk[n // 2] = hk[5]
+        st, bad = api.check_ws(build(torch.as_tensor(hk).cuda().view(torch.uint64)))
+        assert st == L.RG_EDUPKEY and bad in (5, n // 2)
