@@ -179,6 +179,18 @@ rg_status rg_step(const rg_tree *t, const double *d_uold, double *d_unew, double
     RG_REQUIRE(t->ghost == RG_GHOST_INJECT || t->ghost == RG_GHOST_LINEAR, "bad ghost mode %d", t->ghost);
     RG_REQUIRE(d_uold != d_unew, "uold and unew must not alias");
     RG_REQUIRE(form == RG_FP64 || form == RG_MIXED, "bad form %d", form);
+    RG_REQUIRE(aligned(d_dt, 8), "misaligned dt");
+    if (t->sched) {
+        RG_REQUIRE(t->sched->d_list, "schedule without a list");
+    } else {
+        // no list stands between the ranges and the kernels: what
+        // rg_hydro_step_level asks of every level
+        RG_REQUIRE(t->d_nbr27 && t->d_son_mask, "tree without neighbour lists");
+        RG_REQUIRE(aligned(d_uold, 8) && aligned(d_unew, 8), "misaligned pointer");
+        RG_REQUIRE(t->n_oct <= (int64_t(1) << 28), "bad oct range");
+        for (int l = t->lmin; l <= t->lmax; ++l)
+            RG_REQUIRE(t->level_begin[l + 1] >= t->level_begin[l], "bad oct range of level %d", l);
+    }
     hipStream_t s = as_stream(stream);
     const SinkScope sink(t->d_hash_ws);
     const unsigned prep = flags & (RG_STEP_REBUILD | RG_STEP_REKEY);

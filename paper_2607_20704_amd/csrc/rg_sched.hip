@@ -48,7 +48,8 @@ rg_status hydro_tree_levels(const rg_tree *t, const rg_schedule *sc, int l0, int
                             int corr_mode, const double *d_ucoarse2, bool skip_split)
 {
     RG_REQUIRE(t->ghost == RG_GHOST_INJECT || t->ghost == RG_GHOST_LINEAR, "bad ghost mode %d", t->ghost);
-    RG_REQUIRE(!sc || sc->d_list, "schedule without a list");
+    const bool sched = sc && !(tune && tune->no_bricks);
+    RG_REQUIRE(!sched || sc->d_list, "schedule without a list");
     LevelArgs a;
     a.list = sc ? sc->d_list : nullptr;
     a.uold = d_uold;
@@ -72,7 +73,6 @@ rg_status hydro_tree_levels(const rg_tree *t, const rg_schedule *sc, int l0, int
     LevelTab bricks, groups, octs;
     bricks.n = groups.n = octs.n = 0;
     bricks.owes = groups.owes = octs.owes = 0;
-    const bool sched = sc && !(tune && tune->no_bricks);
     int columns = -1;
     for (int l = l0; l <= l1; ++l) {
         const double dx = ldexp(1.0, -l);
@@ -235,7 +235,7 @@ rg_status rg_hydro_step_scheduled(const rg_tree *t, const rg_schedule *sc, int l
     RG_REQUIRE(gamma > 1, "bad gamma");
     RG_REQUIRE(!d_dt_next || (cfl > 0 && aligned(d_dt_next, 8)), "bad cfl or misaligned dt_next");
     return hydro_tree_levels(t, sc, level, level, d_dt, gamma, d_uold, d_uold, d_unew, cfl, d_dt_next, form, tune,
-                            as_stream(stream), t->d_corr, 0, d_uold, false);
+                             as_stream(stream), t->d_corr, 0, d_uold, false);
 }
 
 }  // extern "C"
