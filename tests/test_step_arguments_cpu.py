@@ -57,3 +57,26 @@ def test_step_with_schedule_refuses_bad_buffers(flags):
     assert _step(t, dt=2052, flags=flags) == L.RG_EINVAL
     assert _step(t, u=8192, flags=flags) == L.RG_EINVAL
     assert _step(t, form=7, flags=flags) == L.RG_EINVAL
+
+
+def _refine(**kw):
+    lib = L.lib()
+    t = _tree()
+    t.capacity = 72
+    t.d_hash_ws, t.hash_ws_bytes = 1 << 16, lib.rg_hash_workspace_bytes(72)
+    t.d_sort_ws, t.sort_ws_bytes = 1 << 17, lib.rg_sort_workspace_bytes(72)
+    t.d_ijkl, t.d_keys_scratch, t.d_perm, t.d_level_begin = 1 << 18, 1 << 19, 1 << 20, 1 << 21
+    for k, v in kw.items():
+        setattr(t, k, v)
+    p = L.RgRefineParams()
+    p.rho_thresh, p.lmax = 1.0, 4
+    return lib.rg_refine(ctypes.byref(t), 1 << 22, 1 << 23, ctypes.byref(p), 1 << 24,
+                         lib.rg_refine_workspace_bytes(72), None)
+
+
+@pytest.mark.parametrize("bad", [{"d_keys": None}, {"d_keys_scratch": 256}, {"d_sort_ws": (1 << 17) + 8},
+                                 {"d_keys_scratch": (1 << 19) + 4}, {"d_hash_ws": (1 << 16) + 8}])
+def test_refine_refuses_bad_buffers(bad):
+    """d_keys_scratch = 256 is d_keys: the new keys would be written over the
+    ones they come from."""
+    assert _refine(**bad) == L.RG_EINVAL
