@@ -416,17 +416,17 @@ rg_status rg_refine(rg_tree *t, const double *d_u, double *d_u_new, const rg_ref
     RG_REQUIRE(t->d_ijkl && t->d_keys_scratch && t->d_perm && t->d_sort_ws && t->d_level_begin && t->d_hash_ws,
                "refinement needs coordinates, scratch keys, permutation, sort workspace, level ranges and hash "
                "workspace");
-    // the old tree's keys are read and the new ones formed in the scratch
-    // keys before they are copied over them
-    RG_REQUIRE(t->d_keys && t->d_keys != t->d_keys_scratch, "refinement needs keys, and scratch keys apart from them");
-    RG_REQUIRE(aligned(t->d_keys, 8) && aligned(t->d_keys_scratch, 8), "misaligned keys");
-    RG_REQUIRE(aligned(t->d_sort_ws, 256) && aligned(t->d_hash_ws, 256), "workspaces must be 256-byte aligned");
     const int64_t cap = t->capacity > 0 ? t->capacity : t->n_oct;
     RG_REQUIRE(cap >= t->n_oct && cap <= (int64_t(1) << 28), "capacity %lld below the oct count",
                static_cast<long long>(cap));
     RG_REQUIRE(ws_bytes >= rg_refine_workspace_bytes(cap) && aligned(d_ws, 256), "refine workspace too small");
     RG_REQUIRE(t->sort_ws_bytes >= rg_sort_workspace_bytes(cap), "sort workspace below capacity");
     RG_REQUIRE(t->hash_ws_bytes >= rg_hash_workspace_bytes(cap), "hash workspace below capacity");
+    // the old tree's keys are read and the new ones formed in the scratch
+    // keys before they are copied over them
+    RG_REQUIRE(t->d_keys && t->d_keys != t->d_keys_scratch, "refinement needs keys, and scratch keys apart from them");
+    RG_REQUIRE(aligned(t->d_keys, 8) && aligned(t->d_keys_scratch, 8), "misaligned keys");
+    RG_REQUIRE(aligned(t->d_sort_ws, 256) && aligned(t->d_hash_ws, 256), "workspaces must be 256-byte aligned");
     hipStream_t s = as_stream(stream);
     const int64_t n = t->n_oct;
     RefineWs w = carve(d_ws, cap);
