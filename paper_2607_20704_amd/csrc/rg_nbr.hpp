@@ -21,10 +21,10 @@ constexpr int kNbrOcts = 9;
 constexpr int kNbrChunk = 32;
 
 // Lists longer than this go by sibling groups.  Both ways cost a launch of
-// latency where the list is short (0.03 M octs of a three-level tree: 13 us
-// one by one, whose chain of loads is the shorter one, 21 us by groups); long
-// lists pay per lookup (0.41 M octs outside the bricks of the clumps of levels
-// 7-11: 262 us one by one, 166 us by groups).
+// latency where the list is short (13400 octs: 13 us one by one, whose chain
+// of loads is the shorter one, 23 us by groups); long lists pay per lookup
+// (45800 octs: 34 us one by one and 33 us by groups; 0.41 M octs outside the
+// bricks of the clumps of levels 7-11: 262 and 166 us).
 constexpr int64_t kNbrByGroups = 40000;
 
 struct NbrTable {

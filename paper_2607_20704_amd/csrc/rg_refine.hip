@@ -489,14 +489,17 @@ rg_status rg_refine(rg_tree *t, const double *d_u, double *d_u_new, const rg_ref
     RG_TRY(rg_hash_build(t->d_keys, m, t->d_hash_ws, t->hash_ws_bytes, stream));
     // neighbour lists brick by brick: the complete bricks follow from the
     // keys; the lists' lengths stay on the device, the grids hold as many as
-    // there could be
+    // there could be.  A complete level of at least 8^3 octs is all bricks.
+    int64_t rest = m;
+    for (int l = 4; l <= 10; ++l)
+        if (lb.at[l + 1] - lb.at[l] == int64_t(1) << (3 * (l - 1))) rest -= lb.at[l + 1] - lb.at[l];
     const size_t core = core_bytes(cap);
     const int32_t *lst = nullptr;
     const uint32_t *d_count = nullptr;
     RG_TRY(nbr_lists_device(t->d_keys, m, t->level_begin, t->lmin, t->lmax, static_cast<char *>(d_ws) + core,
                             ws_bytes - core, &lst, &d_count, s));
     return neighbours_scheduled(t->d_hash_ws, t->d_keys, m, t->lmin, t->lmax, t->level_begin[t->lmax], t->bc, lst,
-                                m / 512, lst, m, t->d_nbr27, t->d_father_cell, t->d_son_mask, s, d_count);
+                                m / 512, lst, rest, t->d_nbr27, t->d_father_cell, t->d_son_mask, s, d_count);
 }
 
 }  // extern "C"

@@ -431,60 +431,60 @@ __global__ void k_hash_lookup(const uint64_t *__restrict__ keys, const int32_t *
     out[i] = key == 0 ? -1 : hash_probe(keys, vals, mask, key);
 }
 
-// `list` (optional) maps positions 0..n-1 to oct indices
-__global__ __launch_bounds__(256) void k_neighbours(const uint64_t *__restrict__ okeys, const int32_t *__restrict__ list,
-                                                    int64_t n, int64_t n_oct, int lmin, int bc, int lmax_zero,
-                                                    HashHeader *hdr, const uint64_t *__restrict__ keys,
-                                                    const int32_t *__restrict__ vals, uint64_t mask,
-                                                    int32_t *__restrict__ nbr27, int32_t *__restrict__ father_cell,
-                                                    uint32_t *__restrict__ son_mask,
-                                                    const uint32_t *__restrict__ counts)
+// octs list[0 .. n) (or 0 .. n without a list), one by one or by sibling groups
+__global__ __launch_bounds__(256) void k_neighbours(NbrTable tab, const int32_t *__restrict__ list, int64_t n)
 {
     __shared__ NbrOcts S;
     const int64_t first = int64_t(blockIdx.x) * kNbrOcts;
-    if (counts) {   // the list's place and length are on the device only
-        list += counts[0];
-        n = counts[1];
-        if (first >= n) return;
-    }
-    const int64_t left = n - first;
-    const NbrTable tab{okeys, hdr, keys, vals, mask, nbr27, father_cell, son_mask, lmin, bc, lmax_zero, n_oct};
-    nbr_each_body(tab, list, first, left < kNbrOcts ? static_cast<int>(left) : kNbrOcts, S);
+    nbr_each_body(tab, list, first, static_cast<int>(min(n - first, int64_t(kNbrOcts))), S);
 }
 
-__global__ __launch_bounds__(256) void k_neighbours_groups(const uint64_t *__restrict__ okeys, const int32_t *__restrict__ list,
-                                                    int64_t n, int64_t n_oct, int lmin, int bc, int lmax_zero,
-                                                    HashHeader *hdr, const uint64_t *__restrict__ keys,
-                                                    const int32_t *__restrict__ vals, uint64_t mask,
-                                                    int32_t *__restrict__ nbr27, int32_t *__restrict__ father_cell,
-                                                    uint32_t *__restrict__ son_mask,
-                                                    const uint32_t *__restrict__ counts)
+__global__ __launch_bounds__(256) void k_neighbours_groups(NbrTable tab, const int32_t *__restrict__ list, int64_t n)
 {
     __shared__ NbrChunk S;
     const int64_t first = int64_t(blockIdx.x) * kNbrChunk;
-    if (counts) {   // the list's place and length are on the device only
-        list += counts[0];
-        n = counts[1];
-        if (first >= n) return;
-    }
-    const int64_t left = n - first;
-    const NbrTable tab{okeys, hdr, keys, vals, mask, nbr27, father_cell, son_mask, lmin, bc, lmax_zero, n_oct};
-    nbr_octs_body(tab, list, first, left < kNbrChunk ? static_cast<int>(left) : kNbrChunk, S);
+    nbr_octs_body(tab, list, first, static_cast<int>(min(n - first, int64_t(kNbrChunk))), S);
 }
 
-rg_status launch_neighbours(const uint64_t *d_keys, const int32_t *list, int64_t n, int64_t n_oct, int lmin, int bc,
-                            int lmax_zero, const HashView &h, int32_t *d_nbr27, int32_t *d_father_cell,
-                            uint32_t *d_son_mask, const uint32_t *d_counts, hipStream_t s)
+// The same where the list's place and length are on the device only: list +
+// counts[0], counts[1] octs.  Which way it goes is decided by that length, as
+// launch_neighbours does on the host (refinement of 0.26 M octs, 554 of them
+// outside complete bricks: by groups, because the whole tree is long, 177 us).
+__global__ __launch_bounds__(256) void k_neighbours_counted(NbrTable tab, const int32_t *__restrict__ list,
+                                                            const uint32_t *__restrict__ counts)
 {
-    const bool groups = n > kNbrByGroups;
-    const int chunk = groups ? kNbrChunk : kNbrOcts;
-    const unsigned blocks = static_cast<unsigned>((n + chunk - 1) / chunk);
-    if (groups)
-        k_neighbours_groups<<<blocks, 256, 0, s>>>(d_keys, list, n, n_oct, lmin, bc, lmax_zero, h.hdr, h.keys, h.vals,
-                                                   h.mask, d_nbr27, d_father_cell, d_son_mask, d_counts);
-    else
-        k_neighbours<<<blocks, 256, 0, s>>>(d_keys, list, n, n_oct, lmin, bc, lmax_zero, h.hdr, h.keys, h.vals,
-                                            h.mask, d_nbr27, d_father_cell, d_son_mask, d_counts);
+    __shared__ union {
+        NbrOcts each;
+        NbrChunk chunk;
+    } S;
+    list += counts[0];
+    const int64_t n = counts[1];
+    const int step = n > kNbrByGroups ? kNbrChunk : kNbrOcts;
+    const int64_t first = int64_t(blockIdx.x) * step;
+    if (first >= n) return;
+    const int count = static_cast<int>(min(n - first, int64_t(step)));
+    if (n > kNbrByGroups) nbr_octs_body(tab, list, first, count, S.chunk);
+    else nbr_each_body(tab, list, first, count, S.each);
+}
+
+unsigned nbr_blocks(int64_t n)
+{
+    const int step = n > kNbrByGroups ? kNbrChunk : kNbrOcts;
+    return static_cast<unsigned>((n + step - 1) / step);
+}
+
+// with d_counts, n is the most the list can hold; any shorter list has a place
+// in the grid too
+rg_status launch_neighbours(const NbrTable &tab, const int32_t *list, int64_t n, const uint32_t *d_counts, hipStream_t s)
+{
+    if (d_counts) {
+        const unsigned few = nbr_blocks(n < kNbrByGroups ? n : kNbrByGroups), all = nbr_blocks(n);
+        k_neighbours_counted<<<few > all ? few : all, 256, 0, s>>>(tab, list, d_counts);
+    } else if (n > kNbrByGroups) {
+        k_neighbours_groups<<<nbr_blocks(n), 256, 0, s>>>(tab, list, n);
+    } else {
+        k_neighbours<<<nbr_blocks(n), 256, 0, s>>>(tab, list, n);
+    }
     return launch_status("neighbours");
 }
 
@@ -528,7 +528,8 @@ rg_status neighbours_scheduled(void *d_ws, const uint64_t *d_keys, int64_t n, in
         RG_TRY(launch_status("brick neighbours"));
     }
     if (nrest > 0) {
-        RG_TRY(launch_neighbours(d_keys, rest, nrest, n, lmin, bc, lmax, h, d_nbr27, d_father_cell, d_son_mask, d_counts, s));
+        const NbrTable tab{d_keys, h.hdr, h.keys, h.vals, h.mask, d_nbr27, d_father_cell, d_son_mask, lmin, bc, lmax, n};
+        RG_TRY(launch_neighbours(tab, rest, nrest, d_counts, s));
     }
     return RG_OK;
 }
@@ -808,8 +809,9 @@ rg_status rg_build_neighbours(void *d_ws, const uint64_t *d_keys, int64_t n, int
     HashView h = hash_view(d_ws, cap);
     hipStream_t s = as_stream(stream);
     RG_TRY(fill_u32(d_son_mask, n, 0u, s));
-    return launch_neighbours(d_keys, nullptr, n, n, lmin, bc, RG_MAX_LEVEL + 1, h, d_nbr27, d_father_cell, d_son_mask,
-                             nullptr, s);
+    const NbrTable tab{d_keys, h.hdr, h.keys, h.vals, h.mask, d_nbr27, d_father_cell, d_son_mask, lmin, bc,
+                       RG_MAX_LEVEL + 1, n};
+    return launch_neighbours(tab, nullptr, n, nullptr, s);
 }
 
 }  // extern "C"

@@ -1,0 +1,44 @@
+"""Neighbour lists of a refined tree, by the length of the list outside the
+complete bricks: none, short in a long tree, and longer than the length from
+which sibling groups serve it; against the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import say
+from oracle import oracle as O
+from paper_2607_20704_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+# (base, finest level, radius, boundary): octs outside complete bricks
+TREES = [
+    ("all_bricks", 6, 6, 0.0, I.PERIODIC, lambda r: r == 0),
+    ("no_brick", 3, 4, 0.3, I.OUTFLOW, lambda r: r > 0),
+    ("short_list_long_tree", 7, 8, 0.04, I.PERIODIC, lambda r: 0 < r < 40000),
+    ("short_list_walls", 6, 8, 0.12, I.OUTFLOW, lambda r: 0 < r < 40000),
+    ("long_list", 6, 9, 0.10, I.PERIODIC, lambda r: r > 40000),
+]
+
+
+@pytest.mark.parametrize("name,base,lmax,radius,bc,rest", TREES, ids=[t[0] for t in TREES])
+def test_lists_after_refinement(name, base, lmax, radius, bc, rest):
+    from paper_2607_20704_amd import api
+    ijkl = I.sphere_tree(base, lmax, (0.3, 0.45, 0.6), radius, bc) if lmax > base else I.uniform_tree(base)
+    D = api.DeviceTree(ijkl, bc, capacity=len(ijkl) + len(ijkl) // 2 + 4096)
+    # cells with children stay flagged: the tree is kept, and grown where the
+    # closure asks for more
+    son = D.son_mask.to(torch.int32)
+    split = ((son[:, None] >> torch.arange(8, device="cuda")[None, :]) & 1).reshape(-1).bool()
+    u = torch.ones((8 * D.n, 5), dtype=torch.float64, device="cuda")
+    u[:, 4] = 2.5
+    u[split, 0] = 3.0
+    D.refine(u, rho_thresh=2.0, lmax=lmax)
+    say("refined:", name, D.n, "octs,", int(D.sched.nbr_rest_count), "outside complete bricks")
+    assert rest(int(D.sched.nbr_rest_count))
+    T = O.Tree(D.ijkl_sorted.cpu().numpy(), bc)
+    assert api.check_ws(D.hash_ws)[0] == 0
+    assert np.array_equal(D.keys.cpu().numpy(), T.keys)
+    assert np.array_equal(D.nbr27.cpu().numpy(), T.nbr27)
+    assert np.array_equal(D.father_cell.cpu().numpy(), T.father_cell)
+    assert np.array_equal(D.son_mask.cpu().numpy(), T.son_mask.astype(np.int32))
