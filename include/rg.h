@@ -99,7 +99,8 @@ enum { RG_BC_PERIODIC = 0, RG_BC_OUTFLOW = 1 };
  * cells, else the coarser cell covering them, C itself across an outflow
  * face), and a fine cell at sub-position s gets ((U_C + q_x slope_x) + q_y
  * slope_y) + q_z slope_z, q = -1/4 for s = 0 and +1/4 for s = 1.  Selected
- * per tree (rg_tree.ghost); rg_hydro_step_level, which has no tree, injects. */
+ * per tree (rg_tree.ghost) for every step of it, with or without a schedule;
+ * rg_hydro_step_level, which has no tree, injects. */
 enum { RG_GHOST_INJECT = 0, RG_GHOST_LINEAR = 1 };
 
 /* Precision forms of the hydro update:
@@ -409,7 +410,8 @@ rg_status rg_schedule_build_device(const rg_tree *t, int32_t *d_list, int64_t ca
  * (one 8x8x8 tile per group; tune->no_groups 1 leaves them to the per-oct
  * kernel), its other octs with the per-oct kernel (the last two also record
  * the coarse-side fluxes in t->d_corr).  Same results, bit for bit, as
- * rg_hydro_step_level over the whole level. */
+ * rg_hydro_step_level over the whole level (with t->ghost RG_GHOST_LINEAR the
+ * coarse ghost cells are interpolated, which that call does not do). */
 rg_status rg_hydro_step_scheduled(const rg_tree *t, const rg_schedule *sched, int level, const double *d_dt,
                                   double gamma, const double *d_uold, double *d_unew, double cfl, double *d_dt_next,
                                   int form, const rg_tuning *tune, void *stream);
@@ -432,9 +434,12 @@ rg_status rg_prepare_tree(const rg_tree *t, unsigned flags, void *stream);
  *   rg_cfl_dt) and the next step's dt is computed from unew inside the level
  *   updates plus rg_cfl_dt_corrected into d_dt[1], saving the separate pass
  *   over the state (so a chain of steps s = 0, 1, ... passes d_dt + s);
- *   every level: rg_hydro_step_scheduled if t->sched is set (one launch per
- *   kernel for all levels), else rg_hydro_step_level over the level (uold ->
- *   unew);
+ *   every level (uold -> unew), its coarse ghost cells filled as t->ghost
+ *   says: rg_hydro_step_scheduled if t->sched is set (one launch per kernel
+ *   for all levels), else the per-oct kernel over the level's octs (what
+ *   rg_hydro_step_level runs, which injects: the same bits where t->ghost is
+ *   RG_GHOST_INJECT).  An oct all of whose cells have child octs is left
+ *   to the restriction;
  *   rg_apply_coarse_corrections over all levels above lmin (in one pass, over
  *   the schedule's border lists when t->sched is set: same bits);
  *   rg_restrict_level from lmax down to lmin + 1 on unew.
