@@ -587,8 +587,12 @@ rg_status rg_mg_residual(const rg_tree *t, const double *d_phi, const double *d_
  * rg_mg_level_create builds the hierarchy of level `level` (coarse keys,
  * their hash table, same-level neighbour lists, father links and masks) in
  * one device allocation owned by the handle; synchronises `stream` once per
- * coarse level.  The handle is valid while t's octs are unchanged (checked:
- * RG_EINVAL otherwise).  Errors: RG_EINVAL for a tree that is not periodic, a
+ * coarse level, once for the number of the level's outer faces and at the end.
+ * The handle is valid while the level's octs are unchanged.  Checked: calls
+ * with it return RG_EINVAL where t's or the level's oct counts have changed,
+ * and rg_mg_level_vcycles records RG_EINVAL in the library's error word
+ * (rg_check(NULL); index: an oct) where they have not but the octs have; its
+ * potential is then of no use.  Errors: RG_EINVAL for a tree that is not periodic, a
  * level outside the tree or without octs, lcoarse outside 1..level;
  * RG_EHIP on allocation failure (nothing is then allocated). */
 typedef struct rg_mg_level rg_mg_level;

@@ -47,6 +47,7 @@ struct rg_mg_level {
     int32_t *slots;                      // [n_wall] oct * 6 + side of every absent face
     int64_t n_wall;
     double *wall;                        // [n_wall][4] potential across the absent faces
+    uint64_t *fine_keys;                 // [n_fine] the level's keys when it was built, if it has absent faces
     int32_t *cface;                      // [n_mg][6] face lists of the coarse levels
     double *zeros;                       // four zeros: the absent faces of the coarse levels
     void *hash_ws;
@@ -122,11 +123,18 @@ __global__ void k_coarse_faces(const int32_t *__restrict__ nbr, int64_t n, int32
 // L-1 at the centre of the cell across face `side` from cell c of oct o.  The
 // neighbour sits in coarse cell F + dv (F the father of o), toward side s of
 // that cell's centre: the 8 coarse cells F + dv + {0, s}^3.
+//
+// The face lists and the coarse levels are those of the octs the hierarchy was
+// built from.  Equal counts do not show that the level still has them, so its
+// keys are compared on the way (a complete level, the only kind without absent
+// faces, has no other octs).
 __global__ void k_fine_walls(const double *__restrict__ phi, const int32_t *__restrict__ nbr27,
                              const int32_t *__restrict__ fcell, const int32_t *__restrict__ slots, int64_t n,
-                             int64_t ob, double *__restrict__ wall)
+                             int64_t ob, double *__restrict__ wall, const uint64_t *__restrict__ keys,
+                             const uint64_t *__restrict__ built, int64_t n_fine, HashHeader *hdr)
 {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (keys && t < n_fine && keys[t] != built[t]) flag_error(hdr, RG_EINVAL, ob + t);
     if (t >= 4 * n) return;
     const int32_t os = slots[t >> 2];
     const int64_t o = ob + os / 6;
@@ -642,7 +650,8 @@ rg_status rg_mg_level_create(const rg_tree *t, int level, int lcoarse, rg_mg_lev
     const bool complete = level <= 10 && n_fine == int64_t(1) << (3 * (level - 1));
     const size_t bytes = al256(nm * 8) + al256(nm * 27 * 4) + al256(nm * 4) + al256(size_t(n_fine) * 4) +
                          4 * al256(nm * 8 * 8) + al256(complete ? size_t(n_fine) * 64 : 0) + al256(size_t(n_fine) * 24) +
-                         al256(size_t(n_wall) * 4) + al256(size_t(n_wall) * 32) + al256(nm * 24) + al256(32) +
+                         al256(size_t(n_wall) * 4) + al256(size_t(n_wall) * 32) +
+                         al256(n_wall ? size_t(n_fine) * 8 : 0) + al256(nm * 24) + al256(32) +
                          al256(hash_bytes);
     hipError_t e = hipMalloc(&h->mem, bytes);
     if (e != hipSuccess) {
@@ -668,6 +677,7 @@ rg_status rg_mg_level_create(const rg_tree *t, int level, int lcoarse, rg_mg_lev
     h->face = reinterpret_cast<int32_t *>(take(size_t(n_fine) * 24));
     h->slots = reinterpret_cast<int32_t *>(take(size_t(n_wall) * 4));
     h->wall = reinterpret_cast<double *>(take(size_t(n_wall) * 32));
+    h->fine_keys = reinterpret_cast<uint64_t *>(take(n_wall ? size_t(n_fine) * 8 : 0));
     h->cface = reinterpret_cast<int32_t *>(take(nm * 24));
     h->zeros = reinterpret_cast<double *>(take(32));
     h->hash_ws = take(hash_bytes);
@@ -682,6 +692,8 @@ rg_status rg_mg_level_create(const rg_tree *t, int level, int lcoarse, rg_mg_lev
         e = hipMemcpyAsync(h->face, face, size_t(n_fine) * 24, hipMemcpyDeviceToDevice, s);
         if (e == hipSuccess && n_wall > 0)
             e = hipMemcpyAsync(h->slots, slots, size_t(n_wall) * 4, hipMemcpyDeviceToDevice, s);
+        if (e == hipSuccess && n_wall > 0)
+            e = hipMemcpyAsync(h->fine_keys, t->d_keys + fb, size_t(n_fine) * 8, hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) st = fail(RG_EHIP, "level multigrid faces: %s", hipGetErrorString(e));
     }
     if (st == RG_OK && n_mg > 0) st = rg_hash_build(h->keys, n_mg, h->hash_ws, hash_bytes, stream);
@@ -724,6 +736,7 @@ rg_status rg_mg_level_create(const rg_tree *t, int level, int lcoarse, rg_mg_lev
         delete h;
         return st;
     }
+    (void)err_sink();   // looked up once per device, so that no later call does it under capture
     *out = h;
     return RG_OK;
 }
@@ -753,8 +766,11 @@ rg_status rg_mg_level_vcycles(rg_mg_level *h, const rg_tree *t, double *d_phi, c
     x.ncoarse = ncoarse;
     x.s = as_stream(stream);
     if (h->n_wall > 0 && ncycles > 0) {
-        k_fine_walls<<<grid_for(4 * h->n_wall, 256), 256, 0, x.s>>>(d_phi, t->d_nbr27, t->d_father_cell, h->slots,
-                                                                   h->n_wall, h->fine_begin, h->wall);
+        const int64_t items = 4 * h->n_wall > h->n_fine ? 4 * h->n_wall : h->n_fine;
+        k_fine_walls<<<grid_for(items, 256), 256, 0, x.s>>>(d_phi, t->d_nbr27, t->d_father_cell, h->slots, h->n_wall,
+                                                            h->fine_begin, h->wall,
+                                                            t->d_keys ? t->d_keys + h->fine_begin : nullptr,
+                                                            h->fine_keys, h->n_fine, current_sink());
         RG_TRY(launch_status("level multigrid walls"));
     }
     for (int c = 0; c < ncycles; ++c) RG_TRY(vfine(x));
