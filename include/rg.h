@@ -540,7 +540,8 @@ rg_status rg_refine(rg_tree *t, const double *d_u, double *d_u_new, const rg_ref
  * periodic.  d_phi, d_f, d_r are per-cell arrays over the whole tree (8
  * n_oct doubles, key order).  On entry d_phi and d_f hold the initial guess
  * and the right-hand side on level lfine (f must have zero mean); the other
- * levels' entries are overwritten.  A V-cycle on level l: nu1 red-black
+ * levels' entries are overwritten, and d_r is work space, apart from the other
+ * two unless lfine == lcoarse.  A V-cycle on level l: nu1 red-black
  * Gauss-Seidel sweeps (a red pass over the cells whose coordinates sum to an
  * even number, then a black pass; phi = (sum of the six neighbours - h^2 f)
  * / 6), the residual r = f - Lap phi, restricted into level l-1's f as the

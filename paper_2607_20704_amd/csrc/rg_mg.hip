@@ -138,19 +138,21 @@ struct Mg {
 // Sweeps over level l >= 4, with prolong after adding the correction of the
 // level below: brick sweeps two by two (they go from phi to r and back; r's
 // entries of the level are free between residuals), the last of an odd number
-// in place, colour by colour.
+// in place, colour by colour.  So are all where r is one of the other two
+// arrays, which a call of sweeps alone (lfine == lcoarse) may pass: it has no
+// residual to put there.
 rg_status smooth(const Mg &m, int l, int sweeps, bool prolong = false)
 {
     const rg_tree *t = m.t;
     const int64_t ob = t->level_begin[l], oe = t->level_begin[l + 1];
-    const int pairs = sweeps & ~1;
+    const int pairs = m.r == m.phi || m.r == m.f ? 0 : sweeps & ~1;
     if (prolong && pairs == 0) {
         k_mg_prolong<<<grid_for(8 * (oe - ob), 256), 256, 0, m.s>>>(m.phi, t->d_nbr27, t->d_father_cell, ob, oe);
         RG_TRY(launch_status("multigrid prolong"));
     }
     RG_TRY(mg_brick_sweeps(m.phi + 8 * ob, m.r + 8 * ob, m.f + 8 * ob,
                            prolong ? m.phi + 8 * t->level_begin[l - 1] : nullptr, l, pairs, m.s));
-    if (sweeps & 1)
+    for (int sw = pairs; sw < sweeps; ++sw)
         for (int colour = 0; colour < 2; ++colour) {
             k_mg_smooth<<<grid_for(4 * (oe - ob), 256), 256, 0, m.s>>>(m.phi, m.f, t->d_nbr27, ob, oe,
                                                                       ldexp(1.0, -2 * l), colour);
