@@ -588,7 +588,7 @@ rg_status rg_mg_residual(const rg_tree *t, const double *d_phi, const double *d_
  * rg_mg_level_create builds the hierarchy of level `level` (coarse keys,
  * their hash table, same-level neighbour lists, father links and masks) in
  * one device allocation owned by the handle; synchronises `stream` once per
- * coarse level, once for the number of the level's outer faces and at the end.
+ * coarse level (at least once) and at the end.
  * The handle is valid while the level's octs are unchanged.  Checked: calls
  * with it return RG_EINVAL where t's or the level's oct counts have changed,
  * and rg_mg_level_vcycles records RG_EINVAL in the library's error word

@@ -22,6 +22,7 @@
 // the fraction m_i / (m_i - m_j) of the way and adds (m_i - m_j) / m_i - 1
 // to the Gauss-Seidel diagonal.  Every value is formed in the same order as
 // in the serial reference so that the results agree bit for bit.
+#include "rg_compact.hpp"
 #include "rg_internal.hpp"
 #include "rg_mg_brick.hpp"
 #include "rg_mg_tail.hpp"
@@ -95,21 +96,34 @@ __device__ __forceinline__ double list_sum6(const double *p, const double *wall,
     return ((((v[0] + v[1]) + v[2]) + v[3]) + v[4]) + v[5];
 }
 
-// face lists of the solved level, with the absent faces counted off
-__global__ void k_fine_faces(const int32_t *__restrict__ nbr27, int64_t ob, int64_t n, int32_t *__restrict__ face,
-                             int32_t *__restrict__ slots, int32_t *count)
+// Face lists of the solved level, with the absent faces counted off (one
+// atomic per workgroup: they all meet on one address), and the level's keys if
+// it has any.  Without a list only their number is wanted.
+__global__ __launch_bounds__(kItems) void k_fine_faces(const int32_t *__restrict__ nbr27,
+                                                       const uint64_t *__restrict__ keys, int64_t ob, int64_t n,
+                                                       int32_t *__restrict__ face, int32_t *__restrict__ slots,
+                                                       uint64_t *__restrict__ fine_keys, int32_t *count)
 {
-    const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t >= 6 * n) return;
+    __shared__ uint32_t s[kItems / 64];
+    __shared__ int32_t first;
+    const int64_t t = int64_t(blockIdx.x) * kItems + threadIdx.x;
     const int64_t o = t / 6;
     const int side = static_cast<int>(t - 6 * o);
-    const int32_t e = nbr27[27 * (ob + o) + 13 + face_step(side)];
-    if (e >= 0) {
-        face[t] = static_cast<int32_t>(e - ob);
-    } else {
-        const int32_t slot = atomicAdd(count, 1);
-        if (slots) slots[slot] = static_cast<int32_t>(t);
+    const int32_t e = t < 6 * n ? nbr27[27 * (ob + o) + 13 + face_step(side)] : 0;
+    const bool absent = e < 0;
+    uint32_t total;
+    const uint32_t rank = block_prefix(absent ? 1u : 0u, s, total);
+    if (threadIdx.x == 0 && total) first = atomicAdd(count, static_cast<int32_t>(total));
+    if (!face) return;
+    __syncthreads();
+    if (t >= 6 * n) return;
+    if (side == 0 && fine_keys) fine_keys[o] = keys[ob + o];
+    if (absent) {
+        const int32_t slot = first + static_cast<int32_t>(rank);
+        slots[slot] = static_cast<int32_t>(t);
         face[t] = -1 - slot;
+    } else {
+        face[t] = static_cast<int32_t>(e - ob);
     }
 }
 
@@ -551,18 +565,29 @@ rg_status check_level(const rg_mg_level *h, const rg_tree *t)
     return RG_OK;
 }
 
-struct TempBufs {
-    std::vector<void *> p;
-    ~TempBufs()
+// scratch of the build
+struct Scratch {
+    char *mem = nullptr;
+    size_t used = 0;
+
+    ~Scratch()
     {
-        for (void *q : p) (void)hipFree(q);
+        if (mem) (void)hipFree(mem);
     }
-    rg_status alloc(void **out, size_t bytes)
+    // without memory yet: adds up the sizes
+    template <typename T> T *take(size_t n)
     {
-        *out = nullptr;
-        hipError_t e = hipMalloc(out, bytes < 256 ? 256 : bytes);
+        char *p = mem ? mem + used : nullptr;
+        used += al256(n * sizeof(T));
+        return reinterpret_cast<T *>(p);
+    }
+    rg_status alloc()
+    {
+        void *p = nullptr;
+        hipError_t e = hipMalloc(&p, used < 256 ? 256 : used);
         if (e != hipSuccess) return fail(RG_EHIP, "level multigrid scratch: %s", hipGetErrorString(e));
-        p.push_back(*out);
+        mem = static_cast<char *>(p);
+        used = 0;
         return RG_OK;
     }
 };
@@ -586,52 +611,64 @@ rg_status rg_mg_level_create(const rg_tree *t, int level, int lcoarse, rg_mg_lev
     RG_REQUIRE(n_fine > 0, "level %d holds no octs", level);
     RG_REQUIRE(n_fine <= (int64_t(1) << 28), "level too large");
     hipStream_t s = as_stream(stream);
-    TempBufs tmp;
-    // coarse octs level by level: parents of the finer list, deduplicated
-    // (K >> 3 keeps key order, so equal parents are adjacent)
-    std::vector<uint64_t *> lists(RG_MAX_LEVEL + 2, nullptr);
-    std::vector<int64_t> counts(RG_MAX_LEVEL + 2, 0);
-    const uint64_t *prev = t->d_keys + fb;
-    int64_t nprev = n_fine;
-    uint64_t *shifted = nullptr;
-    int64_t *d_count = nullptr;
-    RG_TRY(tmp.alloc(reinterpret_cast<void **>(&shifted), size_t(n_fine) * sizeof(uint64_t)));
-    RG_TRY(tmp.alloc(reinterpret_cast<void **>(&d_count), sizeof(int64_t)));
     size_t cub_bytes = 0;
     hipcub::DeviceSelect::Unique(nullptr, cub_bytes, static_cast<const uint64_t *>(nullptr),
                                  static_cast<uint64_t *>(nullptr), static_cast<int64_t *>(nullptr),
                                  static_cast<int>(n_fine), s);
+    // coarse octs level by level: parents of the finer list, deduplicated
+    // (K >> 3 keeps key order, so equal parents are adjacent)
+    std::vector<uint64_t *> lists(RG_MAX_LEVEL + 2, nullptr);
+    std::vector<int64_t> counts(RG_MAX_LEVEL + 2, 0);
+    // Two allocations: the first list of parents is as long as the level at
+    // most, the others as that list (0.97 M octs, whole build: 840 us; 1107 with
+    // one allocation and every list as long as the level)
+    Scratch tmp, rest;
+    uint64_t *shifted = nullptr, *parents = nullptr;
+    int64_t *d_count = nullptr;   // octs of the level below; outer faces of the level, counted and counted off
     void *cub_tmp = nullptr;
-    RG_TRY(tmp.alloc(&cub_tmp, cub_bytes));
+    for (int pass = 0; pass < 2; ++pass) {
+        shifted = tmp.take<uint64_t>(n_fine);
+        parents = tmp.take<uint64_t>(n_fine);
+        d_count = tmp.take<int64_t>(3);
+        cub_tmp = tmp.take<char>(cub_bytes);
+        if (pass == 0) RG_TRY(tmp.alloc());
+    }
+    int64_t h_count[2] = {0, 0};
+    auto read_counts = [&]() -> rg_status {
+        hipError_t e = hipMemcpyAsync(h_count, d_count, sizeof(h_count), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return fail(RG_EHIP, "level multigrid: counts: %s", hipGetErrorString(e));
+        return RG_OK;
+    };
+    RG_TRY(fill_u64(reinterpret_cast<uint64_t *>(d_count), 3, 0u, s));
+    k_fine_faces<<<grid_for(6 * n_fine, kItems), kItems, 0, s>>>(t->d_nbr27, t->d_keys, fb, n_fine, nullptr,
+                                                                nullptr, nullptr,
+                                                                reinterpret_cast<int32_t *>(d_count + 1));
+    RG_TRY(launch_status("level multigrid faces"));
+    const uint64_t *prev = t->d_keys + fb;
+    int64_t nprev = n_fine;
     for (int m = level - 1; m >= lcoarse; --m) {
+        if (m == level - 1) {
+            lists[m] = parents;
+        } else if (m == level - 2) {
+            for (int pass = 0; pass < 2; ++pass) {
+                for (int k = m; k >= lcoarse; --k) lists[k] = rest.take<uint64_t>(nprev);
+                if (pass == 0) RG_TRY(rest.alloc());
+            }
+        }
         k_shift3<<<grid_for(nprev, 256), 256, 0, s>>>(prev, nprev, shifted);
         RG_TRY(launch_status("level multigrid parent keys"));
-        RG_TRY(tmp.alloc(reinterpret_cast<void **>(&lists[m]), size_t(nprev) * sizeof(uint64_t)));
         size_t cb = cub_bytes;
         if (hipcub::DeviceSelect::Unique(cub_tmp, cb, shifted, lists[m], d_count, static_cast<int>(nprev), s) !=
             hipSuccess)
             return fail(RG_EHIP, "level multigrid: unique parents");
-        int64_t c = 0;
-        hipError_t e = hipMemcpyAsync(&c, d_count, sizeof(c), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return fail(RG_EHIP, "level multigrid: parent count: %s", hipGetErrorString(e));
-        counts[m] = c;
+        RG_TRY(read_counts());
+        counts[m] = h_count[0];
         prev = lists[m];
-        nprev = c;
+        nprev = counts[m];
     }
-    // face lists of the level, absent faces counted off
-    int32_t *face = nullptr, *slots = nullptr, n_wall = 0;
-    RG_TRY(tmp.alloc(reinterpret_cast<void **>(&face), size_t(n_fine) * 24));
-    RG_TRY(tmp.alloc(reinterpret_cast<void **>(&slots), size_t(n_fine) * 24));
-    RG_TRY(fill_u32(reinterpret_cast<uint32_t *>(d_count), 1, 0u, s));
-    k_fine_faces<<<grid_for(6 * n_fine, 256), 256, 0, s>>>(t->d_nbr27, fb, n_fine, face, slots,
-                                                          reinterpret_cast<int32_t *>(d_count));
-    RG_TRY(launch_status("level multigrid faces"));
-    {
-        hipError_t e = hipMemcpyAsync(&n_wall, d_count, sizeof(n_wall), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return fail(RG_EHIP, "level multigrid faces: %s", hipGetErrorString(e));
-    }
+    if (level == lcoarse) RG_TRY(read_counts());
+    const int64_t n_wall = h_count[1];
     rg_mg_level *h = new rg_mg_level();
     h->level = level;
     h->lcoarse = lcoarse;
@@ -689,12 +726,10 @@ rg_status rg_mg_level_create(const rg_tree *t, int level, int lcoarse, rg_mg_lev
         }
     if (st == RG_OK) st = fill(h->zeros, 0, 4, 0.0, s);
     if (st == RG_OK) {
-        e = hipMemcpyAsync(h->face, face, size_t(n_fine) * 24, hipMemcpyDeviceToDevice, s);
-        if (e == hipSuccess && n_wall > 0)
-            e = hipMemcpyAsync(h->slots, slots, size_t(n_wall) * 4, hipMemcpyDeviceToDevice, s);
-        if (e == hipSuccess && n_wall > 0)
-            e = hipMemcpyAsync(h->fine_keys, t->d_keys + fb, size_t(n_fine) * 8, hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) st = fail(RG_EHIP, "level multigrid faces: %s", hipGetErrorString(e));
+        k_fine_faces<<<grid_for(6 * n_fine, kItems), kItems, 0, s>>>(
+            t->d_nbr27, t->d_keys, fb, n_fine, h->face, h->slots, n_wall ? h->fine_keys : nullptr,
+            reinterpret_cast<int32_t *>(d_count + 2));
+        st = launch_status("level multigrid faces");
     }
     if (st == RG_OK && n_mg > 0) st = rg_hash_build(h->keys, n_mg, h->hash_ws, hash_bytes, stream);
     if (st == RG_OK && n_mg > 0) {
