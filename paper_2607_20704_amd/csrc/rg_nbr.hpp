@@ -153,8 +153,14 @@ __device__ __forceinline__ void nbr_each_body(const NbrTable &T, const int32_t *
 }
 
 struct NbrChunk {
-    uint64_t lead_key[kNbrChunk], loose_key[kNbrChunk];
-    int32_t lead[kNbrChunk], loose[kNbrChunk];   // first octs of complete sibling groups; other octs
+    struct Oct {
+        int4 c;          // coordinates and level
+        uint64_t key;
+        int32_t o;
+    };
+    uint64_t lead_key[kNbrChunk];        // first octs of complete sibling groups
+    int32_t lead[kNbrChunk];
+    Oct loose[kNbrChunk];                // other octs
     int32_t nlead, nloose;
     int32_t slot[4][64];                 // per wave: the 4^3 octs around a group
     int32_t place[4][8];                 // slot of the group's m-th oct
@@ -166,7 +172,10 @@ struct NbrChunk {
 // lane, and expands the eight lists from them, where octs one at a time probe
 // the table 8 x 26 times.  A group's father has eight children, so its son
 // mask is stored whole.  A group that straddles two chunks belongs to the one
-// holding its first oct.  Other octs take half a wave each.
+// holding its first oct.  Other octs take half a wave each; their keys are
+// decoded by the lane that reads them.  With every lane of an oct decoding for
+// itself scattered octs took longer here than one by one (0.047 M of them 38
+// against 33 us, 0.10 M 69 against 60; now 33 and 59).
 __device__ __forceinline__ void nbr_octs_body(const NbrTable &T, const int32_t *__restrict__ list, int64_t first,
                                               int count, NbrChunk &S)
 {
@@ -201,8 +210,12 @@ __device__ __forceinline__ void nbr_octs_body(const NbrTable &T, const int32_t *
             S.lead_key[__popcll(ml & below)] = k;
         }
         if (loose) {
-            S.loose[__popcll(mo & below)] = static_cast<int32_t>(o);
-            S.loose_key[__popcll(mo & below)] = k;
+            NbrChunk::Oct &to = S.loose[__popcll(mo & below)];
+            int32_t i, j, kk, l;
+            key_coords(k, i, j, kk, l);
+            to.c = make_int4(i, j, kk, l);
+            to.key = k;
+            to.o = static_cast<int32_t>(o);
         }
         if (t == 0) {
             S.nlead = __popcll(ml);
@@ -259,10 +272,9 @@ __device__ __forceinline__ void nbr_octs_body(const NbrTable &T, const int32_t *
     const int half = t >> 5, slot = t & 31;
     for (int g = half; g < S.nloose; g += 8) {
         if (slot >= 27) continue;
-        const int64_t o = S.loose[g];
-        int32_t i, j, k, l;
-        const uint64_t key = S.loose_key[g];
-        key_coords(key, i, j, k, l);
+        const int64_t o = S.loose[g].o;
+        const uint64_t key = S.loose[g].key;
+        const int32_t i = S.loose[g].c.x, j = S.loose[g].c.y, k = S.loose[g].c.z, l = S.loose[g].c.w;
         int32_t ni = i + slot % 3 - 1, nj = j + (slot / 3) % 3 - 1, nk = k + slot / 9 - 1;
         const uint64_t kn = nbr_key(T, ni, nj, nk, l);
         const int32_t e = nbr_find(T, slot != 13 ? kn : (l > T.lmin ? key >> 3 : 0));

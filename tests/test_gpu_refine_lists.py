@@ -1,6 +1,7 @@
-"""Neighbour lists of a refined tree, by the length of the list outside the
-complete bricks: none, short in a long tree, and longer than the length from
-which sibling groups serve it; against the oracle's."""
+"""Neighbour lists by the length of the list outside the complete bricks, after
+a refinement: none, short in a long tree, and longer than the length from which
+sibling groups serve it; and of scattered octs, where that long list holds few
+complete groups.  Against the oracle's."""
 import numpy as np
 import pytest
 import torch
@@ -42,3 +43,25 @@ def test_lists_after_refinement(name, base, lmax, radius, bc, rest):
     assert np.array_equal(D.nbr27.cpu().numpy(), T.nbr27)
     assert np.array_equal(D.father_cell.cpu().numpy(), T.father_cell)
     assert np.array_equal(D.son_mask.cpu().numpy(), T.son_mask.astype(np.int32))
+
+
+@pytest.mark.parametrize("schedule", [True, False])
+@pytest.mark.parametrize("share,bc", [(0.18, I.PERIODIC), (0.4, I.OUTFLOW), (0.95, I.PERIODIC)])
+def test_lists_of_scattered_octs(share, bc, schedule):
+    """Cells of a complete level split at random."""
+    from paper_2607_20704_amd import api
+    base = 6
+    cells = np.stack(np.meshgrid(*[np.arange(1 << base)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    cells = cells[np.random.default_rng(17).random(len(cells)) < share]
+    fine = np.concatenate([cells, np.full((len(cells), 1), base + 1)], 1)
+    ijkl = np.ascontiguousarray(np.concatenate([I.uniform_tree(base), fine]).astype(np.int32))
+    D = api.DeviceTree(ijkl, bc, schedule=schedule)
+    T = O.Tree(ijkl, bc)
+    assert len(fine) > 40000
+    for again in range(2):
+        say("scattered:", len(ijkl), "octs, share", share, "again" if again else "")
+        assert api.check_ws(D.hash_ws)[0] == 0
+        assert np.array_equal(D.nbr27.cpu().numpy(), T.nbr27)
+        assert np.array_equal(D.father_cell.cpu().numpy(), T.father_cell)
+        assert np.array_equal(D.son_mask.cpu().numpy(), T.son_mask.astype(np.int32))
+        D.prepare(api.L.RG_STEP_REBUILD)
