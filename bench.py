@@ -419,7 +419,7 @@ def time_dynamic(api, inputs):
     out["deep_amr_refine"] = {
         "octs_per_pass": octs, "refine_ms": round(min(refine_ms), 3), "schedule_ms": round(min(sched_ms), 3),
         "host_schedule_ms": round(host_sched_ms, 1), "hydro_step_ms": round(step_ms, 3),
-        "note": "refine = flags, closure, new oct list, key sort, state gather, level ranges, hash, neighbours"}
+        "note": "refine = flags, closure, new oct list, state gather, level ranges, hash, neighbours"}
     del bufs, full, u, a, D
     torch.cuda.empty_cache()
 
@@ -781,8 +781,8 @@ def main():
 
     def roof(r, f):
         achieved = ALG_BYTES_PER_CELL * cells / (r["hydro_kernel_ms"] * 1e-3) / 1e9
-        # the box is a complete periodic level: its bricks go two by two
-        # along z unless the chosen variant turns that off
+        # the box is a complete level: it is swept by columns unless the chosen
+        # variant turns that off
         single = r["tune"] is not None and len(r["tune"]) > 7 and r["tune"][7]
         kernel = "k_hydro_brick" if single else "k_hydro_column"
         return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -627,11 +627,12 @@ rg_status rg_mg_level_destroy(rg_mg_level *h);
 /* The per-step phases of Table 1 (compute dt, godunov, set unew, upload) for
  * many independent trees at once.  This batched form is an addition of this
  * library, not a scheme of the paper: it fills the GPU with many small
- * boxes, each keeping its own time step.  Each phase of a step is one
- * persistent kernel looping over a work list that spans every tree: hash
+ * boxes, each keeping its own time step.  Each phase of a step is one kernel
+ * over a work list that spans every tree (the hydro update one workgroup per
+ * item unless tune->persistent asks for loops): hash
  * rebuild and neighbour lists (with RG_STEP_REBUILD), CFL dt per tree, the
  * hydro update of every level of every tree (bricks and per-oct groups as in
- * the tree's schedule), the coarse-fine corrections (six passes), and the
+ * the tree's schedule), the coarse-fine corrections (one pass), and the
  * restriction (one pass per depth below each tree's finest level).  The
  * phases of all `nsteps` steps are captured into one HIP graph.
  *

@@ -2,9 +2,10 @@
 //
 // Every phase of a step (hash rebuild, neighbour lists, CFL dt per tree,
 // hydro update of all trees and levels, coarse-fine corrections,
-// restriction) is one persistent kernel that loops over a list of work
-// items spanning all trees; the phases of all steps are captured once into
-// a HIP graph, so a whole run is one hipGraphLaunch.  Each tree keeps its
+// restriction) is a kernel over a list of work items spanning all trees: the
+// hydro update one workgroup per item (or, if the tuning asks for it, a
+// persistent loop), the others persistent loops; the phases of all steps are
+// captured once into a HIP graph, so a whole run is one hipGraphLaunch.  Each tree keeps its
 // own time step (dt is a per-tree device slot).  The per-item work is the
 // same device code as the single-tree kernels (rg_oct.hpp, rg_sib.hpp,
 // rg_brick.hpp, rg_nbr.hpp), so a tree gives the same bits whether run alone
@@ -159,8 +160,10 @@ __device__ __forceinline__ double level_dx(int level)
 }
 
 // FP64 bricks keep each column's state in registers (two waves per SIMD);
-// mixed bricks read it again, at three waves: at four the loop spilled (72
-// scratch loads), and the 64-box graph took 38.0 ms against 35.2 ms at three.
+// mixed bricks read it again, at three waves: kept there, an earlier persistent
+// loop gave wrong folded time steps (denormal values), whose cause was not
+// found.  At four waves that loop spilled (72 scratch loads; 38.0 ms for the 64
+// boxes against 35.2 at three, when one workgroup per item did not exist yet).
 template <typename R, bool P>
 __global__ __launch_bounds__(BT, sizeof(R) == 8 ? 2 : 3) void k_batch_bricks(const BTree *__restrict__ trees,
                                                                             const Item *__restrict__ items,

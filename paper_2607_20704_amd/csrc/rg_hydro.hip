@@ -234,9 +234,10 @@ template <typename R> rg_status launch_form(const LevelArgs &a, const LevelTab &
 {
     // Mixed without interpolated ghosts, whose registers and LDS are few: 96
     // reconstructions and 108 faces of 3 octs fill 128 threads better than the
-    // 128 and 144 of 4 octs fill 256 (clumps of levels 7-11: 551 against 563
-    // us, a 256^3 box by octs 1563 against 1744).  Few octs take what ends
-    // sooner (3224 of them: 4).  FP64 (831 us either way) and interpolated
+    // 128 and 144 of 4 octs fill 256 (52600 octs: 52 against 57 us; 9200: 18.5
+    // against 19.8; a 256^3 box by octs 1563 against 1744).  Few octs end
+    // sooner with 4, or as soon (6500: 17.2 and 17.3 us; 3300: 15.0 and 14.8).
+    // FP64 (831 us either way) and interpolated
     // ghosts (mixed 678 against 661) keep 4.
     const bool three = sizeof(R) == 4 && !a.ghost && tab_items(lv) > 8192 &&
                        !(tune && (tune->octs_per_group || tune->threads));

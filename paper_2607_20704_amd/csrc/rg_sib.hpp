@@ -117,8 +117,10 @@ __device__ __forceinline__ int side_slot(int ax, int hi)
     return nslot(ax == 0 ? d : 0, ax == 1 ? d : 0, ax == 2 ? d : 0);
 }
 
-// Workgroup size: FP64, whose five groups per compute unit are LDS-bound, one
-// stencil cell per thread; mixed four waves, one per SIMD (clumps of levels
+// Workgroup size: FP64 one stencil cell per thread, 69 registers: seven waves
+// per SIMD, 28 on a compute unit, hold five workgroups (a sixth needs 30), and
+// so does the LDS (32.4 KB each), so that easing one alone gains nothing; 256
+// threads take 84 registers; mixed four waves, one per SIMD (clumps of levels
 // 7-11, one step: FP64 830 us at 320 threads, 840 at 256; mixed 634 and 562;
 // with interpolated ghosts FP64 947 and 966, mixed 719 and 662).
 __host__ __device__ constexpr int sib_threads(bool fp64) { return fp64 ? 320 : 256; }
@@ -158,7 +160,8 @@ __device__ __forceinline__ uint32_t sib_mask_at(const uint32_t *sm, int x, int y
 
 // What bounds it: latency and issue, not memory.  A group takes about 12 us
 // from its first load to its last store, most of it waiting for dependent
-// loads and barriers, and the chip holds as many groups as their LDS allows.
+// loads and barriers, and the chip holds as many groups as their LDS and
+// registers allow.
 // Of 3200 VALU instructions per FP64 group 1400 are the scheme's arithmetic;
 // the rest was index arithmetic, three divergent passes over the axes for
 // cells of the face layer, which have one state each, and tests for walls,
