@@ -26,6 +26,9 @@
 //     4.2 M     27    310    59     309   206           299   205
 //     16.8 M    27    848   177     847   712           815   715
 //     16.8 M    30    827   190     830   763           814   761
+#include <algorithm>
+#include <utility>
+
 #include "rg_internal.hpp"
 
 namespace rg {
@@ -40,7 +43,9 @@ constexpr int kGroupTiles = 64;    // tiles whose counts are added up as they ar
 struct SortArgs {
     uint32_t *unsorted;       // some neighbouring keys are out of order
     uint32_t *cnt;            // [tile][digit]
-    uint32_t *sum;            // [group of kGroupTiles tiles][digit]
+    uint32_t *sum;            // [group of kGroupTiles tiles][digit], zero before the pass
+    uint32_t *next_sum;       // the next pass's, cleared by this one's scatter
+    uint32_t nsum;            // words of either
     const uint64_t *src;
     const int32_t *val;       // nullptr in the first pass: the index itself
     uint64_t *dst;
@@ -55,11 +60,11 @@ struct SortArgs {
 __global__ void k_rekey_begin(uint32_t *unsorted) { *unsorted = 0; }
 
 // Thread 0 of a workgroup holds the key before the workgroup's own 255.  sum:
-// the group counts of all passes, cleared here for the sort.
+// the group counts, cleared here for the sort.
 __global__ __launch_bounds__(256) void k_rekey(const int32_t *__restrict__ ijkl, int64_t n, uint64_t mask,
                                                uint64_t *__restrict__ keys, uint64_t *__restrict__ out,
                                                int32_t *__restrict__ perm, uint32_t *unsorted,
-                                               uint32_t *__restrict__ sum, int nsum)
+                                               uint32_t *__restrict__ sum, uint32_t nsum)
 {
     __shared__ uint64_t s[256];
     const int t = threadIdx.x;
@@ -204,6 +209,7 @@ template <int BITS, int ROUNDS> __global__ __launch_bounds__(kSortT) void k_reke
     } stage;
     __shared__ uint32_t keys_here;
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    for (uint32_t i = tile * kSortT + t; i < a.nsum; i += a.tiles * kSortT) a.next_sum[i] = 0;
     // per digit: all tiles' counts, and those of the tiles before this one
     const uint32_t group = tile / kGroupTiles, groups = (a.tiles + kGroupTiles - 1) / kGroupTiles;
     uint32_t total[E] = {}, start[E] = {};
@@ -330,8 +336,17 @@ uint32_t tiles_of(int64_t n)
     return static_cast<uint32_t>((n + tile - 1) / tile);
 }
 
+// Tiles that the workspace has tables for: at least as many as any smaller n
+// has, although the tiles become fewer where they become larger.
+uint32_t table_tiles(int64_t n)
+{
+    if (n <= kFewKeys) return tiles_of(n);
+    const int64_t one_part = int64_t(kManyRounds) * kSortT * kMaxTiles;
+    return n > one_part ? kMaxTiles : std::max(tiles_of(kFewKeys), tiles_of(n));
+}
+
 // words of one pass's group counts
-uint32_t sums_of(int64_t n) { return (tiles_of(n) + kGroupTiles - 1) / kGroupTiles << kMaxBits; }
+uint32_t sums_of(int64_t n) { return (table_tiles(n) + kGroupTiles - 1) / kGroupTiles << kMaxBits; }
 
 template <int BITS> void sort_pass(const SortArgs &a, bool few, hipStream_t s)
 {
@@ -350,8 +365,7 @@ template <int BITS> void sort_pass(const SortArgs &a, bool few, hipStream_t s)
 size_t rekey_workspace_bytes(int64_t n)
 {
     n = n > 0 ? n : 1;
-    return 256 + al((size_t(4) << kMaxBits) * tiles_of(n)) + al(4 * size_t(kMaxPasses) * sums_of(n)) + al(8 * n) +
-           al(4 * n);
+    return 256 + al((size_t(4) << kMaxBits) * table_tiles(n)) + 2 * al(4 * size_t(sums_of(n))) + al(8 * n) + al(4 * n);
 }
 
 // Keys of the octs d_ijkl into d_keys, sorted over their low end_bit bits into
@@ -374,9 +388,12 @@ rg_status rekey(const int32_t *d_ijkl, int64_t n, uint64_t *d_keys, uint64_t *d_
     a.tiles = tiles_of(n);
     a.parts = parts_of(n);
     a.cnt = reinterpret_cast<uint32_t *>(p);
-    p += al((size_t(4) << kMaxBits) * a.tiles);
-    uint32_t *sum = reinterpret_cast<uint32_t *>(p);
-    p += al(4 * size_t(kMaxPasses) * sums_of(n));
+    p += al((size_t(4) << kMaxBits) * table_tiles(n));
+    a.nsum = sums_of(n);
+    a.sum = reinterpret_cast<uint32_t *>(p);
+    p += al(4 * size_t(a.nsum));
+    a.next_sum = reinterpret_cast<uint32_t *>(p);
+    p += al(4 * size_t(a.nsum));
     uint64_t *tmp = reinterpret_cast<uint64_t *>(p);
     p += al(8 * n);
     int32_t *tmp_perm = reinterpret_cast<int32_t *>(p);
@@ -384,8 +401,7 @@ rg_status rekey(const int32_t *d_ijkl, int64_t n, uint64_t *d_keys, uint64_t *d_
     const uint64_t mask = (uint64_t(1) << end_bit) - 1;
     k_rekey_begin<<<1, 1, 0, s>>>(a.unsorted);
     k_rekey<<<static_cast<unsigned>((n + 254) / 255), 256, 0, s>>>(d_ijkl, n, mask, d_keys, d_sorted, d_perm,
-                                                                   a.unsorted, sum,
-                                                                   passes * static_cast<int>(sums_of(n)));
+                                                                   a.unsorted, a.sum, a.nsum);
     RG_TRY(launch_status("rekey"));
     a.src = d_keys;
     a.val = nullptr;
@@ -394,7 +410,6 @@ rg_status rekey(const int32_t *d_ijkl, int64_t n, uint64_t *d_keys, uint64_t *d_
         const bool to_out = ((passes - 1 - k) & 1) == 0;
         a.dst = to_out ? d_sorted : tmp;
         a.dval = to_out ? d_perm : tmp_perm;
-        a.sum = sum + k * sums_of(n);
         a.shift = width * k;
         const int bits = end_bit - a.shift < width ? end_bit - a.shift : width;
         a.dmask = (1u << bits) - 1u;
@@ -403,6 +418,7 @@ rg_status rekey(const int32_t *d_ijkl, int64_t n, uint64_t *d_keys, uint64_t *d_
         RG_TRY(launch_status("rekey sort"));
         a.src = a.dst;
         a.val = a.dval;
+        std::swap(a.sum, a.next_sum);
     }
     return RG_OK;
 }
